@@ -13,6 +13,7 @@
 // and eight K values for lane group l / 16; it receives C[4 (l / 16) + e][l % 16].
 #include <hip/hip_bfloat16.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
@@ -109,99 +110,147 @@ __global__ void __launch_bounds__(256) conv_fwd_kernel(const bf16_t* __restrict_
     }
 }
 
-// The same convolution for Cin = Cout = 32 without an im2col tile: with K
-// ordered (tap, channel), the 32 K values of one MFMA step are the 32 channels
-// of one input pixel, so lane (pixel l % 16, group l / 16) reads its B
-// operand, 8 channels = 16 bytes, straight from the staged input rows.  Block:
-// kTile32 consecutive pixels of one row, 4 waves of 64 (4 groups of 16); LDS
-// holds the three input rows the taps read (kTile32 + 2 dil pixels each, 80-byte
-// pixel stride so the 16 lanes of a read hit distinct banks), filled with
-// 16-byte loads; each lane keeps its 18 weight fragments (9 taps x 2 output
-// tiles) in registers.  Same MFMAs in the same order on the same values as
-// conv_fwd_kernel<32, 32>, so the results are identical.  x (and mask) must be
-// 16-byte aligned.
 constexpr int kTile32 = 256;
-constexpr int kPxStride = 40;  // bf16 per staged pixel (32 used)
 constexpr int kStageW = kTile32 + 2 * kMaxDil;
-constexpr int kRows32 = 4;  // output rows per block (the weight fragments are loaded once)
+constexpr int kRows32 = 4;  // output rows per block of the first layer (the weight fragments are loaded once)
 
-__global__ void __launch_bounds__(256) conv32_fwd_kernel(const bf16_t* __restrict__ x,
-                                                         const bf16_t* __restrict__ mask,
-                                                         const bf16_t* __restrict__ w,
-                                                         const float* __restrict__ bias,
-                                                         bf16_t* __restrict__ y, int H, int W, int dil,
-                                                         int relu) {
-    __shared__ __align__(16) bf16_t rows[3][kStageW * kPxStride];
-    const int x0 = blockIdx.x * kTile32, n = blockIdx.z;
-    const size_t img = (size_t)n * H * W;
-    const int nx = kTile32 + 2 * dil;  // staged pixels per row
+// Raw buffer descriptor of one tensor row (wave-uniform base): a load at an
+// offset at or past `bytes` returns zeros without a memory access, which is
+// the zero padding.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const bf16_t* p, uint32_t bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a) |
+                       ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32);
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), (short)0,
+                                             (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+constexpr int kOutside = 0x7FFFFFF0;  // offset past every row
+
+typedef short v2s __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u8a __attribute__((ext_vector_type(4), aligned(8)));
+
+// v with every bf16 whose mask value is not > 0 (zero, negative, NaN) cleared.
+__device__ __forceinline__ uint4 relu_masked(uint4 v, uint4 m) {
+    const uint32_t mw[4] = {m.x, m.y, m.z, m.w};
+    uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        // the sign of -b & ~b & ~(inf - b) is set for b > 0 that is no NaN
+        const v2s b = __builtin_bit_cast(v2s, mw[h]);
+        const uint32_t neg = __builtin_bit_cast(uint32_t, (v2s)(-b));
+        const uint32_t nan = __builtin_bit_cast(uint32_t, (v2s)((v2s){0x7F80, 0x7F80} - b));
+        vw[h] &= __builtin_bit_cast(uint32_t, (v2s)(__builtin_bit_cast(v2s, neg & ~(mw[h] | nan)) >> 15));
+    }
+    return make_uint4(vw[0], vw[1], vw[2], vw[3]);
+}
+
+// The same convolution for Cin = Cout = 32, with neither an im2col tile nor
+// LDS: with K ordered (tap, channel), the 32 K values of one MFMA step are the
+// 32 channels of one input pixel, so lane (pixel l % 16, group l / 16) needs 16
+// contiguous bytes of it and a wave's operand for one tap is 1 KB of
+// consecutive memory.  A wave takes a column of 16 pixels and walks down R
+// rows: a row's three operands (kx = 0..2) stay in registers for the three
+// output rows that read them, so each output row costs three loads, two rows
+// ahead of their use.  With dilation d the rows of one residue mod d are such a
+// column of their own (row k of phase f is image row f + d k).  The weight rows
+// are dealt to the two output tiles so that a lane ends up with 8 consecutive
+// channels: one 16-byte store per pixel and lane, 1 KB per wave.  Every output is
+// the MFMAs of conv_fwd_kernel<32, 32> in the same order on the same values, so
+// the results are identical.  x (and mask) must be 16-byte aligned.
+// Bound: HBM (128 B per pixel, 192 with the mask): on four 1242 x 375 images
+// 49 us (4.9 TB/s, the rate of a large copy) and 120 us with the mask (357 MB,
+// past the 256 MB of the Infinity Cache), where rows staged in LDS for each of
+// the three output rows that read them took 167 and 190 us.
+template <bool MASK>
+__global__ void __launch_bounds__(256) conv32_column_kernel(const bf16_t* __restrict__ x,
+                                                            const bf16_t* __restrict__ mask,
+                                                            const bf16_t* __restrict__ w,
+                                                            const float* __restrict__ bias,
+                                                            bf16_t* __restrict__ y, int H, int W, int dil,
+                                                            int relu, int R) {
+    constexpr int kAhead = 2, NR = 3 + kAhead;  // rows in flight past the window; rows in registers
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int ln = lane & 15, g = lane >> 4;
-    // weight fragments: output 16 t + ln, tap, channels 8 g .. 8 g + 7 (kept for all rows)
-    v8bf a[2][9];
+    const int c0 = __builtin_amdgcn_readfirstlane(blockIdx.x * 64 + wv * 16);
+    if (c0 >= W) return;
+    const int p = c0 + ln;
+    const int phase = blockIdx.y % dil, k0 = blockIdx.y / dil * R;
+    const int nk = min(R, (H - phase + dil - 1) / dil - k0);
+    if (nk <= 0) return;
+    const size_t img = (size_t)blockIdx.z * H * W;
+    int off[3];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int kx = 0; kx < 3; ++kx) {
+        const int xx = p + (kx - 1) * dil;
+        off[kx] = xx >= 0 && xx < W ? xx * 64 + 16 * g : kOutside;
+    }
+    // tile t, row r holds output channel 8 (r / 4) + 4 t + r % 4
+    v8bf a[2][9];
+    float bz[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int o = 8 * (ln >> 2) + 4 * t + (ln & 3);
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap)
-            a[t][tap] = *reinterpret_cast<const v8bf*>(w + ((size_t)(t * 16 + ln) * 9 + tap) * 32 + 8 * g);
-    for (int rr = 0; rr < kRows32; ++rr) {
-        const int row = blockIdx.y * kRows32 + rr;
-        if (row >= H) break;  // block-uniform
-        __syncthreads();      // the previous row's reads of the staged rows are done
-        // stage: 4 x 16 bytes per pixel, zero outside the image
-        for (int e = threadIdx.x; e < 3 * nx * 4; e += 256) {
-            const int ky = e / (nx * 4), r = e - ky * nx * 4, px = r >> 2, q = r & 3;
-            const int yy = row + (ky - 1) * dil, xx = x0 - dil + px;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (yy >= 0 && yy < H && xx >= 0 && xx < W) {
-                const size_t o = (img + (size_t)yy * W + xx) * 32 + 8 * q;
-                v = *reinterpret_cast<const uint4*>(x + o);
-                if (mask) {
-                    const uint4 m = *reinterpret_cast<const uint4*>(mask + o);
-                    const uint32_t mw[4] = {m.x, m.y, m.z, m.w};
-                    uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+            a[t][tap] = *reinterpret_cast<const v8bf*>(w + ((size_t)o * 9 + tap) * 32 + 8 * g);
 #pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        const uint32_t lo = bf2f((bf16_t)(mw[h] & 0xFFFFu)) > 0.f ? 0x0000FFFFu : 0u;
-                        const uint32_t hi = bf2f((bf16_t)(mw[h] >> 16)) > 0.f ? 0xFFFF0000u : 0u;
-                        vw[h] &= lo | hi;
-                    }
-                    v = make_uint4(vw[0], vw[1], vw[2], vw[3]);
-                }
-            }
-            *reinterpret_cast<uint4*>(&rows[ky][px * kPxStride + 8 * q]) = v;
+        for (int e = 0; e < 4; ++e) bz[t][e] = bias ? bias[8 * g + 4 * t + e] : 0.f;
+    }
+    uint4 f[NR][3], fm[NR][3];  // row k0 - 1 + i in slot i % NR
+    auto load_row = [&](int i, uint4 (&v)[3], uint4 (&m)[3]) {
+        const int yy = phase + dil * (k0 - 1 + i);
+        const bool in = yy >= 0 && yy < H && i <= nk + 1;
+        const size_t row = (img + (size_t)(in ? yy : 0) * W) * 32;
+        const __amdgpu_buffer_rsrc_t rx = row_rsrc(x + row, in ? (uint32_t)W * 64u : 0u);
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+            v[kx] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rx, off[kx], 0, 0));
+        if constexpr (MASK) {
+            const __amdgpu_buffer_rsrc_t rm = row_rsrc(mask + row, in ? (uint32_t)W * 64u : 0u);
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+                m[kx] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rm, off[kx], 0, 0));
         }
-        __syncthreads();
-#pragma unroll 1
-        for (int grp = 0; grp < 4; ++grp) {
-            const int p = wv * 64 + grp * 16 + ln;  // pixel of this lane's B column within the tile
+    };
+    auto ready = [&](uint4 (&v)[3], const uint4 (&m)[3]) {
+        if constexpr (MASK) {
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) v[kx] = relu_masked(v[kx], m[kx]);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < NR - 1; ++i) load_row(i, f[i], fm[i]);
+    ready(f[0], fm[0]);
+    ready(f[1], fm[1]);
+    for (int j0 = 0; j0 < nk; j0 += NR) {
+#pragma unroll
+        for (int u = 0; u < NR; ++u) {
+            const int j = j0 + u;
+            if (j >= nk) return;
+            load_row(j + NR - 1, f[(u + NR - 1) % NR], fm[(u + NR - 1) % NR]);
+            ready(f[(u + 2) % NR], fm[(u + 2) % NR]);
             v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap) {
-                const int ky = tap / 3, kx = tap - 3 * ky;
-                const v8bf bv = *reinterpret_cast<const v8bf*>(&rows[ky][(p + kx * dil) * kPxStride + 8 * g]);
+                const v8bf bv = __builtin_bit_cast(v8bf, f[(u + tap / 3) % NR][tap % 3]);
                 acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][tap], bv, acc[0], 0, 0, 0);
                 acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][tap], bv, acc[1], 0, 0, 0);
             }
-            const int px = x0 + p;
-            if (px < W) {
-                bf16_t* out = y + (img + (size_t)row * W + px) * 32;
+            v4u8a o;
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    uint32_t packed[2];
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        float v0 = acc[t][2 * h] + (bias ? bias[t * 16 + 4 * g + 2 * h] : 0.f);
-                        float v1 = acc[t][2 * h + 1] + (bias ? bias[t * 16 + 4 * g + 2 * h + 1] : 0.f);
-                        if (relu) {
-                            v0 = fmaxf(v0, 0.f);
-                            v1 = fmaxf(v1, 0.f);
-                        }
-                        packed[h] = f2bf2(v0, v1);
+                for (int h = 0; h < 2; ++h) {
+                    float v0 = acc[t][2 * h] + bz[t][2 * h];
+                    float v1 = acc[t][2 * h + 1] + bz[t][2 * h + 1];
+                    if (relu) {
+                        v0 = fmaxf(v0, 0.f);
+                        v1 = fmaxf(v1, 0.f);
                     }
-                    *reinterpret_cast<uint2*>(out + t * 16 + 4 * g) = make_uint2(packed[0], packed[1]);
+                    o[2 * t + h] = f2bf2(v0, v1);
                 }
-            }
+            const int yy = phase + dil * (k0 + j);
+            if (p < W) *reinterpret_cast<v4u8a*>(y + (img + (size_t)yy * W + p) * 32 + 8 * g) = o;
         }
     }
 }
@@ -705,6 +754,23 @@ bool use_conv32(const void* x, const void* mask) {
     return staged_conv_enabled();
 }
 
+void launch_conv32(const bf16_t* x, const bf16_t* mask, const bf16_t* w, const float* bias, bf16_t* y, int n, int H,
+                   int W, int dil, int relu, hipStream_t st) {
+    // Rows per wave: about 4608 waves (one and a half rounds of three waves per
+    // SIMD), so the two halo rows a wave reads on top stay a small share; more,
+    // shorter waves reread more, fewer leave the chip idle at the end (four
+    // 1242 x 375 images: 49 us with 4608 waves, 56 with 3072, 53 with 6144, 60
+    // with 12288).  At least 4 rows where the call is too small to fill the chip.
+    const size_t rows = (size_t)((W + 15) / 16) * n * H;  // 16-pixel rows
+    const int R = (int)std::min<size_t>(std::max<size_t>(rows / 4608, 4), 64);
+    const int hp = (H + dil - 1) / dil;
+    const dim3 grid((W + 63) / 64, dil * ((hp + R - 1) / R), n);
+    if (mask)
+        hipLaunchKernelGGL((conv32_column_kernel<true>), grid, dim3(256), 0, st, x, mask, w, bias, y, H, W, dil, relu, R);
+    else
+        hipLaunchKernelGGL((conv32_column_kernel<false>), grid, dim3(256), 0, st, x, mask, w, bias, y, H, W, dil, relu, R);
+}
+
 size_t wgrad_part_bytes(int n, int H, int W, int cin, int cout) {
     const size_t nblk = (size_t)((W + kTilePx - 1) / kTilePx) * ((H + kWgRows - 1) / kWgRows) * n;
     const int cpad = (cin + 15) / 16 * 16;
@@ -731,8 +797,7 @@ extern "C" sff_status sff_conv3x3_bf16_fwd(int32_t n, int32_t H, int32_t W, int3
         hipLaunchKernelGGL((conv_fwd_kernel<3, 32>), grid, dim3(256), 0, st, x, nullptr, w, bias, y,
                            H, W, dil, relu);
     else if (use_conv32(x, nullptr))
-        hipLaunchKernelGGL(conv32_fwd_kernel, dim3((W + kTile32 - 1) / kTile32, (H + kRows32 - 1) / kRows32, n), dim3(256), 0, st, x,
-                           nullptr, w, bias, y, H, W, dil, relu);
+        launch_conv32(x, nullptr, w, bias, y, n, H, W, dil, relu, st);
     else
         hipLaunchKernelGGL((conv_fwd_kernel<32, 32>), grid, dim3(256), 0, st, x, nullptr, w, bias,
                            y, H, W, dil, relu);
@@ -762,8 +827,7 @@ extern "C" sff_status sff_conv3x3_bf16_dgrad(int32_t n, int32_t H, int32_t W, in
     hipLaunchKernelGGL(flip_weights_kernel, dim3((cin * 9 * cout + 255) / 256), dim3(256), 0, st, w,
                        wt, cin, cout);
     if (use_conv32(dy, relu_out))
-        hipLaunchKernelGGL(conv32_fwd_kernel, dim3((W + kTile32 - 1) / kTile32, (H + kRows32 - 1) / kRows32, n), dim3(256), 0, st, dy,
-                           relu_out, wt, nullptr, dx, H, W, dil, 0);
+        launch_conv32(dy, relu_out, wt, nullptr, dx, n, H, W, dil, 0, st);
     else
         hipLaunchKernelGGL((conv_fwd_kernel<32, 32>), dim3((W + kTilePx - 1) / kTilePx, H, n), dim3(256),
                            0, st, dy, relu_out, wt, nullptr, dx, H, W, dil, 0);
