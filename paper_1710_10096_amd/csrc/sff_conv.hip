@@ -339,197 +339,285 @@ __global__ void flip_weights_kernel(const bf16_t* __restrict__ w, bf16_t* __rest
 }
 
 // ------------------------------------------------------------ weight grad --
-// Block: a 64-pixel-wide band of kWgRows rows.  For every row segment the
-// block stages dz^T [COUT][64] and, for each kernel row, the input row
-// transposed [CIN][64 + 2 d] in LDS; wave t accumulates the (o-tile, i-tile)
-// pair t for all 9 taps (K = pixels).  Partial results per block are reduced
-// in a fixed order by a second kernel.
-constexpr int kWgRows = 32;  // 960 blocks on four KITTI-size images: 1.3% faster per training step than 16; 8 and 64 slower
+// dW[o][tap][i] = sum over pixels: the K dimension of the MFMAs is 32
+// consecutive pixels of one row, so both operands are needed transposed
+// (channel-major), while memory holds the channels of a pixel together.  A wave
+// takes a column of 32 pixels and walks down R rows (with dilation d: rows of
+// one residue mod d).  Per row it puts the 32 + 2 d input pixels and the 32
+// pixels of dz = dy (masked by the ReLU) into its own LDS slice as they come
+// (16-byte writes) and reads them back through the transposing LDS load
+// (ds_read_b64_tr_b16: 16 lanes read 4 pixels x 16 channels and lane i gets
+// channel i of the 4 pixels).  The operand of an input row serves the three
+// kernel rows at once: dz of the three output rows around it is kept in
+// registers, so a row is staged and read once (16 transposing reads for 36
+// MFMAs), and the whole 32 x 288 gradient is accumulated in the wave's
+// registers.  The waves of a block are added in order at the end, the blocks by
+// wgrad_reduce_kernel.  For Cin = 3 the staged row holds the 9 (kx, channel)
+// values of each pixel, padded to 16.  The bias gradient is dz times a matrix of
+// ones.  Global loads run one row ahead.
+// Bound: HBM (192 B per pixel with the mask: 357 MB on four 1242 x 375 images,
+// 73 us at the rate of a large copy).  There, with dy and its mask one tensor
+// (238 MB): 50 us for Cin = 32 and 37 us for Cin = 3, against 328 and 270 us for
+// blocks that scattered every row transposed into LDS in 2-byte writes, three
+// times over.
+constexpr int kWgPx = 32, kWgWaves = 8;
+constexpr int kWgXPx = kWgPx + 2 * kMaxDil;                  // staged input pixels, at most
+constexpr int kWgSlice = kWgXPx * 32 + kWgPx * 32;           // bf16 of one wave: input row, dz row
+constexpr int kWgRedTiles = 6;                               // accumulator tiles summed at a time
+template <int CIN>
+constexpr int kWgTiles = CIN == 32 ? 36 : 6;  // (ot, it, tap) or (ot, ky) tiles of 16 x 16
 
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) conv_wgrad_kernel(const bf16_t* __restrict__ x,
-                                                         const bf16_t* __restrict__ dy,
-                                                         const bf16_t* __restrict__ mask,
-                                                         float* __restrict__ part, int H, int W,
-                                                         int dil, int vec) {
-    constexpr int IT = (CIN + 15) / 16, OT = COUT / 16, XW = kTilePx + 2 * kMaxDil;
-    __shared__ __align__(16) bf16_t dzT[COUT][kTilePx];
-    __shared__ __align__(16) bf16_t xT[3][IT * 16][XW];
-    __shared__ float dbs[4][COUT];
-    const int x0 = blockIdx.x * kTilePx, r0 = blockIdx.y * kWgRows, n = blockIdx.z;
-    const size_t img = (size_t)n * H * W;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int ln = lane & 15, g = lane >> 4;
-    // wave wv handles pairs wv, wv + 4, ... of the OT x IT (o-tile, i-tile) grid
-    constexpr int NP = OT * IT, PPW = (NP + 3) / 4;
-    v4f acc[PPW][9];
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) bf16_t* lds_bf16;
+
+// 8 K values (pixels px .. px + 7 of the lane's group) of channel c0 + l % 16
+// from a staged row of `stride` bf16 per pixel.
+__device__ __forceinline__ v8bf read_transposed(lds_bf16 row, int px, int c0, int stride) {
+    const int i = threadIdx.x & 15;
+    lds_bf16 p = row + (px + (i >> 2)) * stride + c0 + 4 * (i & 3);
+    struct {
+        v4s lo, hi;
+    } r;
+    r.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
+    r.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p + 4 * stride));
+    return __builtin_bit_cast(v8bf, r);
+}
+
+// 8 bf16 at byte offset off of a row: one 16-byte load, or eight 2-byte ones
+// where the tensor is not 16-byte aligned.
+template <bool VEC>
+__device__ __forceinline__ uint4 load_piece(__amdgpu_buffer_rsrc_t rs, int off) {
+    if constexpr (VEC) {
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+    } else {
+        uint32_t w[4];
 #pragma unroll
-    for (int q = 0; q < PPW; ++q)
-#pragma unroll
-        for (int t = 0; t < 9; ++t) acc[q][t] = v4f{0.f, 0.f, 0.f, 0.f};
-    float db = 0.f;  // thread (wv, lane < COUT) sums dz of channel lane over its pixels
-    for (int rr = 0; rr < kWgRows; ++rr) {
-        const int row = r0 + rr;
-        if (row >= H) break;
-        __syncthreads();
-        bool staged = false;
-        if constexpr (CIN == 32 && COUT == 32) {
-            if (vec) {
-                // 16-byte loads (8 channels of one pixel), scattered transposed into LDS
-                {
-                    const int p = threadIdx.x >> 2, q = threadIdx.x & 3;  // 64 pixels x 4 pieces
-                    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                    if (x0 + p < W) {
-                        const size_t off = (img + (size_t)row * W + x0 + p) * 32 + 8 * q;
-                        v = *reinterpret_cast<const uint4*>(dy + off);
-                        if (mask) {
-                            const uint4 m = *reinterpret_cast<const uint4*>(mask + off);
-                            const uint32_t mw[4] = {m.x, m.y, m.z, m.w};
-                            uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                            for (int h = 0; h < 4; ++h) {
-                                const uint32_t lo = bf2f((bf16_t)(mw[h] & 0xFFFFu)) > 0.f ? 0x0000FFFFu : 0u;
-                                const uint32_t hi = bf2f((bf16_t)(mw[h] >> 16)) > 0.f ? 0xFFFF0000u : 0u;
-                                vw[h] &= lo | hi;
-                            }
-                            v = make_uint4(vw[0], vw[1], vw[2], vw[3]);
-                        }
-                    }
-                    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) dzT[8 * q + t][p] = (bf16_t)(vw[t >> 1] >> (16 * (t & 1)));
-                }
-                for (int e = threadIdx.x; e < 3 * XW * 4; e += 256) {
-                    const int ky = e / (XW * 4), r = e - ky * XW * 4, j = r >> 2, q = r & 3;
-                    const int yy = row + (ky - 1) * dil, xx = x0 - kMaxDil + j;
-                    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                    if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-                        v = *reinterpret_cast<const uint4*>(x + (img + (size_t)yy * W + xx) * 32 + 8 * q);
-                    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) xT[ky][8 * q + t][j] = (bf16_t)(vw[t >> 1] >> (16 * (t & 1)));
-                }
-                staged = true;
-            }
+        for (int h = 0; h < 4; ++h) {
+            const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * h, 0, 0);
+            const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * h + 2, 0, 0);
+            w[h] = (lo & 0xFFFFu) | (hi << 16);
         }
-        if (!staged) {
-            for (int e = threadIdx.x; e < COUT * kTilePx; e += 256) {
-                const int p = e / COUT, o = e - p * COUT;
-                bf16_t v = 0;
-                if (x0 + p < W) {
-                    const size_t off = (img + (size_t)row * W + x0 + p) * COUT + o;
-                    v = dy[off];
-                    if (mask && !(bf2f(mask[off]) > 0.f)) v = 0;
-                }
-                dzT[o][p] = v;
-            }
-            for (int e = threadIdx.x; e < 3 * IT * 16 * XW; e += 256) {
-                const int ky = e / (IT * 16 * XW), r = e - ky * IT * 16 * XW;
-                const int c = r / XW, j = r - c * XW;
-                const int yy = row + (ky - 1) * dil, xx = x0 - kMaxDil + j;
-                bf16_t v = 0;
-                if (c < CIN && yy >= 0 && yy < H && xx >= 0 && xx < W)
-                    v = x[(img + (size_t)yy * W + xx) * CIN + c];
-                xT[ky][c][j] = v;
-            }
-        }
-        __syncthreads();
-        if (lane < COUT) {
-            float s = 0.f;
-            for (int p = wv * 16; p < wv * 16 + 16; ++p) s += bf2f(dzT[lane][p]);
-            db += s;
-        }
-#pragma unroll
-        for (int q = 0; q < PPW; ++q) {
-            const int pair = wv + 4 * q;
-            if (pair >= NP) break;
-            const int ot = pair / IT, it = pair - ot * IT;
-#pragma unroll
-            for (int ks = 0; ks < kTilePx / 32; ++ks) {
-                const v8bf av = *reinterpret_cast<const v8bf*>(&dzT[ot * 16 + ln][ks * 32 + 8 * g]);
-#pragma unroll
-                for (int tap = 0; tap < 9; ++tap) {
-                    const int ky = tap / 3, kx = tap % 3;
-                    const bf16_t* src = &xT[ky][it * 16 + ln][kMaxDil + (kx - 1) * dil + ks * 32 + 8 * g];
-                    v8bf bv;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) bv[e] = __builtin_bit_cast(__bf16, src[e]);
-                    acc[q][tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[q][tap], 0, 0, 0);
-                }
-            }
-        }
-    }
-    // partial layout: [block][COUT][9][IT*16] + db [block][COUT] (after all blocks)
-    const size_t blk = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    float* pw = part + blk * COUT * 9 * IT * 16;
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-        const int pair = wv + 4 * q;
-        if (pair >= NP) break;
-        const int ot = pair / IT, it = pair - ot * IT;
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                pw[((size_t)(ot * 16 + 4 * g + e) * 9 + tap) * IT * 16 + it * 16 + ln] = acc[q][tap][e];
-    }
-    if (lane < COUT) dbs[wv][lane] = db;
-    __syncthreads();
-    if (threadIdx.x < COUT) {
-        const size_t nblk = (size_t)gridDim.x * gridDim.y * gridDim.z;
-        part[nblk * COUT * 9 * IT * 16 + blk * COUT + threadIdx.x] =
-            dbs[0][threadIdx.x] + dbs[1][threadIdx.x] + dbs[2][threadIdx.x] + dbs[3][threadIdx.x];
+        return make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
 
-// Fixed-order sum of the per-block partials: dw [COUT][3][3][CIN], db [COUT].
-// Sum of the per-block partials, in a fixed order: 16 outputs per block, 16
-// threads per output; thread s sums blocks s, s + 16, s + 32, ... with four
-// independent accumulators (their loads in flight together), and the 16
-// segment sums of an output are added in order through LDS.
-constexpr int kRedOut = 16, kRedSeg = 16;
+template <int CIN, bool VEC>
+__global__ void __launch_bounds__(64 * kWgWaves) wgrad_column_kernel(const bf16_t* __restrict__ x,
+                                                                     const bf16_t* __restrict__ dy,
+                                                                     const bf16_t* __restrict__ mask,
+                                                                     float* __restrict__ part, int H, int W, int dil,
+                                                                     int R, int strips, int chunks, int units) {
+    constexpr int NT = kWgTiles<CIN>;
+    constexpr int kRed = kWgWaves * kWgRedTiles * 256;  // floats
+    constexpr int kStage = kWgWaves * kWgSlice / 2;     // floats
+    __shared__ __align__(16) float lds[kRed > kStage ? kRed : kStage];
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    const int g = lane >> 4;
+    v4f acc[NT], accb[2];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+    accb[0] = accb[1] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int unit = blockIdx.x * kWgWaves + wv; unit < units; unit += gridDim.x * kWgWaves) {
+        const int strip = unit % strips, c = unit / strips, n = c / chunks, cy = c % chunks;
+        const int phase = cy % dil, k0 = cy / dil * R, x0 = strip * kWgPx;
+        const int nk = min(R, (H - phase + dil - 1) / dil - k0);
+        const size_t img = (size_t)n * H * W;
+        lds_bf16 xs = (lds_bf16)(lds) + wv * kWgSlice, zs = xs + kWgXPx * 32;
+        constexpr int XP = CIN == 32 ? 4 : 1;  // 16-byte pieces of the input row per lane
+        // byte offsets of this lane's pieces in a row of x and of dy
+        int xo[CIN == 32 ? XP : 8], zo[2];
+        if constexpr (CIN == 32) {
+#pragma unroll
+            for (int k = 0; k < XP; ++k) {
+                const int e = 64 * k + lane, px = e >> 2, xx = x0 - dil + px;
+                xo[k] = px < kWgPx + 2 * dil && xx >= 0 && xx < W ? xx * 64 + 16 * (e & 3) : kOutside;
+            }
+        } else {  // pixel lane / 2, (kx, channel) values 8 (lane & 1) .. + 7
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int e = 8 * (lane & 1) + k, kx = e / 3, xx = x0 + (lane >> 1) + (kx - 1) * dil;
+                xo[k] = e < 9 && xx >= 0 && xx < W ? (xx * 3 + e - 3 * kx) * 2 : kOutside;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int e = 64 * k + lane, xx = x0 + (e >> 2);
+            zo[k] = xx < W ? xx * 64 + 16 * (e & 3) : kOutside;
+        }
+        uint4 xv[XP], zv[2], mv[2];
+        auto load_x = [&](int i) {  // input row i (the window's row of output row i)
+            const int yy = phase + dil * (k0 + i);
+            const bool in = yy >= 0 && yy < H && i <= nk;
+            const __amdgpu_buffer_rsrc_t rs =
+                row_rsrc(x + (img + (size_t)(in ? yy : 0) * W) * CIN, in ? (uint32_t)W * 2u * CIN : 0u);
+            if constexpr (CIN == 32) {
+#pragma unroll
+                for (int k = 0; k < XP; ++k)
+                    if (k < 3 || dil > 8) xv[k] = load_piece<VEC>(rs, xo[k]);
+            } else {
+                uint32_t w[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) w[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, xo[k], 0, 0) & 0xFFFFu;
+                xv[0] = make_uint4(w[0] | w[1] << 16, w[2] | w[3] << 16, w[4] | w[5] << 16, w[6] | w[7] << 16);
+            }
+        };
+        auto load_z = [&](int i) {  // dz row i, zero outside the chunk
+            const bool in = i >= 0 && i < nk;
+            const size_t row = (img + (size_t)(in ? phase + dil * (k0 + i) : 0) * W) * 32;
+            const __amdgpu_buffer_rsrc_t rs = row_rsrc(dy + row, in ? (uint32_t)W * 64u : 0u);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) zv[k] = load_piece<VEC>(rs, zo[k]);
+            if (mask) {
+                const __amdgpu_buffer_rsrc_t rm = row_rsrc(mask + row, in ? (uint32_t)W * 64u : 0u);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) mv[k] = load_piece<VEC>(rm, zo[k]);
+            }
+        };
+        v8bf ones;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+        v8bf dz[3][2];  // dz rows i - 1, i, i + 1 at step i
+#pragma unroll
+        for (int r = 0; r < 3; ++r) dz[r][0] = dz[r][1] = (v8bf)(__bf16)0.0f;
+        load_x(-1);
+        load_z(0);
+        for (int i = -1; i <= nk; ++i) {
+            // the wave's slice is its own; its LDS operations run in order
+            auto put = [&](lds_bf16 p, uint4 v) { *reinterpret_cast<__attribute__((address_space(3))) v4u*>(p) = __builtin_bit_cast(v4u, v); };
+            if constexpr (CIN == 32) {
+#pragma unroll
+                for (int k = 0; k < XP; ++k)
+                    if (k < 3 || dil > 8) put(xs + (64 * k + lane) * 8, xv[k]);
+            } else {
+                put(xs + lane * 8, xv[0]);
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) put(zs + (64 * k + lane) * 8, mask ? relu_masked(zv[k], mv[k]) : zv[k]);
+            load_x(i + 1);
+            load_z(i + 2);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                dz[0][t] = dz[1][t];
+                dz[1][t] = dz[2][t];
+                dz[2][t] = read_transposed(zs, 8 * g, 16 * t, 32);
+                accb[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2][t], ones, accb[t], 0, 0, 0);
+            }
+            // input row i meets output row i + 1 - ky at kernel row ky
+            if constexpr (CIN == 32) {
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                    for (int it = 0; it < 2; ++it) {
+                        const v8bf b = read_transposed(xs, 8 * g + kx * dil, 16 * it, 32);
+#pragma unroll
+                        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+                            for (int ot = 0; ot < 2; ++ot) {
+                                v4f& q = acc[(ot * 2 + it) * 9 + 3 * ky + kx];
+                                q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2 - ky][ot], b, q, 0, 0, 0);
+                            }
+                    }
+            } else {
+                const v8bf b = read_transposed(xs, 8 * g, 0, 16);
+#pragma unroll
+                for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+                    for (int ot = 0; ot < 2; ++ot)
+                        acc[ot * 3 + ky] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2 - ky][ot], b, acc[ot * 3 + ky], 0, 0, 0);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    // sums of the block's waves, in wave order: kWgRedTiles tiles at a time;
+    // partial layout [block][NT + 2 tiles][element][lane] (the last two: dz times ones)
+    float* out = part + (size_t)blockIdx.x * (NT + 2) * 256;
+#pragma unroll
+    for (int t0 = 0; t0 < NT + 2; t0 += kWgRedTiles) {
+        constexpr int N = kWgRedTiles;
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+            if (t0 + t < NT + 2) {
+                const v4f v = t0 + t < NT ? acc[t0 + t < NT ? t0 + t : 0] : accb[t0 + t < NT ? 0 : t0 + t - NT];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) lds[(wv * N + t) * 256 + e * 64 + lane] = v[e];
+            }
+        __syncthreads();
+        const int cnt = min(N, NT + 2 - t0) * 256;
+        for (int e = threadIdx.x; e < cnt; e += 64 * kWgWaves) {
+            float sum = lds[e];
+#pragma unroll
+            for (int k = 1; k < kWgWaves; ++k) sum += lds[k * N * 256 + e];
+            out[t0 * 256 + e] = sum;
+        }
+    }
+}
+
+// Sum of the per-block partials, in a fixed order: 32 accumulator elements per
+// block, 8 threads per element; thread s sums blocks s, s + 8, s + 16, ... with
+// four independent accumulators (their loads in flight together), and the 8
+// segment sums are added in order through LDS.
+constexpr int kRedOut = 32, kRedSeg = 8;
 
 __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* __restrict__ part, float* __restrict__ dw,
-                                                           float* __restrict__ db, int nblk, int cin, int cout,
-                                                           int cpad) {
+                                                           float* __restrict__ db, int nblk, int cin) {
     __shared__ float seg[kRedSeg][kRedOut];
     const int lo = threadIdx.x % kRedOut, sg = threadIdx.x / kRedOut;
-    const int e = blockIdx.x * kRedOut + lo;
-    const int nw = cout * 9 * cin;
-    const bool valid = e < nw + cout;
-    const float* src = part;
-    size_t stride = 0;
-    if (e < nw) {
-        const int o = e / (9 * cin), r = e - o * 9 * cin;
-        const int tap = r / cin, i = r - tap * cin;
-        stride = (size_t)cout * 9 * cpad;
-        src = part + ((size_t)o * 9 + tap) * cpad + i;
-    } else if (valid) {
-        stride = (size_t)cout;
-        src = part + (size_t)nblk * cout * 9 * cpad + (e - nw);
-    }
+    const int e = blockIdx.x * kRedOut + lo;  // tile, element, lane
+    const int nt = cin == 32 ? kWgTiles<32> : kWgTiles<3>;
+    const size_t stride = (size_t)(nt + 2) * 256;
     float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    if (valid) {
-        int b = sg;
-        for (; b + 3 * kRedSeg < nblk; b += 4 * kRedSeg) {
-            a0 += src[(size_t)b * stride];
-            a1 += src[(size_t)(b + kRedSeg) * stride];
-            a2 += src[(size_t)(b + 2 * kRedSeg) * stride];
-            a3 += src[(size_t)(b + 3 * kRedSeg) * stride];
-        }
-        for (; b < nblk; b += kRedSeg) a0 += src[(size_t)b * stride];
+    const float* src = part + e;
+    int b = sg;
+    for (; b + 3 * kRedSeg < nblk; b += 4 * kRedSeg) {
+        a0 += src[(size_t)b * stride];
+        a1 += src[(size_t)(b + kRedSeg) * stride];
+        a2 += src[(size_t)(b + 2 * kRedSeg) * stride];
+        a3 += src[(size_t)(b + 3 * kRedSeg) * stride];
     }
+    for (; b < nblk; b += kRedSeg) a0 += src[(size_t)b * stride];
     seg[sg][lo] = (a0 + a1) + (a2 + a3);
     __syncthreads();
-    if (sg == 0 && valid) {
-        float t = 0.f;
+    if (sg != 0) return;
+    float t = 0.f;
 #pragma unroll
-        for (int k = 0; k < kRedSeg; ++k) t += seg[k][lo];
-        if (e < nw)
-            dw[e] = t;
-        else
-            db[e - nw] = t;
+    for (int k = 0; k < kRedSeg; ++k) t += seg[k][lo];
+    const int tile = e >> 8, r = 4 * ((e & 63) >> 4) + ((e >> 6) & 3), col = e & 15;
+    if (tile >= nt) {
+        if (col == 0) db[16 * (tile - nt) + r] = t;
+    } else if (cin == 32) {  // tile (ot 2 + it) 9 + tap
+        const int oi = tile / 9, tap = tile - 9 * oi;
+        dw[((size_t)((oi >> 1) * 16 + r) * 9 + tap) * 32 + (oi & 1) * 16 + col] = t;
+    } else if (col < 9) {  // tile ot 3 + ky, column kx 3 + channel
+        const int ot = tile / 3, ky = tile - 3 * ot;
+        dw[(size_t)(ot * 16 + r) * 27 + ky * 9 + col] = t;
     }
+}
+
+// Rows per wave of the weight gradient: at most 2048 waves, the most that are
+// resident at once (one block of 8 per CU), so no wave starts late; at least 8
+// rows, so that the two halo rows stay a small share of small calls.  Where
+// columns alone are more than 2048, a wave takes several, one after another.
+struct WgradSplit {
+    int strips, R, chunks, units, blocks;
+};
+WgradSplit wgrad_split(int n, int H, int W, int dil) {
+    WgradSplit s;
+    s.strips = (W + kWgPx - 1) / kWgPx;
+    const size_t rows = (size_t)s.strips * n * H;
+    const int hp = (H + dil - 1) / dil;
+    s.R = (int)std::min<size_t>(std::max<size_t>((rows + 2047) / 2048, 8), (size_t)hp);
+    do {
+        s.chunks = dil * ((hp + s.R - 1) / s.R);
+        s.units = n * s.strips * s.chunks;
+    } while (s.units > 2048 && s.R++ < hp);
+    s.blocks = std::min((s.units + kWgWaves - 1) / kWgWaves, 256);
+    return s;
 }
 
 bool conv_shape_ok(int n, int H, int W, int cin, int cout, int dil) {
@@ -771,10 +859,11 @@ void launch_conv32(const bf16_t* x, const bf16_t* mask, const bf16_t* w, const f
         hipLaunchKernelGGL((conv32_column_kernel<false>), grid, dim3(256), 0, st, x, mask, w, bias, y, H, W, dil, relu, R);
 }
 
-size_t wgrad_part_bytes(int n, int H, int W, int cin, int cout) {
-    const size_t nblk = (size_t)((W + kTilePx - 1) / kTilePx) * ((H + kWgRows - 1) / kWgRows) * n;
-    const int cpad = (cin + 15) / 16 * 16;
-    return align256(nblk * ((size_t)cout * 9 * cpad + cout) * sizeof(float));
+// Partials of the weight gradient, for whichever dilation takes most.
+size_t wgrad_part_bytes(int n, int H, int W, int cin) {
+    size_t blocks = 0;
+    for (int d = 1; d <= kMaxDil; ++d) blocks = std::max(blocks, (size_t)wgrad_split(n, H, W, d).blocks);
+    return align256(blocks * ((cin == 32 ? kWgTiles<32> : kWgTiles<3>) + 2) * 256 * sizeof(float));
 }
 
 }  // namespace
@@ -808,7 +897,7 @@ extern "C" size_t sff_conv3x3_bf16_bwd_workspace_bytes(int32_t n, int32_t H, int
                                                        int32_t cin, int32_t cout) {
     if (!conv_shape_ok(n, H, W, cin, cout, 1)) return 0;
     return align256((size_t)cin * 9 * cout * sizeof(uint16_t)) +
-           wgrad_part_bytes(n, H, W, cin, cout);
+           wgrad_part_bytes(n, H, W, cin);
 }
 
 extern "C" sff_status sff_conv3x3_bf16_dgrad(int32_t n, int32_t H, int32_t W, int32_t cin,
@@ -842,22 +931,24 @@ extern "C" sff_status sff_conv3x3_bf16_wgrad(int32_t n, int32_t H, int32_t W, in
     if (!conv_shape_ok(n, H, W, cin, cout, dil) || !x || !dy || !dw || !db)
         return SFF_ERR_INVALID_ARG;
     const size_t off = align256((size_t)cin * 9 * cout * sizeof(uint16_t));
-    const size_t need = off + wgrad_part_bytes(n, H, W, cin, cout);
+    const size_t need = off + wgrad_part_bytes(n, H, W, cin);
     if (!workspace || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return SFF_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
     float* part = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + off);
-    const dim3 grid((W + kTilePx - 1) / kTilePx, (H + kWgRows - 1) / kWgRows, n);
-    const int nblk = grid.x * grid.y * grid.z;
+    const WgradSplit sp = wgrad_split(n, H, W, dil);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(sp.blocks), dim3(64 * kWgWaves), 0, st, x, dy, relu_out, part, H, W, dil, sp.R,
+                           sp.strips, sp.chunks, sp.units);
+    };
+    const bool vec = use_conv32(dy, relu_out);
     if (cin == 3)
-        hipLaunchKernelGGL((conv_wgrad_kernel<3, 32>), grid, dim3(256), 0, st, x, dy, relu_out, part,
-                           H, W, dil, 0);
+        vec ? launch(wgrad_column_kernel<3, true>) : launch(wgrad_column_kernel<3, false>);
     else
-        hipLaunchKernelGGL((conv_wgrad_kernel<32, 32>), grid, dim3(256), 0, st, x, dy, relu_out,
-                           part, H, W, dil, use_conv32(x, relu_out) && use_conv32(dy, nullptr) ? 1 : 0);
-    const int cpad = (cin + 15) / 16 * 16;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((cout * 9 * cin + cout + kRedOut - 1) / kRedOut), dim3(256), 0,
-                       st, part, dw, db, nblk, cin, cout, cpad);
+        vec && use_conv32(x, nullptr) ? launch(wgrad_column_kernel<32, true>) : launch(wgrad_column_kernel<32, false>);
+    const int nt = cin == 32 ? kWgTiles<32> : kWgTiles<3>;
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((nt + 2) * 256 / kRedOut), dim3(256), 0, st, part, dw, db, sp.blocks,
+                       cin);
     return launch_status();
 }
 

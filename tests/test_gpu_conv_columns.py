@@ -47,3 +47,32 @@ def test_column_kernel_same_as_im2col(sff, case, monkeypatch):
     monkeypatch.setenv("SFF_CONV_IM2COL", "1")
     for a, r in zip(got, all_three()):
         assert torch.equal(a.view(torch.int16), r.view(torch.int16))
+
+
+WGRAD_CASES = [(1, 1, 1, 3, 1), (1, 8, 32, 32, 1), (1, 9, 33, 32, 1), (2, 7, 31, 3, 2), (1, 40, 65, 32, 9),
+               (1, 35, 64, 32, 16), (3, 20, 100, 3, 5), (2, 375, 400, 32, 1), (2, 375, 400, 3, 1), (300, 9, 250, 32, 1)]
+
+
+@pytest.mark.parametrize("case", WGRAD_CASES, ids=str)
+def test_weight_gradient_columns(sff, case):
+    """Columns of 32 pixels, chunks of 8 or more rows, residues of the dilation
+    and (last case) more columns than waves, against float64 on the same values.
+    An FP32 sum of N terms in any order is within N 2^-24 of the sum of their
+    magnitudes; the chains here (a wave's rows, its MFMAs of 32 products, 8 waves,
+    up to 32 + 8 block partials) are below 2000 terms long."""
+    import torch
+    n, H, W, cin, dil = case
+    print("[case] weight gradient", case, file=sys.stderr, flush=True)
+    g = torch.Generator().manual_seed(H * 1000 + W + dil)
+    x = torch.randn((n, H, W, cin), generator=g).bfloat16().cuda()
+    dy = torch.randn((n, H, W, 32), generator=g).bfloat16().cuda()
+    m = torch.randn((n, H, W, 32), generator=g).bfloat16().cuda()
+    dw, db = sff.sff_conv3x3_bf16_wgrad(x, dy, dil, m)
+    dz = torch.where(m > 0, dy, torch.zeros_like(dy)).double().reshape(-1, 32).t().contiguous()
+    xp = torch.nn.functional.pad(x.double(), (0, 0, dil, dil, dil, dil))
+    for ky in range(3):
+        for kx in range(3):
+            xs = xp[:, ky * dil:ky * dil + H, kx * dil:kx * dil + W].reshape(-1, cin)
+            ref, mag = dz @ xs, dz.abs() @ xs.abs()
+            assert ((dw[:, ky, kx].double() - ref).abs() <= 2000 * 2.0 ** -24 * mag + 1e-12).all()
+    assert ((db.double() - dz.sum(1)).abs() <= 2000 * 2.0 ** -24 * dz.abs().sum(1) + 1e-12).all()
