@@ -144,6 +144,24 @@ __device__ __forceinline__ uint4 relu_masked(uint4 v, uint4 m) {
     return make_uint4(vw[0], vw[1], vw[2], vw[3]);
 }
 
+// A lane's 8 output channels (two tiles of 4): bias, ReLU, rounded to BF16.
+__device__ __forceinline__ v4u8a pack8(const v4f (&acc)[2], const float (&bz)[2][4], int relu) {
+    v4u8a o;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float v0 = acc[t][2 * h] + bz[t][2 * h];
+            float v1 = acc[t][2 * h + 1] + bz[t][2 * h + 1];
+            if (relu) {
+                v0 = fmaxf(v0, 0.f);
+                v1 = fmaxf(v1, 0.f);
+            }
+            o[2 * t + h] = f2bf2(v0, v1);
+        }
+    return o;
+}
+
 // The same convolution for Cin = Cout = 32, with neither an im2col tile nor
 // LDS: with K ordered (tap, channel), the 32 K values of one MFMA step are the
 // 32 channels of one input pixel, so lane (pixel l % 16, group l / 16) needs 16
@@ -158,11 +176,11 @@ __device__ __forceinline__ uint4 relu_masked(uint4 v, uint4 m) {
 // the MFMAs of conv_fwd_kernel<32, 32> in the same order on the same values, so
 // the results are identical.  x (and mask) must be 16-byte aligned.
 // Bound: HBM (128 B per pixel, 192 with the mask): on four 1242 x 375 images
-// 49 us (4.9 TB/s, the rate of a large copy) and 120 us with the mask (357 MB,
+// 49 us (4.9 TB/s, the rate of a large copy) and 88 us with the mask (357 MB,
 // past the 256 MB of the Infinity Cache), where rows staged in LDS for each of
 // the three output rows that read them took 167 and 190 us.
 template <bool MASK>
-__global__ void __launch_bounds__(256) conv32_column_kernel(const bf16_t* __restrict__ x,
+__global__ void __launch_bounds__(256, 2) conv32_column_kernel(const bf16_t* __restrict__ x,
                                                             const bf16_t* __restrict__ mask,
                                                             const bf16_t* __restrict__ w,
                                                             const float* __restrict__ bias,
@@ -236,68 +254,69 @@ __global__ void __launch_bounds__(256) conv32_column_kernel(const bf16_t* __rest
                 acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][tap], bv, acc[0], 0, 0, 0);
                 acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][tap], bv, acc[1], 0, 0, 0);
             }
-            v4u8a o;
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    float v0 = acc[t][2 * h] + bz[t][2 * h];
-                    float v1 = acc[t][2 * h + 1] + bz[t][2 * h + 1];
-                    if (relu) {
-                        v0 = fmaxf(v0, 0.f);
-                        v1 = fmaxf(v1, 0.f);
-                    }
-                    o[2 * t + h] = f2bf2(v0, v1);
-                }
             const int yy = phase + dil * (k0 + j);
-            if (p < W) *reinterpret_cast<v4u8a*>(y + (img + (size_t)yy * W + p) * 32 + 8 * g) = o;
+            if (p < W) *reinterpret_cast<v4u8a*>(y + (img + (size_t)yy * W + p) * 32 + 8 * g) = pack8(acc, bz, relu);
         }
     }
 }
 
 // The first layer (Cin = 3: K = 27, one MFMA step) without an im2col tile:
-// the three input rows of a 256-pixel tile are staged in LDS and each lane
-// reads its 8 (tap, channel) K values straight from them; the two weight
-// fragments stay in registers for the block's rows.  Same operands as
-// conv_fwd_kernel<3, 32>, so the same results.
+// the input rows that the 4 output rows of a 256-pixel tile read are staged in
+// LDS together (6 with dilation 1, else 12), so their loads are in flight at
+// once and the block waits at one barrier, and each lane reads its 8 (tap,
+// channel) K values straight from them; the two weight fragments stay in
+// registers, their rows dealt as in conv32_column_kernel so that a lane stores 16
+// bytes.  Same operands as conv_fwd_kernel<3, 32>, so the same results.
+// Bound: the stores (64 B per pixel; 24 us on four 1242 x 375 images at the
+// rate of a large copy): 35 us there, against 58 us with three rows staged per
+// output row between two barriers.
 __global__ void __launch_bounds__(256) conv3_fwd_kernel(const bf16_t* __restrict__ x,
                                                         const bf16_t* __restrict__ w,
                                                         const float* __restrict__ bias,
                                                         bf16_t* __restrict__ y, int H, int W, int dil,
                                                         int relu) {
-    __shared__ bf16_t rows[3][kStageW * 3];
-    const int x0 = blockIdx.x * kTile32, n = blockIdx.z;
+    __shared__ bf16_t rows[3 * kRows32][kStageW * 3];
+    const int x0 = blockIdx.x * kTile32, r0 = blockIdx.y * kRows32, n = blockIdx.z;
     const size_t img = (size_t)n * H * W;
-    const int nx = kTile32 + 2 * dil;
+    const int nx3 = (kTile32 + 2 * dil) * 3;  // staged values per row
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int ln = lane & 15, g = lane >> 4;
+    // slot of output row rr's input row ky: rr + ky with dilation 1 (shared), else 3 rr + ky
+    const int per = dil == 1 ? 1 : 3, ns = dil == 1 ? kRows32 + 2 : 3 * kRows32;
+    for (int s = 0; s < ns; ++s) {
+        const int yy = dil == 1 ? r0 + s - 1 : r0 + s / 3 + (s % 3 - 1) * dil;
+        const bool in = yy >= 0 && yy < H;
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(x + (img + (size_t)(in ? yy : 0) * W) * 3, in ? (uint32_t)W * 6u : 0u);
+        for (int e = threadIdx.x; e < nx3; e += 256) {
+            const int j = (x0 - dil) * 3 + e;  // value of the row
+            rows[s][e] = (bf16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, j >= 0 ? 2 * j : kOutside, 0, 0);
+        }
+    }
     v8bf a[2];
+    float bz[2][4];
     int koff[8];  // LDS offset of K value 8 g + e relative to the lane's pixel (-1: zero padding)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bz[t][e] = bias ? bias[8 * g + 4 * t + e] : 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int k = 8 * g + e;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
-            a[t][e] = __builtin_bit_cast(__bf16, k < 27 ? w[(size_t)(t * 16 + ln) * 27 + k] : (bf16_t)0);
+            a[t][e] = __builtin_bit_cast(
+                __bf16, k < 27 ? w[(size_t)(8 * (ln >> 2) + 4 * t + (ln & 3)) * 27 + k] : (bf16_t)0);
         const int tap = k / 3, ci = k - 3 * tap, ky = tap / 3, kx = tap - 3 * ky;
         koff[e] = k < 27 ? ky * kStageW * 3 + kx * dil * 3 + ci : -1;
     }
+    __syncthreads();
     for (int rr = 0; rr < kRows32; ++rr) {
-        const int row = blockIdx.y * kRows32 + rr;
-        if (row >= H) break;  // block-uniform
-        __syncthreads();
-        for (int e = threadIdx.x; e < 3 * nx * 3; e += 256) {
-            const int ky = e / (nx * 3), r = e - ky * nx * 3, px = r / 3, ci = r - 3 * px;
-            const int yy = row + (ky - 1) * dil, xx = x0 - dil + px;
-            bf16_t v = 0;
-            if (yy >= 0 && yy < H && xx >= 0 && xx < W) v = x[(img + (size_t)yy * W + xx) * 3 + ci];
-            rows[ky][px * 3 + ci] = v;
-        }
-        __syncthreads();
-#pragma unroll 1
+        const int row = r0 + rr;
+        if (row >= H) break;
+#pragma unroll
         for (int grp = 0; grp < 4; ++grp) {
             const int p = wv * 64 + grp * 16 + ln;
-            const bf16_t* src = &rows[0][p * 3];
+            const bf16_t* src = &rows[per * rr][p * 3];
             v8bf bv;
 #pragma unroll
             for (int e = 0; e < 8; ++e) bv[e] = __builtin_bit_cast(__bf16, koff[e] >= 0 ? src[koff[e]] : (bf16_t)0);
@@ -306,24 +325,7 @@ __global__ void __launch_bounds__(256) conv3_fwd_kernel(const bf16_t* __restrict
             for (int t = 0; t < 2; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], bv, v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
             const int px = x0 + p;
-            if (px < W) {
-                bf16_t* out = y + (img + (size_t)row * W + px) * 32;
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    uint32_t packed[2];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        float v0 = acc[t][2 * h] + (bias ? bias[t * 16 + 4 * g + 2 * h] : 0.f);
-                        float v1 = acc[t][2 * h + 1] + (bias ? bias[t * 16 + 4 * g + 2 * h + 1] : 0.f);
-                        if (relu) {
-                            v0 = fmaxf(v0, 0.f);
-                            v1 = fmaxf(v1, 0.f);
-                        }
-                        packed[h] = f2bf2(v0, v1);
-                    }
-                    *reinterpret_cast<uint2*>(out + t * 16 + 4 * g) = make_uint2(packed[0], packed[1]);
-                }
-            }
+            if (px < W) *reinterpret_cast<v4u8a*>(y + (img + (size_t)row * W + px) * 32 + 8 * g) = pack8(acc, bz, relu);
         }
     }
 }
