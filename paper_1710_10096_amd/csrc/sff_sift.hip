@@ -880,13 +880,12 @@ __global__ void __launch_bounds__(256) sift_half_step_kernel(SiftMatchArgs a, in
     }
 }
 
-// The same half-step with the window gathers shared by the wave (one wave per
-// block, 64 pixels of the colour in one image row).  Per window row, slot
-// f = 64 k + lane (k < 7) serves owner f / 7 at window column f % 7 - 3: it
-// loads that column's R, T, S and X elements (the 7 columns of one owner are
-// consecutive lanes, so a load instruction reads a few contiguous runs instead
-// of 64 scattered elements) and writes the three distances to LDS; the owner
-// then adds its 21 distances in the per-lane kernel's order (column, then
+// Window gathers shared by the wave (64 pixels of one image row).  Per window
+// row, slot f = 64 k + lane (k < 7) serves owner f / 7 at window column
+// f % 7 - 3: it loads that column's R, T, S and X elements (the 7 columns of one
+// owner are consecutive lanes, so a load instruction reads a few contiguous runs
+// instead of 64 scattered elements) and writes the three distances to LDS; the
+// owner then adds its 21 distances in the per-lane kernel's order (column, then
 // temporal, stereo, cross), so every sum is the same FP32 value, and stops
 // after the first row whose partial sum reaches the bound.  Tiles are
 // numbered column-major and dealt to the XCDs in vertical strips, which keeps
@@ -957,39 +956,235 @@ struct SiftCoop {
     }
 };
 
-__global__ void __launch_bounds__(64) sift_half_step_coop_kernel(SiftMatchArgs a, int it, int colour,
-                                                                 int tiles_x) {
-    __shared__ float dist_lds[64 * kDistStride];
-    const int per_field = tiles_x * a.H;
+// The half-step with the window gathers shared by the wave as above, and the
+// costs compared by estimates.  A candidate is taken only if its exact FP32 sum
+// (the per-lane kernel's, every operation rounded in its order) is below the
+// current vector's; the estimate forms the same 147 distances with fused
+// multiply-adds and the hardware root (a quarter of the operations of the exact
+// one) and adds them in whatever order is cheapest (a slot keeps its own sum
+// over the window rows, an owner adds 7 of them).  It is within 32 u of the true
+// sum, the exact one within 150 u of it (u = 2^-24), so the exact sum lies within
+// 2^-15 of the estimate, and disjoint intervals decide a comparison.  Where they
+// overlap (ties, mostly) both sums are formed exactly, and so is, once at the
+// end, the cost of a vector that was taken; 9 owners at a time (63 lanes, one per
+// owner and window column).  Estimates that are infinite, or so small that a
+// subnormal square could matter, decide nothing; a NaN estimate means a NaN sum,
+// which is never taken.  Partial sums are lower bounds, looked at after the last
+// four window rows (6.2 of the 7 rows are needed on average on a KITTI-size pair,
+// so earlier looks cost more than they save).
+// A block is 4 waves on 4 consecutive rows; the reference elements their windows
+// read (10 x 134) are staged in LDS once, clamped, for all candidates, so a slot
+// gathers three elements of 12 bytes per window row.
+// Bound: the texture data path (three gathers of 64 x 12 bytes, ~20 cache
+// accesses each, per slot and window row: 83 % busy), the vector ALU at 55 %.
+// KITTI-size pair, both fields: 574 us per half-step, where exact sums of all
+// candidates with four gathers took 753 us (one matching iteration with them 1.43
+// -> 1.12 ms); three and four waves per SIMD (168 and 128 VGPRs) spill: 9.2 and
+// 11.0 ms per 6 iterations against 8.0 ms, measured with an earlier form.
+constexpr int kHsRows = 4;                                  // image rows (waves) per block
+constexpr int kHsCols = 2 * 63 + 1 + 1 + 2 * kWinR;         // reference columns of a tile
+constexpr int kExactOwners = 64 / kSiftSlots;               // 9
+constexpr int kExactRows = 4;                               // window rows summed per pass over LDS
+constexpr int kExactStride = kExactRows * 3 * kSiftSlots;   // floats per owner
+constexpr int kHsSlice = kSiftSlots * 64;                   // floats of a wave's slice (estimate sums)
+static_assert(kExactOwners * kExactStride + 16 <= 2 * kHsSlice, "wave slice");
+constexpr int kNoElement = 0x7FFFFFF0;                      // offset past every image's map
+constexpr float kEstimateErr = 0x1p-15f;
+
+typedef float v3f __attribute__((ext_vector_type(3)));
+
+// Raw buffer descriptor of one image's features (wave-uniform): loads at or past
+// its size return zeros without a memory access.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t phi_rsrc(const float4* p, uint32_t bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a) |
+                       ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32);
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), (short)0,
+                                             (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
+__device__ __forceinline__ v3f load3(__amdgpu_buffer_rsrc_t rs, int off, int soff) {
+    return __builtin_bit_cast(v3f, __builtin_amdgcn_raw_buffer_load_b96(rs, off, soff, 0));
+}
+
+// Distance for the estimate: fused, hardware root (1 ulp).
+__device__ __forceinline__ float fdist3_fast(v3f a, v3f b) {
+    const float e0 = a.x - b.x, e1 = a.y - b.y, e2 = a.z - b.z;
+    return __builtin_amdgcn_sqrtf(fmaf(e2, e2, fmaf(e1, e1, e0 * e0)));
+}
+
+struct SiftHalf {
+    __amdgpu_buffer_rsrc_t rT, rS, rX;
+    const float4* ref;  // the block's reference tile in LDS, at the wave's first window row
+    float* slice;       // this wave's LDS [2 kHsSlice]
+    int H, W, s, y, lane, x0, par;
+
+    // Window column (slot f of the 64 owners): owner, x, and the vector handed over.
+    struct Column {
+        int xt, xs, xx, yv, lc;
+    };
+    __device__ __forceinline__ Column column(int o, int c, uint32_t uv, uint32_t dd, bool use) const {
+        const int u = (int)(int16_t)(uv & 0xFFFFu), v = (int)(int16_t)(uv >> 16);
+        const int d0 = (int)(int16_t)(dd & 0xFFFFu), d1 = (int)(int16_t)(dd >> 16);
+        Column q;
+        q.lc = 2 * o + par + c;
+        const int px = x0 - kWinR + q.lc;
+        q.xt = use ? clampi(px + u, 0, W - 1) * 16 : kNoElement;
+        q.xs = use ? clampi(px - s * d0, 0, W - 1) * 16 : kNoElement;
+        q.xx = use ? clampi(px + u - s * d1, 0, W - 1) * 16 : kNoElement;
+        q.yv = y + v;
+        return q;
+    }
+    __device__ __forceinline__ void load_row(const Column& q, int wy, v3f& r, v3f& t, v3f& sv, v3f& xv) const {
+        const uint32_t row = (uint32_t)clampi(q.yv + wy, 0, H - 1), W16 = (uint32_t)W * 16u;
+        const float4 rr = ref[(wy + kWinR) * kHsCols + q.lc];
+        r = v3f{rr.x, rr.y, rr.z};
+        t = load3(rT, (int)(__umul24(row, W16) + (uint32_t)q.xt), 0);
+        sv = load3(rS, q.xs, clampi(y + wy, 0, H - 1) * W * 16);
+        xv = load3(rX, (int)(__umul24(row, W16) + (uint32_t)q.xx), 0);
+    }
+
+    // Estimate of the cost of each owner's candidate h, [lo, hi] around the
+    // exact sum.  A lane ends early (lo >= bound) once a partial sum says so;
+    // lo = infinity without a candidate.  Called by all lanes.
+    __device__ __forceinline__ void estimate(bool want, short4 h, float bound, float& lo, float& hi) const {
+        const uint32_t uv = (uint32_t)(uint16_t)h.x | ((uint32_t)(uint16_t)h.y << 16);
+        const uint32_t dd = (uint32_t)(uint16_t)h.z | ((uint32_t)(uint16_t)h.w << 16);
+        uint64_t open = __ballot(want);
+        Column q[kSiftSlots];
+        float acc[kSiftSlots];
+#pragma unroll
+        for (int k = 0; k < kSiftSlots; ++k) {
+            const int f = 64 * k + lane, o = f / kSiftSlots;
+            q[k] = column(o, f - kSiftSlots * o, (uint32_t)__shfl((int)uv, o), (uint32_t)__shfl((int)dd, o),
+                          (open >> o) & 1);
+            acc[k] = 0.f;
+        }
+        lo = hi = INFINITY;
+        // rows -3 .. 0, then one at a time: few sums reach the bound earlier
+#pragma unroll 1
+        for (int wy = -kWinR; wy <= kWinR; ++wy) {
+            v3f r[kSiftSlots], t[kSiftSlots], sv[kSiftSlots], xv[kSiftSlots];
+#pragma unroll
+            for (int k = 0; k < kSiftSlots; ++k) load_row(q[k], wy, r[k], t[k], sv[k], xv[k]);
+#pragma unroll
+            for (int k = 0; k < kSiftSlots; ++k) {
+                acc[k] += fdist3_fast(r[k], t[k]);
+                acc[k] += fdist3_fast(r[k], sv[k]);
+                acc[k] += fdist3_fast(r[k], xv[k]);
+            }
+            if (wy < 0) continue;
+#pragma unroll
+            for (int k = 0; k < kSiftSlots; ++k) slice[64 * k + lane] = acc[k];
+            sift_wave_sync();
+            float sum = 0.f;
+#pragma unroll
+            for (int c = 0; c < kSiftSlots; ++c) sum += slice[kSiftSlots * lane + c];
+            sift_wave_sync();
+            if (want && ((open >> lane) & 1)) {
+                const bool sure = sum > 1e-10f && sum < INFINITY;
+                lo = sure ? sum * (1.f - kEstimateErr) : sum != sum ? INFINITY : 0.f;  // NaN: never taken
+                hi = sure ? sum * (1.f + kEstimateErr) : INFINITY;
+            }
+            open = __ballot(lo < bound);
+            if (open == 0) return;
+#pragma unroll
+            for (int k = 0; k < kSiftSlots; ++k)  // owners turned down gather nothing more
+                if (!((open >> ((64 * k + lane) / kSiftSlots)) & 1)) q[k].xt = q[k].xs = q[k].xx = kNoElement;
+        }
+    }
+
+    // The exact sums of the owners in `open` (eq. (1), sift_cost_below's value
+    // without its early end); meaningless in the other lanes.
+    __device__ __forceinline__ float exact(bool open, short4 h) const {
+        const uint32_t uv = (uint32_t)(uint16_t)h.x | ((uint32_t)(uint16_t)h.y << 16);
+        const uint32_t dd = (uint32_t)(uint16_t)h.z | ((uint32_t)(uint16_t)h.w << 16);
+        uint32_t* list = reinterpret_cast<uint32_t*>(slice + kExactOwners * kExactStride);
+        const int j = lane / kSiftSlots, c = lane - kSiftSlots * j;
+        float sum = 0.f;
+        uint64_t left = __ballot(open);
+        while (left) {
+            const int rank = __popcll(left & ((1ull << lane) - 1ull));
+            const bool mine = ((left >> lane) & 1) && rank < kExactOwners;
+            if (mine) list[rank] = (uint32_t)lane;
+            sift_wave_sync();
+            const bool serve = j < min(kExactOwners, __popcll(left));
+            const int o = serve ? (int)list[j] : 0;
+            const Column q = column(o, c, (uint32_t)__shfl((int)uv, o), (uint32_t)__shfl((int)dd, o), serve);
+#pragma unroll
+            for (int w0 = -kWinR; w0 <= kWinR; w0 += kExactRows) {
+                v3f r[kExactRows], t[kExactRows], sv[kExactRows], xv[kExactRows];
+#pragma unroll
+                for (int e = 0; e < kExactRows; ++e)
+                    if (w0 + e <= kWinR) load_row(q, w0 + e, r[e], t[e], sv[e], xv[e]);
+#pragma unroll
+                for (int e = 0; e < kExactRows; ++e)
+                    if (w0 + e <= kWinR && serve) {
+                        float* d = slice + j * kExactStride + e * 3 * kSiftSlots + 3 * c;
+                        const float4 a = make_float4(r[e].x, r[e].y, r[e].z, 0.f);
+                        d[0] = fdist3(a, make_float4(t[e].x, t[e].y, t[e].z, 0.f));
+                        d[1] = fdist3(a, make_float4(sv[e].x, sv[e].y, sv[e].z, 0.f));
+                        d[2] = fdist3(a, make_float4(xv[e].x, xv[e].y, xv[e].z, 0.f));
+                    }
+                sift_wave_sync();
+                if (mine) {
+                    const float* d = slice + rank * kExactStride;
+#pragma unroll
+                    for (int e = 0; e < 3 * kSiftSlots * kExactRows; ++e)
+                        if (w0 + e / (3 * kSiftSlots) <= kWinR) sum = sum + d[e];
+                }
+                sift_wave_sync();
+            }
+            left &= ~__ballot(mine);
+        }
+        return sum;
+    }
+};
+
+__global__ void __launch_bounds__(64 * kHsRows) sift_half_step_wave_kernel(SiftMatchArgs a, int it, int colour,
+                                                                           int tiles_x, int tiles_y) {
+    __shared__ float4 ref_lds[(kHsRows + 2 * kWinR) * kHsCols];
+    __shared__ float slices[kHsRows][2 * kHsSlice];
+    const int per_field = tiles_x * tiles_y;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);  // column-major tiles, a strip per XCD
     const int z = tile / per_field;
     const int tr = tile - z * per_field;
-    const int tx = tr / a.H, i = tr - tx * a.H;
-    const int lane = threadIdx.x;
+    const int tx = tr / tiles_y, i0 = (tr - tx * tiles_y) * kHsRows;
+    const int di = z / a.batch, b = z - di * a.batch;
+    const int s = a.ndir == 2 ? (di == 0 ? 1 : -1) : a.dir0;
+    const size_t npx = (size_t)a.H * a.W;
+    const SiftViews V = sift_views(a.phi + (size_t)b * 4 * npx, a.H, a.W, s);
+    for (int e = threadIdx.x; e < (kHsRows + 2 * kWinR) * kHsCols; e += 64 * kHsRows) {
+        const int r = e / kHsCols, c = e - r * kHsCols;
+        ref_lds[e] = V.R[(size_t)clampi(i0 - kWinR + r, 0, a.H - 1) * a.W + clampi(2 * tx * 64 - kWinR + c, 0, a.W - 1)];
+    }
+    __syncthreads();
+    const int w = wave_id(), i = i0 + w;
+    if (i >= a.H) return;  // whole wave, after the block's only barrier
+    const int lane = threadIdx.x & 63;
     const int par = (i + colour) & 1;
     const int j = 2 * (tx * 64 + lane) + par;
     const bool act = j < a.W;
     const int jj = min(j, a.W - 1);
-    const int di = z / a.batch, b = z - di * a.batch;
-    const int s = a.ndir == 2 ? (di == 0 ? 1 : -1) : a.dir0;
-    const size_t npx = (size_t)a.H * a.W;
-    SiftCoop E;
-    E.V = sift_views(a.phi + (size_t)b * 4 * npx, a.H, a.W, s);
-    E.dist = dist_lds;
-    E.lane = lane;
+    SiftHalf E;
+    const uint32_t bytes = (uint32_t)(npx * 16);
+    E.rT = phi_rsrc(V.T, bytes);
+    E.rS = phi_rsrc(V.S, bytes);
+    E.rX = phi_rsrc(V.X, bytes);
+    E.ref = ref_lds + w * kHsCols;
+    E.slice = slices[w];
+    E.H = a.H;
+    E.W = a.W;
+    E.s = s;
     E.y = i;
-#pragma unroll
-    for (int k = 0; k < kSiftSlots; ++k) {
-        const int f = 64 * k + lane, o = f / kSiftSlots, c = f - kSiftSlots * o;
-        E.so[k] = o;
-        E.sx[k] = min(2 * (tx * 64 + o) + par, a.W - 1) + c - kWinR;
-        E.sd[k] = o * kDistStride + 3 * c;
-    }
+    E.lane = lane;
+    E.x0 = 2 * tx * 64;
+    E.par = par;
     short4* field = reinterpret_cast<short4*>(a.hyp) + (size_t)z * npx;
     float* cost = a.cost + (size_t)z * npx;
     const size_t o = (size_t)i * a.W + jj;
     short4 best = field[o];
-    float bestc = cost[o];
+    const float bestc = cost[o];
     const short4 own = best;
     const int ni[4] = {i, i - 1, i, i + 1};
     const int nj[4] = {jj - 1, jj, jj + 1, jj};
@@ -1001,45 +1196,68 @@ __global__ void __launch_bounds__(64) sift_half_step_coop_kernel(SiftMatchArgs a
         nh[q] = in[q] ? field[(size_t)ni[q] * a.W + nj[q]] : own;
     }
     auto eq = [](short4 p, short4 q) { return p.x == q.x && p.y == q.y && p.z == q.z && p.w == q.w; };
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        bool dup = eq(nh[q], own);
-#pragma unroll
-        for (int p = 0; p < q; ++p) dup = dup || (in[p] && eq(nh[q], nh[p]));
-        const bool want = in[q] && !dup;
-        if (!__any(want)) continue;
-        const float c = E.cost_below(want, nh[q], bestc);
-        if (want && c < bestc) {
-            bestc = c;
-            best = nh[q];
+    // the current vector's cost lies in [blo, bhi] (both its exact cost at first)
+    float blo = bestc, bhi = bestc;
+    auto score = [&](bool want, short4 h) {
+        want = want && bhi > 0.f;  // a cost of zero (or NaN) cannot be improved on
+        if (!__any(want)) return;
+        float lo, hi;
+        E.estimate(want, h, bhi, lo, hi);
+        bool take = want && hi < blo;
+        const bool close = want && !take && lo < bhi;  // the estimates do not decide
+        if (__any(close)) {
+            const bool redo = close && blo < bhi;
+            const float eb = E.exact(redo, best);
+            if (redo) blo = bhi = eb;
+            const float eh = E.exact(close, h);
+            if (close && eh < bhi) {
+                take = true;
+                lo = hi = eh;
+            }
         }
-    }
-    const short4 centre = best;
+        if (take) {
+            blo = lo;
+            bhi = hi;
+            best = h;
+        }
+    };
+    const short4 n0 = nh[0], n1 = nh[1], n2 = nh[2], n3 = nh[3];
+    // a vector equal to one already scored has the same cost: no strict improvement
+    const bool w0 = in[0] && !eq(n0, own);
+    const bool w1 = in[1] && !eq(n1, own) && !(in[0] && eq(n1, n0));
+    const bool w2 = in[2] && !eq(n2, own) && !(in[0] && eq(n2, n0)) && !(in[1] && eq(n2, n1));
+    const bool w3 = in[3] && !eq(n3, own) && !(in[0] && eq(n3, n0)) && !(in[1] && eq(n3, n1)) && !(in[2] && eq(n3, n2));
+    short4 centre = best;
     const uint64_t seed = a.seeds[b];
-    for (int t = 0; t < a.rs_samples; ++t) {
-        const int r = max(1, a.rs_r0 >> t);
-        U4 ctr;
-        ctr.x = (uint32_t)(i * a.W + jj);
-        ctr.y = (uint32_t)it;
-        ctr.z = (kSiftLevelTag << 16) | ((uint32_t)t << 8) | (s < 0 ? 1u : 0u);
-        ctr.w = 0u;
-        const U4 rnd = philox4x32_10(ctr, (uint32_t)seed, (uint32_t)(seed >> 32));
+#pragma unroll 1
+    for (int t = -4; t < a.rs_samples; ++t) {  // left, up, right, down, then the samples
         short4 c;
-        c.x = (short)clampi(centre.x + uniform_offset(rnd.x, r), -a.fmax, a.fmax);
-        c.y = (short)clampi(centre.y + uniform_offset(rnd.y, r), -a.fmax, a.fmax);
-        c.z = (short)clampi(centre.z + uniform_offset(rnd.z, r), 0, a.dmax);
-        c.w = (short)clampi(centre.w + uniform_offset(rnd.w, r), 0, a.dmax);
-        const bool want = act && !eq(c, centre);
-        if (!__any(want)) continue;
-        const float cc = E.cost_below(want, c, bestc);
-        if (want && cc < bestc) {
-            bestc = cc;
-            best = c;
+        bool want;
+        if (t < 0) {
+            c = t == -4 ? n0 : t == -3 ? n1 : t == -2 ? n2 : n3;
+            want = t == -4 ? w0 : t == -3 ? w1 : t == -2 ? w2 : w3;
+        } else {
+            if (t == 0) centre = best;
+            const int r = max(1, a.rs_r0 >> t);
+            U4 ctr;
+            ctr.x = (uint32_t)(i * a.W + jj);
+            ctr.y = (uint32_t)it;
+            ctr.z = (kSiftLevelTag << 16) | ((uint32_t)t << 8) | (s < 0 ? 1u : 0u);
+            ctr.w = 0u;
+            const U4 rnd = philox4x32_10(ctr, (uint32_t)seed, (uint32_t)(seed >> 32));
+            c.x = (short)clampi(centre.x + uniform_offset(rnd.x, r), -a.fmax, a.fmax);
+            c.y = (short)clampi(centre.y + uniform_offset(rnd.y, r), -a.fmax, a.fmax);
+            c.z = (short)clampi(centre.z + uniform_offset(rnd.z, r), 0, a.dmax);
+            c.w = (short)clampi(centre.w + uniform_offset(rnd.w, r), 0, a.dmax);
+            want = act && !eq(c, centre);
         }
+        score(want, c);
     }
+    const bool redo = act && blo < bhi;
+    const float eb = E.exact(redo, best);
     if (act) {
         field[o] = best;
-        cost[o] = bestc;
+        cost[o] = redo ? eb : blo;
     }
 }
 
@@ -1238,15 +1456,17 @@ extern "C" sff_status sff_match_sift(const sff_params* p, int32_t batch, int32_t
     else
         hipLaunchKernelGGL(sift_cost_coop_kernel, dim3(((p->W + 63) / 64) * p->H * nz), dim3(64), 0, st, a,
                            (p->W + 63) / 64);
+    // the wave-shared half-step's 32-bit offsets reach maps below 2 GiB per image
+    const bool lane_step = lane || npx * sizeof(float4) >= (size_t)kNoElement;
     const int tiles_x = ((p->W + 1) / 2 + 63) / 64, tiles_y = (p->H + 3) / 4;
     for (int it = 0; it < iters; ++it)
         for (int colour = 0; colour < 2; ++colour) {
-            if (lane)
+            if (lane_step)
                 hipLaunchKernelGGL(sift_half_step_kernel, dim3(tiles_x * tiles_y * nz), dim3(256), 0, st, a,
                                    it, colour, tiles_x, tiles_y);
             else
-                hipLaunchKernelGGL(sift_half_step_coop_kernel, dim3(tiles_x * p->H * nz), dim3(64), 0, st, a,
-                                   it, colour, tiles_x);
+                hipLaunchKernelGGL(sift_half_step_wave_kernel, dim3(tiles_x * tiles_y * nz), dim3(64 * kHsRows), 0, st,
+                                   a, it, colour, tiles_x, tiles_y);
         }
     return launch_status();
 }
