@@ -156,6 +156,24 @@ __device__ __forceinline__ float quad_sum(float v) {
     return v;
 }
 
+// v / n for r = 1 / n correctly rounded: the product's remainder is exact in an
+// fma, and adding it back rounds the quotient correctly (Markstein, IBM J. Res.
+// Dev. 34, 1990), so the result is that of the division, in 3 operations instead
+// of about 10.  n is a norm (finite, > 0) and v at most n, zero or far above the
+// subnormal range.
+__device__ __forceinline__ float div_by(float v, float n, float r) {
+    const float q = v * r;
+    return fmaf(fmaf(-q, n, v), r, q);
+}
+
+// Image and pixel of descriptor g of a pair (g < 4 npx < 2^31).
+__device__ __forceinline__ void desc_pixel(int g, int npx, int W, int& m, int& y, int& x) {
+    m = (int)(g >= npx) + (int)(g >= 2 * npx) + (int)(g >= 3 * npx);
+    const int p = g - m * npx;
+    y = p / W;
+    x = p - y * W;
+}
+
 // Quarter q (cell row q: 4 cells x 8 bins, descriptor entries 32 q .. 32 q + 31)
 // of the normalised descriptor of pixel (y, x); the 4 quarters of a pixel sit in
 // one quad of lanes, which must all be active.
@@ -179,17 +197,17 @@ __device__ __forceinline__ void desc_quarter(const float* __restrict__ cs, int H
     for (int k = 0; k < 32; ++k) ss += v[k] * v[k];
     ss = quad_sum(ss);
     if (ss > 0.f) {
-        const float n = sqrtf(ss);
+        const float n = sqrtf(ss), rn = 1.f / n;
         float s2 = 0.f;
 #pragma unroll
         for (int k = 0; k < 32; ++k) {
-            v[k] = fminf(v[k] / n, kClampV);
+            v[k] = fminf(div_by(v[k], n, rn), kClampV);
             s2 += v[k] * v[k];
         }
         s2 = quad_sum(s2);
-        const float n2 = sqrtf(s2);
+        const float n2 = sqrtf(s2), rn2 = 1.f / n2;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) v[k] = v[k] / n2;
+        for (int k = 0; k < 32; ++k) v[k] = div_by(v[k], n2, rn2);
     }
 }
 
@@ -266,23 +284,21 @@ __device__ __forceinline__ void gram_store(double* part, int lane, const f64x4 (
                 part[(size_t)(16 * I1 + row0 + 4 * v) * kDesc + 16 * J + col] = acc[n][v];
 }
 
-__global__ void __launch_bounds__(256) gram_kernel(GramArgs a) {
+__global__ void __launch_bounds__(256, 2) gram_kernel(GramArgs a) {
     __shared__ float D[kGramPx][kDesc + 4];
     const int t = threadIdx.x, q = t & 3, px = t >> 2, lane = t & 63, w = wave_id();
     const int H = a.H, W = a.W, He = H + kExt, We = W + kExt;
-    const long npx = (long)H * W, total = 4 * npx;
+    const int npx = H * W, total = 4 * npx;
     const int pair = blockIdx.y;
     const float* Cs = a.Cs + (size_t)pair * 4 * kBins * He * We;
     f64x4 acc[9];
 #pragma unroll
     for (int n = 0; n < 9; ++n) acc[n] = f64x4{0.0, 0.0, 0.0, 0.0};
     double sacc = 0.0;
-    for (long base = (long)blockIdx.x * kGramPx; base < total; base += (long)a.nblk * kGramPx) {
-        const long g = base + px;
-        const long ge = g < total ? g : total - 1;
-        const int m = (int)(ge / npx);
-        const int p = (int)(ge - m * npx);
-        const int y = p / W, x = p - y * W;
+    for (int base = blockIdx.x * kGramPx; base < total; base += a.nblk * kGramPx) {
+        const int g = base + px;
+        int m, y, x;
+        desc_pixel(min(g, total - 1), npx, W, m, y, x);
         float v[32];
         desc_quarter(Cs + (size_t)m * kBins * He * We, He, We, y, x, q, v);
 #pragma unroll
@@ -667,31 +683,41 @@ __global__ void __launch_bounds__(256) eig_kernel(const double* __restrict__ cov
 }
 
 // phi = axes (f - mean) per pixel of the pair's four images, float4 (phi, 0).
-__global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ Cs,
-                                                      const float* __restrict__ ax32,
-                                                      float4* __restrict__ phi, int H, int W) {
+// A lane keeps its quarter of the three axes and the mean in registers (128
+// values) for all the pixels it projects; loaded for every pixel they were four
+// fifths of the kernel's reads (442 us on a KITTI-size pair).  Two waves per SIMD.
+constexpr int kProjBlocks = 512;  // per pair at most: two blocks per CU
+__global__ void __launch_bounds__(256, 2) project_kernel(const float* __restrict__ Cs,
+                                                         const float* __restrict__ ax32,
+                                                         float4* __restrict__ phi, int H, int W) {
     const int He = H + kExt, We = W + kExt;
     const int t = threadIdx.x, q = t & 3;
-    const long npx = (long)H * W, total = 4 * npx;
+    const int npx = H * W, total = 4 * npx;
     const int pair = blockIdx.y;
-    const long g = (long)blockIdx.x * kGramPx + (t >> 2);
-    const long ge = g < total ? g : total - 1;
-    const int m = (int)(ge / npx);
-    const int p = (int)(ge - m * npx);
-    const int y = p / W, x = p - y * W;
-    float v[32];
-    desc_quarter(Cs + ((size_t)pair * 4 + m) * kBins * He * We, He, We, y, x, q, v);
     const float* ax = ax32 + (size_t)pair * 4 * kDesc + 32 * q;
-    float f[3] = {0.f, 0.f, 0.f};
+    float A[4][32];
 #pragma unroll
-    for (int k = 0; k < 32; ++k) {
-        const float d = v[k] - ax[3 * kDesc + k];
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) f[c] = fmaf(ax[c * kDesc + k], d, f[c]);
+        for (int k = 0; k < 32; ++k) A[c][k] = ax[c * kDesc + k];
+#pragma unroll 1
+    for (int base = blockIdx.x * kGramPx; base < total; base += gridDim.x * kGramPx) {
+        const int g = base + (t >> 2), ge = min(g, total - 1);
+        int m, y, x;
+        desc_pixel(ge, npx, W, m, y, x);
+        float v[32];
+        desc_quarter(Cs + ((size_t)pair * 4 + m) * kBins * He * We, He, We, y, x, q, v);
+        float f[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+            const float d = v[k] - A[3][k];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) f[c] = fmaf(A[c][k], d, f[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) f[c] = quad_sum(f[c]);
+        if (g < total && q == 0) phi[(size_t)pair * total + ge] = make_float4(f[0], f[1], f[2], 0.f);
     }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) f[c] = quad_sum(f[c]);
-    if (g < total && q == 0) phi[(size_t)pair * total + ge] = make_float4(f[0], f[1], f[2], 0.f);
 }
 
 // ------------------------------------------------------------------ cost --
@@ -1385,7 +1411,8 @@ extern "C" sff_status sff_sift_pca(const sff_params* p, int32_t batch, const uin
     }
     hipLaunchKernelGGL(eig_kernel, dim3(batch), dim3(256), 0, st, cov, mean, sqm, eigval, axes, ax32);
     const long total = 4L * (long)g.npx;
-    hipLaunchKernelGGL(project_kernel, dim3((unsigned)((total + kGramPx - 1) / kGramPx), batch), dim3(256), 0,
+    const long groups = (total + kGramPx - 1) / kGramPx;
+    hipLaunchKernelGGL(project_kernel, dim3((unsigned)std::min<long>(groups, kProjBlocks), batch), dim3(256), 0,
                        st, Cs, ax32, reinterpret_cast<float4*>(phi), g.H, g.W);
     return launch_status();
 }
