@@ -35,7 +35,8 @@ constexpr int kExt = 2 * kHalf - kCell;     // 9 extra rows / columns of the cel
 constexpr int kDesc = 128;
 constexpr float kClampV = 0.2f;
 constexpr int kGramPx = 64;                 // descriptors per Gram step (4 threads each)
-constexpr int kMaxGramBlocks = 512;  // two blocks per CU
+constexpr int kMaxGramBlocks = 256;  // one block per CU
+constexpr size_t kGramMaxPx = 16384;  // descriptors per Gram block (exact int32 sums)
 constexpr int kPart = kDesc * kDesc + kDesc;  // doubles per Gram partial
 constexpr int kSub = 8;                     // subspace dimension of the eigen iteration
 constexpr int kCheck = 4;                   // iterations between Rayleigh-Ritz checks
@@ -59,10 +60,12 @@ inline SiftGeom sift_geom(const sff_params& p) {
     return g;
 }
 
+// At most one block per CU, each with at least two steps of 128 descriptors if
+// there are that many, and never more than kGramMaxPx.
 inline int gram_blocks(const SiftGeom& g) {
     const size_t per = 4 * g.npx;
-    const size_t nb = (per + 32 * kGramPx - 1) / (32 * kGramPx);
-    return (int)std::max<size_t>(1, std::min<size_t>(kMaxGramBlocks, nb));
+    const size_t nb = (per + 4 * kGramPx - 1) / (4 * kGramPx);
+    return (int)std::max(std::max<size_t>(1, std::min<size_t>(kMaxGramBlocks, nb)), (per + kGramMaxPx - 1) / kGramMaxPx);
 }
 
 struct SiftWs {
@@ -171,38 +174,50 @@ __device__ __forceinline__ void desc_pixel(int g, int npx, int W, int& m, int& y
 // Quarter q (cell row q: 4 cells x 8 bins, descriptor entries 32 q .. 32 q + 31)
 // of the normalised descriptor of pixel (y, x); the 4 quarters of a pixel sit in
 // one quad of lanes, which must all be active.
-__device__ __forceinline__ void desc_quarter(const float* __restrict__ cs, int He, int We, int y, int x,
-                                             int q, float (&v)[32]) {
+__device__ __forceinline__ void desc_cells(const float* __restrict__ cs, int We, int y, int x, int q,
+                                           float4 (&c)[8]) {
     const float4* row = reinterpret_cast<const float4*>(cs + ((size_t)(y + kCell * q) * We + x) * kBins);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const float4 lo = row[2 * kCell * j], hi = row[2 * kCell * j + 1];
-        v[8 * j + 0] = lo.x;
-        v[8 * j + 1] = lo.y;
-        v[8 * j + 2] = lo.z;
-        v[8 * j + 3] = lo.w;
-        v[8 * j + 4] = hi.x;
-        v[8 * j + 5] = hi.y;
-        v[8 * j + 6] = hi.z;
-        v[8 * j + 7] = hi.w;
+        c[2 * j] = row[2 * kCell * j];
+        c[2 * j + 1] = row[2 * kCell * j + 1];
     }
-    float ss = 0.f;
+}
+
+// The entries are multiplied by `scale`, a power of two or zero (exact).
+__device__ __forceinline__ void desc_normalise(const float4 (&c)[8], float (&v)[32], float scale = 1.f) {
 #pragma unroll
-    for (int k = 0; k < 32; ++k) ss += v[k] * v[k];
-    ss = quad_sum(ss);
+    for (int j = 0; j < 8; ++j) {
+        v[4 * j + 0] = c[j].x;
+        v[4 * j + 1] = c[j].y;
+        v[4 * j + 2] = c[j].z;
+        v[4 * j + 3] = c[j].w;
+    }
+    // the order of the sums' roundings is written out, so that every kernel forms
+    // the same descriptor to the bit
+    auto square_sum = [&]() {
+        float s = fmaf(v[0], v[0], v[1] * v[1]);
+#pragma unroll
+        for (int k = 2; k < 32; ++k) s = fmaf(v[k], v[k], s);
+        return quad_sum(s);
+    };
+    const float ss = square_sum();
     if (ss > 0.f) {
         const float n = sqrtf(ss), rn = 1.f / n;
-        float s2 = 0.f;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            v[k] = fminf(div_by(v[k], n, rn), kClampV);
-            s2 += v[k] * v[k];
-        }
-        s2 = quad_sum(s2);
+        for (int k = 0; k < 32; ++k) v[k] = fminf(div_by(v[k], n, rn), kClampV);
+        const float s2 = square_sum();
         const float n2 = sqrtf(s2), rn2 = 1.f / n2;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) v[k] = div_by(v[k], n2, rn2);
+        for (int k = 0; k < 32; ++k) v[k] = div_by(v[k], n2, rn2) * scale;
     }
+}
+
+__device__ __forceinline__ void desc_quarter(const float* __restrict__ cs, int We, int y, int x, int q,
+                                             float (&v)[32]) {
+    float4 c[8];
+    desc_cells(cs, We, y, x, q, c);
+    desc_normalise(c, v);
 }
 
 // Dense SIFT written out: [nimg][H][W][128], 64 pixels per block.
@@ -217,7 +232,7 @@ __global__ void __launch_bounds__(256) sift_out_kernel(const float* __restrict__
     const int p = (int)(ge - (long)m * H * W);
     const int y = p / W, x = p - y * W;
     float v[32];
-    desc_quarter(Cs + (size_t)m * kBins * He * We, He, We, y, x, q, v);
+    desc_quarter(Cs + (size_t)m * kBins * He * We, We, y, x, q, v);
     if (g >= total) return;
     float4* o = reinterpret_cast<float4*>(out + (size_t)ge * kDesc + 32 * q);
 #pragma unroll
@@ -226,96 +241,204 @@ __global__ void __launch_bounds__(256) sift_out_kernel(const float* __restrict__
 
 // ------------------------------------------------------------------- PCA --
 
-// Gram matrix and sum of the descriptors of one pair (4 H W of them), FP64:
-// each block takes every nblk-th group of 64 descriptors and stages them in
-// LDS; the 36 upper-triangle 16 x 16 tiles of the Gram matrix accumulate on
-// the FP64 matrix cores (v_mfma_f64_16x16x4f64: A = 16 descriptor entries of 4
-// pixels, B = 16 entries of the same pixels).  Wave w owns the tile rows w and
-// 7 - w (9 tiles); the operand of tile column J is also the A operand of tile
-// row J, so each 4-pixel step loads 8 - w values per lane.  Partials (upper
-// tiles only) go to part[pair][block].
+// Gram matrix and sum of the descriptors of one pair (4 H W of them), summed
+// exactly in integers on the int8 matrix cores.  An entry f (0 <= f <= 1, FP32)
+// is the fixed-point number F 2^-38 with F = sum_i d_i 256^i, five digits d_i in
+// [-128, 127]: exact for f >= 2^-15 (24 significant bits), within 2^-39 below.
+// With digit planes D_i, G = sum_ij 2^(8 (i + j) - 76) D_i D_j^T; the 19
+// products with i + j >= 3 are formed (v_mfma_i32_16x16x64_i8, K = 64 pixels),
+// those of one i + j in one accumulator, exact below 2^31 (5 products of 2^14 per
+// pixel, at most kGramMaxPx pixels per block).  The dropped ones are at most
+// 2^-44 per pixel, with mixed signs: on a KITTI-size pair the covariance agrees
+// with FP64 products of the same descriptors to 1e-12 of its norm, and its error
+// against 64 bits is that of the FP32 descriptors, 4e-8, as before.  (With
+// i + j >= 4 alone it is 3e-11 off: a small entry's lowest digit is a multiple of
+// a power of two, and of +128 and -128 a digit can only be the latter, so its mean
+// is not zero.)
+// Each block takes every nblk-th group of 128 descriptors: a thread forms a
+// quarter descriptor and writes its entries' upper four digits (a word) and
+// lowest digit (a byte) entry-major to LDS; wave w turns entries 16 w .. + 15
+// into digit operands (16 pixels of one entry and digit per lane: byte
+// permutations of 4 x 4 words), left in LDS for all waves.  An entry's pixels are
+// turned and exchanged in runs of 4 (slot and digit addresses below) so that
+// neither the writes nor the reads meet in a bank.  Waves 2 p and 2 p + 1 share
+// the tile rows p and 7 - p of the upper triangle (9 of the 36 16 x 16 tiles).
+// Partials (FP64, upper tiles only) go to part[pair][block].
+// Bound: the vector ALU (forming and splitting descriptors, 55 % of the cycles)
+// and the matrix units beside it (40 %).  The int8 products take less than half
+// of the FP64 products' time at the units' rates; KITTI-size pair: 369 us, against
+// 742 us with v_mfma_f64_16x16x4f64; 408 us with all waves of a block in the same
+// phase, 470 us with two blocks of 4 waves per CU (their accumulators spill).
 struct GramArgs {
     const float* Cs;
     double* part;
     int H, W, nblk;
 };
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+constexpr int kDigits = 5, kSum0 = 3, kSums = 6;  // digits of an entry; values of i + j, from kSum0
+constexpr float kFix = 0x1p30f;        // scale of the upper four digits
 
-template <int W>
-__device__ __forceinline__ void gram_tiles(const float (*D)[kDesc + 4], int lane, f64x4 (&acc)[9]) {
-    constexpr int I1 = 7 - W;
-    const int li = lane & 15, lk = lane >> 4;
-    for (int k0 = 0; k0 < kGramPx; k0 += 4) {
-        double b[8];
-#pragma unroll
-        for (int J = W; J < 8; ++J) b[J] = (double)D[k0 + lk][16 * J + li];
-        int n = 0;
-#pragma unroll
-        for (int J = W; J < 8; ++J, ++n) acc[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[W], b[J], acc[n], 0, 0, 0);
-#pragma unroll
-        for (int J = I1; J < 8; ++J, ++n)
-            if (I1 != W) acc[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[I1], b[J], acc[n], 0, 0, 0);
-    }
+// Tile n (of 9) of wave pair p: rows p (8 - p tiles), then 7 - p.
+__device__ __forceinline__ void gram_tile(int p, int n, int& I, int& J) {
+    const bool first = n < 8 - p;
+    I = first ? p : 7 - p;
+    J = first ? p + n : n - 1;  // 7 - p + n - (8 - p)
 }
 
-template <int W>
-__device__ __forceinline__ void gram_store(double* part, int lane, const f64x4 (&acc)[9]) {
-    constexpr int I1 = 7 - W;
-    // accumulator element v of lane l: row l / 16 + 4 v, column l % 16 of the
-    // tile (the operands: A[l % 16][l / 16], B[l / 16][l % 16])
-    const int col = lane & 15, row0 = lane >> 4;
-    int n = 0;
-#pragma unroll
-    for (int J = W; J < 8; ++J, ++n)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) part[(size_t)(16 * W + row0 + 4 * v) * kDesc + 16 * J + col] = acc[n][v];
-#pragma unroll
-    for (int J = I1; J < 8; ++J, ++n)
-        if (I1 != W)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                part[(size_t)(16 * I1 + row0 + 4 * v) * kDesc + 16 * J + col] = acc[n][v];
+// Digit planes of 4 words (digit i of word n in byte i) transposed: byte n of
+// word i of the result is digit i of word n.
+__device__ __forceinline__ void digits_4x4(const uint32_t (&w)[4], uint32_t (&d)[4]) {
+    const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), b = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+    const uint32_t c = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), e = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+    d[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+    d[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    d[2] = __builtin_amdgcn_perm(e, c, 0x05040100u);
+    d[3] = __builtin_amdgcn_perm(e, c, 0x07060302u);
 }
 
-__global__ void __launch_bounds__(256, 2) gram_kernel(GramArgs a) {
-    __shared__ float D[kGramPx][kDesc + 4];
-    const int t = threadIdx.x, q = t & 3, px = t >> 2, lane = t & 63, w = wave_id();
+constexpr int kGramTiles = 5;                          // tiles of a wave, at most
+constexpr int kGramWaves = 8, kGramStep = 2 * kGramPx;  // waves of a block, descriptors per step
+
+__global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
+    __shared__ __align__(16) uint32_t hi[2][kDesc * kGramPx];  // entry-major: upper digits,
+    __shared__ __align__(16) int8_t low[2][kDesc * kGramPx];   // lowest digit
+    __shared__ i32x4 ops[2][8 * kDigits * 64];                 // operands [tile][digit][lane]
+    const int t = threadIdx.x, q = t & 3, px = (t >> 2) & 63, lane = t & 63, w = wave_id();
     const int H = a.H, W = a.W, He = H + kExt, We = W + kExt;
     const int npx = H * W, total = 4 * npx;
     const int pair = blockIdx.y;
     const float* Cs = a.Cs + (size_t)pair * 4 * kBins * He * We;
-    f64x4 acc[9];
+    i32x4 acc[kGramTiles][kSums];
+    int dsum[kDigits];  // this lane's digit sums of entry 16 w + l % 16
 #pragma unroll
-    for (int n = 0; n < 9; ++n) acc[n] = f64x4{0.0, 0.0, 0.0, 0.0};
-    double sacc = 0.0;
-    for (int base = blockIdx.x * kGramPx; base < total; base += a.nblk * kGramPx) {
-        const int g = base + px;
+    for (int n = 0; n < kGramTiles; ++n)
+#pragma unroll
+        for (int k = 0; k < kSums; ++k) acc[n][k] = i32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < kDigits; ++i) dsum[i] = 0;
+    const int wp = w >> 1, n0 = (w & 1) * kGramTiles, nt = w & 1 ? 9 - kGramTiles : kGramTiles;
+    float4 rows[8];  // the cells of the step after next
+    auto load = [&](int base) {
         int m, y, x;
-        desc_pixel(min(g, total - 1), npx, W, m, y, x);
+        desc_pixel(min(base + (t >> 2), total - 1), npx, W, m, y, x);
+        desc_cells(Cs + (size_t)m * kBins * He * We, We, y, x, q, rows);
+    };
+    // digits of the descriptors in `rows`, to LDS
+    auto digits = [&](int base) {
         float v[32];
-        desc_quarter(Cs + (size_t)m * kBins * He * We, He, We, y, x, q, v);
+        desc_normalise(rows, v, base + (t >> 2) < total ? kFix : 0.f);
+        // pixel slot turned by the quarter, so that a wave's writes meet all banks
+        const int slot = (px + 16 * q) & 63;
+        uint32_t* hs = hi[w >> 2];
+        int8_t* ls = low[w >> 2];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) D[px][32 * q + k] = g < total ? v[k] : 0.f;
-        __syncthreads();
-        switch (w) {  // wave-uniform
-            case 0: gram_tiles<0>(D, lane, acc); break;
-            case 1: gram_tiles<1>(D, lane, acc); break;
-            case 2: gram_tiles<2>(D, lane, acc); break;
-            default: gram_tiles<3>(D, lane, acc); break;
+        for (int k = 0; k < 32; ++k) {
+            // lowest digit, rounded, + 128: its bit 8 carries into the upper ones
+            const uint32_t l = (uint32_t)fmaf(__builtin_amdgcn_fractf(v[k]), 256.f, 128.5f);
+            const int e = 32 * q + k;  // e & 15 = k & 15, (e >> 2) & 3 = (k >> 2) & 3
+            hs[e * kGramPx + (slot ^ (4 * (k & 15)))] = ((uint32_t)v[k] + (l >> 8) + 0x00808080u) ^ 0x00808080u;
+            ls[e * kGramPx + (slot ^ (16 * ((k >> 2) & 3)))] = (int8_t)(l ^ 0x80u);
         }
-        if (t < kDesc)
-            for (int k = 0; k < kGramPx; ++k) sacc += (double)D[k][t];
+    };
+    // digit operands of entry tile w: lane = entry l % 16, pixels 16 (l / 16) .. + 15
+    // (the entries are quarter w / 2's)
+    auto operands = [&]() {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int li = lane & 15, lg = ((lane >> 4) + wp) & 3, e = 16 * w + li;
+            uint32_t d[kDigits][4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint4 v4 = *reinterpret_cast<const uint4*>(hi[s] + e * kGramPx + 4 * ((4 * lg + c) ^ li));
+                const uint32_t ww[4] = {v4.x, v4.y, v4.z, v4.w};
+                uint32_t dd[4];
+                digits_4x4(ww, dd);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[i + 1][c] = dd[i];
+            }
+            const uint4 l4 = *reinterpret_cast<const uint4*>(low[s] + e * kGramPx + 16 * (lg ^ ((li >> 2) & 3)));
+            d[0][0] = l4.x;
+            d[0][1] = l4.y;
+            d[0][2] = l4.z;
+            d[0][3] = l4.w;
+#pragma unroll
+            for (int i = 0; i < kDigits; ++i) {
+                ops[s][(w * kDigits + i) * 64 + lane] = i32x4{(int)d[i][0], (int)d[i][1], (int)d[i][2], (int)d[i][3]};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) dsum[i] = __builtin_amdgcn_sdot4((int)d[i][c], 0x01010101, dsum[i], false);
+            }
+        }
+    };
+    auto products = [&]() {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            i32x4 opa[kDigits];
+#pragma unroll
+            for (int n = 0; n < kGramTiles; ++n) {
+                if (n >= nt) break;  // wave-uniform
+                int I, J;
+                gram_tile(wp, n0 + n, I, J);
+                if (n == 0 || n0 + n == 8 - wp)
+#pragma unroll
+                    for (int i = 0; i < kDigits; ++i) opa[i] = ops[s][(I * kDigits + i) * 64 + lane];
+                i32x4 opb[kDigits];
+#pragma unroll
+                for (int j = 0; j < kDigits; ++j) opb[j] = ops[s][(J * kDigits + j) * 64 + lane];
+#pragma unroll
+                for (int i = 0; i < kDigits; ++i)
+#pragma unroll
+                    for (int j = max(0, kSum0 - i); j < kDigits; ++j)
+                        acc[n][i + j - kSum0] =
+                            __builtin_amdgcn_mfma_i32_16x16x64_i8(opa[i], opb[j], acc[n][i + j - kSum0], 0, 0, 0);
+            }
+        }
+    };
+    const int first = blockIdx.x * kGramStep, step = a.nblk * kGramStep;
+    load(first);
+    digits(first);
+    load(first + step);
+    for (int base = first; base < total; base += step) {
         __syncthreads();
+        operands();
+        __syncthreads();
+        // this step's products and the next step's digits use different LDS; the
+        // two waves of a SIMD take them in opposite order, so that the matrix
+        // unit and the vector ALU are both busy
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            if (h == (w >> 2)) {
+                products();
+            } else {
+                digits(base + step);
+                load(base + 2 * step);
+            }
+        }
     }
     double* part = a.part + ((size_t)pair * a.nblk + blockIdx.x) * kPart;
-    switch (w) {
-        case 0: gram_store<0>(part, lane, acc); break;
-        case 1: gram_store<1>(part, lane, acc); break;
-        case 2: gram_store<2>(part, lane, acc); break;
-        default: gram_store<3>(part, lane, acc); break;
+    // accumulator element v of lane l: row 4 (l / 16) + v, column l % 16 of the tile
+#pragma unroll
+    for (int n = 0; n < kGramTiles; ++n) {
+        if (n >= nt) break;
+        int I, J;
+        gram_tile(wp, n0 + n, I, J);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            double gs = 0.0;
+#pragma unroll
+            for (int k = 0; k < kSums; ++k) gs = fma((double)acc[n][k][v], (double)(1ull << (8 * k)), gs);
+            part[(size_t)(16 * I + 4 * (lane >> 4) + v) * kDesc + 16 * J + (lane & 15)] = gs * 0x1p-52;
+        }
     }
-    if (t < kDesc) part[kDesc * kDesc + t] = sacc;
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < kDigits; ++i) {
+        int s = dsum[i];  // over the four pixel groups
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        sum = fma((double)s, (double)(1ull << (8 * i)), sum);
+    }
+    if (lane < 16) part[kDesc * kDesc + 16 * w + lane] = sum * 0x1p-38;
 }
 
 // Partials summed per entry (upper tiles of G, then S) with 8 interleaved
@@ -700,7 +823,7 @@ __global__ void __launch_bounds__(256, 2) project_kernel(const float* __restrict
         int m, y, x;
         desc_pixel(ge, npx, W, m, y, x);
         float v[32];
-        desc_quarter(Cs + ((size_t)pair * 4 + m) * kBins * He * We, He, We, y, x, q, v);
+        desc_quarter(Cs + ((size_t)pair * 4 + m) * kBins * He * We, We, y, x, q, v);
         float f[3] = {0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < 32; ++k) {
@@ -1385,7 +1508,7 @@ extern "C" sff_status sff_sift_pca(const sff_params* p, int32_t batch, const uin
     launch_cells(g, nimg, p->C, imgs, Cs, st);
     const int nblk = gram_blocks(g);
     GramArgs ga{Cs, part, g.H, g.W, nblk};
-    hipLaunchKernelGGL(gram_kernel, dim3(nblk, batch), dim3(256), 0, st, ga);
+    hipLaunchKernelGGL(gram_kernel, dim3(nblk, batch), dim3(64 * kGramWaves), 0, st, ga);
     double* gsum = reinterpret_cast<double*>(ws + L.gsum);
     hipLaunchKernelGGL(gram_sum_kernel, dim3((kSumEntries + 255) / 256, batch), dim3(256), 0, st, part, nblk,
                        gsum);
