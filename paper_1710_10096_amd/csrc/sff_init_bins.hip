@@ -188,20 +188,34 @@ __global__ void __launch_bounds__(256) op_planes_kernel(BinInitArgs a, OpPlanes 
 // each product sums over all K values.  Lane l receives D[4 (l / 16) + e]
 // [l % 16], e = 0..3: candidates 4 g + e of the tile against its own query.
 //
-// K > 1 (initialisation with K temporal leaves): each lane keeps its K best
-// (key, target index) per query, sorted (a candidate enters after kept ones of
-// equal key, which have smaller indices); the lists are merged per query in
-// LDS, each leaf gets its own cross-row search, and the combination with the
-// smallest T + S + X distance wins (the earlier leaf on ties).
+// K > 1 (initialisation with K temporal leaves): a first scan, at coarse levels
+// of every second row of each wave, keeps only minima.  16 lanes hold minima of disjoint sets of
+// a query's candidates, so the K-th smallest of them bounds the query's K-th
+// smallest key; a second scan of all rows appends the candidates up to the bound
+// (10 to 50 for K = 4) to the query's list in LDS, from which the K smallest
+// (distance, index) are selected; where a list overflows, the K-th smallest of
+// what it holds is the bound of another scan.  Each leaf gets its own cross-row search, and
+// the combination with the smallest T + S + X distance wins (the earlier leaf on
+// ties).  A block in which a list overflows with equal keys or a key is not
+// exact in fp32 takes the leaves one by one instead, each the smallest
+// (key, index) past the previous, with int32 keys.
+// Sorted lists of K entries in every lane's registers took 256 VGPRs, and some
+// of the 64 lanes inserted in about half of all steps: 1024 x 436, fmax 400, 1.79
+// ms for K = 4 and 1.25 ms for K = 2, now 0.53 and 0.52 ms (K = 1: 0.36 ms).
+constexpr int kLeafCap = 56;  // candidates a query's list holds (75 KB of LDS with K = 4: two blocks per CU)
+
 template <int C, int K>
 __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes P) {
     using KS = KSplit<C>;
-    __shared__ unsigned long long red[kWaves * 4][kQRows][16][K];
+    // partial minima of the 16 lanes of a query; for K > 1 also the lists
+    __shared__ unsigned long long red[K == 1 ? kWaves * 4 : kLeafCap][kQRows][16];
+    __shared__ int list_n[kQRows][16];
     __shared__ int res_u[kQRows][16][K], res_v[kQRows][16][K];
     __shared__ uint32_t res_t[kQRows][16][K];
     __shared__ int res_n[kQRows][16];
     __shared__ unsigned long long red2[kParts][kQRows][16];
     __shared__ unsigned long long redx[K][kParts][kQRows][16];
+    static_assert(kLeafCap >= kWaves * 4, "the lists' memory also holds partial minima");
     const int lane = threadIdx.x & 63, w = wave_id();
     const int nq = lane & 15, g = lane >> 4;
     const int j0 = blockIdx.x * 16, i0 = blockIdx.y * kQRows;
@@ -225,8 +239,6 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
     // queries (B operands), one 16-column tile per query row
     h8 q32[kQRows][KS::N32 > 0 ? KS::N32 : 1];
     h4 q16[kQRows];
-    int best[kQRows], btile[kQRows];   // K = 1: minimum key and its first tile
-    int tk[kQRows][K], ti[kQRows][K];  // K > 1: sorted keys and target indices
     const int jq = min(j0 + nq, Wk - 1);
 #pragma unroll
     for (int t = 0; t < kQRows; ++t) {
@@ -236,16 +248,12 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             q32[t][c] = *reinterpret_cast<const h8*>(P.q32 + ((size_t)c * P.nzk + o) * 32 + 8 * g);
         if constexpr (KS::N16 > 0) q16[t] = *reinterpret_cast<const h4*>(P.q16 + o * 16 + 4 * g);
     }
-    // Scan: per query only the minimum key over this lane's candidates and the
-    // first tile (in increasing target index) that reaches it are kept; the
-    // target inside that tile is recovered afterwards.
     const int rlo = max(0, i0 - F), rhi = min(Hk - 1, i0 + kQRows - 1 + F);
     const int nct = (16 + 2 * F + 15) / 16;
     const int ct_lo = max(0, (F - j0) >> 4);                 // first c0 + 15 >= 0
     const int ct_hi = min(nct - 1, (Wk - 1 - j0 + F) >> 4);  // last c0 < Wk
     const int ntl = ct_hi - ct_lo + 1;
     const int nrw = rlo + w <= rhi ? (rhi - rlo - w) / kWaves + 1 : 0;
-    const int total = ntl > 0 ? nrw * ntl : 0;
 
     struct Tile {
         h8 a32[KS::N32 > 0 ? KS::N32 : 1];
@@ -270,26 +278,18 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
         T.bsq[3] = q.w;
         return T;
     };
-    // The scan, with keys as fp32 (the fast form) or as int32 (exact for any
-    // key).  An fp32 key is the correctly rounded sum of two exact terms, so
-    // it is exact whenever the key is below 2^24 in magnitude, and a key at or
-    // above 2^24 rounds to a value at or above 2^24: the kept minimum (or the
-    // K kept keys) and their order are exact unless one of them is at or above
-    // 2^24, and then the block scans again with int32 keys.
-    auto run_scan = [&](auto key_tag, auto& S) {
+    // The scan: use(t, k, r, c0, ct) gets the keys of the lane's four candidates
+    // (row r, columns c0 + 4 g + e) against query row t, as fp32 (the fast form)
+    // or as int32 (exact for any key), infinite or INT_MAX outside the image or
+    // the query's box; candidates come in increasing index.  An fp32 key is the
+    // correctly rounded sum of two exact terms, so it is exact whenever the key is
+    // below 2^24 in magnitude, and a key at or above 2^24 rounds to a value at or
+    // above 2^24: the smallest keys and their order are exact unless one of them
+    // is at or above 2^24.  Takes every `every`-th of the wave's rows.
+    auto run_scan = [&](auto key_tag, int every, auto&& use) {
         using KT = decltype(key_tag);
         constexpr bool kFloat = std::is_same<KT, float>::value;
-        const KT kNone = kFloat ? (KT)__builtin_huge_valf() : (KT)INT_MAX;
-#pragma unroll
-        for (int t = 0; t < kQRows; ++t) {
-            S.best[t] = kNone;
-            S.btile[t] = 0;
-#pragma unroll
-            for (int l = 0; l < K; ++l) {
-                S.tk[t][l] = kNone;
-                S.ti[t][l] = 0;
-            }
-        }
+        const int total = ntl > 0 ? (nrw + every - 1) / every * ntl : 0;
         Tile ta{}, tb{};
         int r = rlo + w, ct = ct_lo;
         if (total > 0) ta = load_tile(r, ct);
@@ -297,17 +297,14 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             int rn = r, ctn = ct + 1;
             if (ctn > ct_hi) {
                 ctn = ct_lo;
-                rn += kWaves;
+                rn += kWaves * every;
             }
             if (q + 1 < total) nxt = load_tile(rn, ctn);
             const int c0 = j0 - F + 16 * ct;
-            const int tile_id = (r << 16) | ct;
             // every query row of the block has row r inside its box (wave-uniform)
             const bool all_rows = i0 + kQRows - 1 < Hk && r >= i0 + kQRows - 1 - F && r <= i0 + F;
-            // Keys of one tile for every query row.  Candidates outside the image
-            // or this lane's query box get INT_MAX (above any true key); interior
-            // tiles (every candidate inside every query's box) and rows inside
-            // every query row's box skip those tests.  Both conditions are
+            // Interior tiles (every candidate inside every query's box) and rows
+            // inside every query row's box skip those tests.  Both conditions are
             // wave-uniform.
             auto score = [&](auto interior, auto rows_in) {
                 constexpr bool kInterior = decltype(interior)::value;
@@ -315,63 +312,40 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
                 bool ok[4] = {true, true, true, true};
                 // fp32 keys: a candidate outside the box or the image gets an
                 // infinite norm once per tile, so its keys come out infinite
-                // (the kNone of this form) in every row without a select each
+                // in every row without a select each
                 float bq[4] = {cur.bsq[0], cur.bsq[1], cur.bsq[2], cur.bsq[3]};
                 if constexpr (!kInterior) {
-    #pragma unroll
+#pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int jc = c0 + 4 * g + e;
                         ok[e] = (unsigned)(jc - jq + F) <= (unsigned)(2 * F) && (unsigned)jc < (unsigned)Wk;
                         if constexpr (kFloat) bq[e] = ok[e] ? bq[e] : __builtin_huge_valf();
                     }
                 }
-    #pragma unroll
+#pragma unroll
                 for (int t = 0; t < kQRows; ++t) {
                     if constexpr (!kRowsIn) {
                         const int iq = i0 + t;
                         if (iq >= Hk || r < iq - F || r > iq + F) continue;
                     }
                     f4 acc = {0.f, 0.f, 0.f, 0.f};
-    #pragma unroll
+#pragma unroll
                     for (int c = 0; c < KS::N32; ++c)
                         acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(cur.a32[c], q32[t][c], acc, 0, 0, 0);
                     if constexpr (KS::N16 > 0)
                         acc = __builtin_amdgcn_mfma_f32_16x16x16f16(cur.a16, q16[t], acc, 0, 0, 0);
                     KT k[4];
-    #pragma unroll
+#pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         // |b'|^2 + (-2 a'.b'), the product exact in fp32
                         if constexpr (kFloat) {
                             k[e] = bq[e] + acc[e];
                         } else {
                             k[e] = (int)cur.bsq[e] + (int)acc[e];
-                            if constexpr (!kInterior) k[e] = ok[e] ? k[e] : kNone;
+                            if constexpr (!kInterior) k[e] = ok[e] ? k[e] : INT_MAX;
                         }
                     }
-                    if constexpr (K == 1) {
-                        // the running minimum folded in (two 3-input minima), the
-                        // tile recorded when it strictly decreases
-                        const KT nb = min(min(S.best[t], k[0]), min(min(k[1], k[2]), k[3]));
-                        S.btile[t] = nb < S.best[t] ? tile_id : S.btile[t];
-                        S.best[t] = nb;
-                    } else {
-    #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            if (!__any(k[e] < S.tk[t][K - 1])) continue;  // wave-uniform
-                            KT nk = k[e];
-                            int ni = r * Wk + c0 + 4 * g + e;
-    #pragma unroll
-                            for (int l = 0; l < K; ++l) {
-                                const bool lt = nk < S.tk[t][l];
-                                const KT ok_ = S.tk[t][l];
-                                const int oi = S.ti[t][l];
-                                S.tk[t][l] = lt ? nk : ok_;
-                                S.ti[t][l] = lt ? ni : oi;
-                                nk = lt ? ok_ : nk;
-                                ni = lt ? oi : ni;
-                            }
-                        }
-                    }
+                    use(t, k, r, c0, ct);
                 }
             };
             const bool interior = c0 >= 0 && c0 + 15 < Wk && c0 >= j0 + 15 - F && c0 + 15 <= j0 + F;
@@ -394,120 +368,243 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             if (q + 1 < total) scan_one(tb, ta, q + 1);
         }
     };
-    struct StateF {
-        float best[kQRows];
-        int btile[kQRows];
-        float tk[kQRows][K];
-        int ti[kQRows][K];
-    } SF;
-    run_scan(0.f, SF);
-    bool redo = false;
-    const float kExact = 16777216.f;  // 2^24
-#pragma unroll
-    for (int t = 0; t < kQRows; ++t) {
-        if constexpr (K == 1) redo = redo || (SF.best[t] >= kExact && SF.best[t] != __builtin_huge_valf());
-#pragma unroll
-        for (int l = 0; l < K; ++l)
-            if constexpr (K > 1) redo = redo || (SF.tk[t][l] >= kExact && SF.tk[t][l] != __builtin_huge_valf());
-    }
-    if (__syncthreads_or(redo)) {
-        struct StateI {
-            int best[kQRows];
-            int btile[kQRows];
-            int tk[kQRows][K];
-            int ti[kQRows][K];
-        } SI;
-        run_scan(0, SI);
-#pragma unroll
-        for (int t = 0; t < kQRows; ++t) {
-            best[t] = SI.best[t];
-            btile[t] = SI.btile[t];
-#pragma unroll
-            for (int l = 0; l < K; ++l) {
-                tk[t][l] = SI.tk[t][l];
-                ti[t][l] = SI.ti[t][l];
-            }
-        }
-    } else {
-#pragma unroll
-        for (int t = 0; t < kQRows; ++t) {
-            best[t] = SF.best[t] == __builtin_huge_valf() ? INT_MAX : (int)SF.best[t];
-            btile[t] = SF.btile[t];
-#pragma unroll
-            for (int l = 0; l < K; ++l) {
-                tk[t][l] = SF.tk[t][l] == __builtin_huge_valf() ? INT_MAX : (int)SF.tk[t][l];
-                ti[t][l] = SF.ti[t][l];
-            }
-        }
-    }
-    // the smallest target index of the winning tile that reaches the minimum
-    // (exact bin-grid squared distances, equal to the MFMA identity's)
     const __amdgpu_buffer_rsrc_t rR = image_rsrc(base + (size_t)vR * a.img_bytes, ib);
     const __amdgpu_buffer_rsrc_t rT = image_rsrc(base + (size_t)vT * a.img_bytes, ib);
     const __amdgpu_buffer_rsrc_t rS = image_rsrc(base + (size_t)vS * a.img_bytes, ib);
     const __amdgpu_buffer_rsrc_t rX = image_rsrc(base + (size_t)vX * a.img_bytes, ib);
-#pragma unroll 1
-    for (int t = 0; t < kQRows; ++t) {
-        if constexpr (K > 1) {
-            const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
+    constexpr float kInf = __builtin_huge_valf(), kExact = 16777216.f;  // 2^24
+    // leaf l of query (t, q): (ssd, target index) packed
+    auto set_leaf = [&](int t, int q, int l, unsigned long long m) {
+        const uint32_t idx = (uint32_t)m;
+        const int ri = (int)(idx / (uint32_t)Wk), rj = (int)(idx % (uint32_t)Wk);
+        res_v[t][q][l] = n * (ri - (i0 + t));
+        res_u[t][q][l] = n * (rj - min(j0 + q, Wk - 1));
+        res_t[t][q][l] = (uint32_t)(m >> 32);
+    };
+    bool redo = false;
+    if constexpr (K == 1) {
+        // Per query only the minimum key over this lane's candidates and the
+        // first tile that reaches it are kept (the running minimum folded in by
+        // two 3-input minima, the tile recorded when it strictly decreases); the
+        // target inside that tile is recovered afterwards.
+        float best[kQRows];
+        int btile[kQRows];
 #pragma unroll
-            for (int l = 0; l < K; ++l)
-                red[w * 4 + g][t][nq][l] =
-                    tk[t][l] == INT_MAX
-                        ? ~0ull
-                        : ((unsigned long long)((uint32_t)tk[t][l] + asq) << 32) | (uint32_t)ti[t][l];
-            continue;
+        for (int t = 0; t < kQRows; ++t) {
+            best[t] = kInf;
+            btile[t] = 0;
         }
-        uint32_t bssd = 0xFFFFFFFFu, bidx = 0;
-        if (best[t] != INT_MAX) {
-            const int r = btile[t] >> 16, c0 = j0 - F + 16 * (btile[t] & 0xFFFF);
-            uint4 qg[bin_pieces(C)];
-            load_grid<C>(rR, addr(n * jq, n * min(i0 + t, Hk - 1)), qg);
-            const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
-            bssd = (uint32_t)best[t] + asq;
-            bool found = false;
+        run_scan(0.f, 1, [&](int t, const float (&k)[4], int r, int c0, int ct) {
+            const float nb = min(min(best[t], k[0]), min(min(k[1], k[2]), k[3]));
+            btile[t] = nb < best[t] ? (r << 16) | ct : btile[t];
+            best[t] = nb;
+        });
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int jc = c0 + 4 * g + e;
-                const bool ok = (unsigned)(jc - jq + F) <= (unsigned)(2 * F) && (unsigned)jc < (unsigned)Wk;
-                if (ok && !found) {
-                    uint4 cg[bin_pieces(C)];
-                    load_grid<C>(rT, addr(n * jc, n * r), cg);
-                    if (grid_ssd<C>(qg, cg) == bssd) {
-                        found = true;
-                        bidx = (uint32_t)(r * Wk + jc);
+        for (int t = 0; t < kQRows; ++t) redo = redo || (best[t] >= kExact && best[t] != kInf);
+        redo = __syncthreads_or(redo);
+        if (!redo) {
+            // the smallest target index of the winning tile that reaches the minimum
+            // (exact bin-grid squared distances, equal to the MFMA identity's)
+#pragma unroll
+            for (int t = 0; t < kQRows; ++t) {
+                uint32_t bssd = 0xFFFFFFFFu, bidx = 0;
+                if (best[t] != kInf) {
+                    const int r = btile[t] >> 16, c0 = j0 - F + 16 * (btile[t] & 0xFFFF);
+                    uint4 qg[bin_pieces(C)];
+                    load_grid<C>(rR, addr(n * jq, n * min(i0 + t, Hk - 1)), qg);
+                    const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
+                    bssd = (uint32_t)(int)best[t] + asq;
+                    bool found = false;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int jc = c0 + 4 * g + e;
+                        const bool ok = (unsigned)(jc - jq + F) <= (unsigned)(2 * F) && (unsigned)jc < (unsigned)Wk;
+                        if (ok && !found) {
+                            uint4 cg[bin_pieces(C)];
+                            load_grid<C>(rT, addr(n * jc, n * r), cg);
+                            if (grid_ssd<C>(qg, cg) == bssd) {
+                                found = true;
+                                bidx = (uint32_t)(r * Wk + jc);
+                            }
+                        }
                     }
                 }
+                red[w * 4 + g][t][nq] = ((unsigned long long)bssd << 32) | bidx;
+            }
+            __syncthreads();
+            // combine the 16 partial minima (waves x lane groups) of each query
+            if (threadIdx.x < kQRows * 16) {
+                const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
+                unsigned long long m = ~0ull;
+                for (int k = 0; k < kWaves * 4; ++k) m = red[k][t][q] < m ? red[k][t][q] : m;
+                if ((uint32_t)(m >> 32) != 0xFFFFFFFFu) set_leaf(t, q, 0, m);
+                res_n[t][q] = (uint32_t)(m >> 32) != 0xFFFFFFFFu;
             }
         }
-        red[w * 4 + g][t][nq][0] = ((unsigned long long)bssd << 32) | bidx;
+    } else {
+        // bounds: the K-th smallest of the 16 lanes' minima, plus 1 (a list takes
+        // keys strictly below); none where fp32 keys would not be exact
+        float(*minima)[kQRows][16] = reinterpret_cast<float(*)[kQRows][16]>(&red[0][0][0]);
+        float(*bounds)[16] = reinterpret_cast<float(*)[16]>(&redx[0][0][0][0]);
+        {
+            float best[kQRows];
+#pragma unroll
+            for (int t = 0; t < kQRows; ++t) best[t] = kInf;
+            // At a stride of 4 pixels and more neighbouring patches differ, and a
+            // bound from half of the rows keeps the lists short (1024 x 436, K = 4,
+            // n = 4: 534 us against 629 from all rows); below, a minimum's
+            // neighbours pass the bound too and lists overflow (160 x 96, n = 1:
+            // 244 against 154 us).
+            run_scan(0.f, n >= 4 ? 2 : 1, [&](int t, const float (&k)[4], int, int, int) {
+                best[t] = min(min(best[t], k[0]), min(min(k[1], k[2]), k[3]));
+            });
+#pragma unroll
+            for (int t = 0; t < kQRows; ++t) minima[w * 4 + g][t][nq] = best[t];
+        }
+        __syncthreads();
+        if (threadIdx.x < kQRows * 16) {
+            const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
+            float sm[K];
+#pragma unroll
+            for (int l = 0; l < K; ++l) sm[l] = kInf;
+            for (int k = 0; k < kWaves * 4; ++k) {
+                float v = minima[k][t][q];
+#pragma unroll
+                for (int l = 0; l < K; ++l) {
+                    const float lo = fminf(v, sm[l]);
+                    v = fmaxf(v, sm[l]);
+                    sm[l] = lo;
+                }
+            }
+            bounds[t][q] = sm[K - 1] < kExact - 1.f ? sm[K - 1] + 1.f : kInf;
+            list_n[t][q] = 0;
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (bool again = true; again;) {
+            float bound[kQRows];
+#pragma unroll
+            for (int t = 0; t < kQRows; ++t) bound[t] = bounds[t][nq];
+            run_scan(0.f, 1, [&](int t, const float (&k)[4], int r, int c0, int) {
+                if (!__any(min(min(k[0], k[1]), min(k[2], k[3])) < bound[t])) return;  // wave-uniform, mostly
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k[e] < bound[t]) {
+                        redo = redo || k[e] >= kExact;
+                        const int at = atomicAdd(&list_n[t][nq], 1);
+                        const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
+                        if (at < kLeafCap)
+                            red[at][t][nq] = ((unsigned long long)((uint32_t)(int)k[e] + asq) << 32) |
+                                             (uint32_t)(r * Wk + c0 + 4 * g + e);
+                    }
+            });
+            redo = __syncthreads_or(redo);
+            if (redo) break;
+            // a list that overflowed: the K-th smallest of the candidates it holds is a
+            // lower bound for the next try, unless too many are equal
+            bool over = false;
+            if (threadIdx.x < kQRows * 16) {
+                const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
+                if (list_n[t][q] > kLeafCap) {
+                    unsigned long long sm[K];
+#pragma unroll
+                    for (int l = 0; l < K; ++l) sm[l] = ~0ull;
+                    for (int k = 0; k < kLeafCap; ++k) {
+                        unsigned long long v = red[k][t][q];
+#pragma unroll
+                        for (int l = 0; l < K; ++l) {
+                            const unsigned long long lo = v < sm[l] ? v : sm[l];
+                            v = v < sm[l] ? sm[l] : v;
+                            sm[l] = lo;
+                        }
+                    }
+                    const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + min(j0 + q, Wk - 1)];
+                    const float tighter = (float)(int)((uint32_t)(sm[K - 1] >> 32) - asq) + 1.f;
+                    redo = !(tighter < bounds[t][q]);
+                    bounds[t][q] = tighter;
+                    over = true;
+                }
+            }
+            again = __syncthreads_or(over);
+            if (again) {
+                redo = __syncthreads_or(redo);
+                if (redo) break;
+                if (threadIdx.x < kQRows * 16) list_n[threadIdx.x >> 4][threadIdx.x & 15] = 0;
+                __syncthreads();
+            }
+        }
+        if (!redo && threadIdx.x < kQRows * 16) {
+            // the K smallest, by K selection passes (indices are distinct)
+            const int t = threadIdx.x >> 4, q = threadIdx.x & 15, cnt = list_n[t][q];
+            unsigned long long prev = 0;
+            int nl = 0;
+            for (; nl < min(K, cnt); ++nl) {
+                unsigned long long m = ~0ull;
+                for (int k = 0; k < cnt; ++k) {
+                    const unsigned long long v = red[k][t][q];
+                    if ((nl == 0 || v > prev) && v < m) m = v;
+                }
+                set_leaf(t, q, nl, m);
+                prev = m;
+            }
+            res_n[t][q] = nl;
+        }
     }
-    __syncthreads();
-    // combine the 16 partial lists (waves x lane groups) of each query: the K
-    // smallest (ssd, index) keys, by K selection passes (indices are distinct)
-    if (threadIdx.x < kQRows * 16) {
-        const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
-        unsigned long long prev = 0;
-        int nl = 0;
+    if (redo) {  // block-uniform
+        // leaf by leaf with int32 keys: the smallest (key, index) past the previous
+        int pk[kQRows], pi[kQRows];
+#pragma unroll
+        for (int t = 0; t < kQRows; ++t) {
+            pk[t] = INT_MIN;
+            pi[t] = -1;
+        }
+        if (threadIdx.x < kQRows * 16) res_n[threadIdx.x >> 4][threadIdx.x & 15] = 0;
 #pragma unroll 1
         for (int l = 0; l < K; ++l) {
-            unsigned long long m = ~0ull;
-            for (int k = 0; k < kWaves * 4; ++k)
+            int best[kQRows], bidx[kQRows];
 #pragma unroll
-                for (int e = 0; e < K; ++e) {
-                    const unsigned long long v = red[k][t][q][e];
-                    if ((l == 0 || v > prev) && v < m) m = v;
+            for (int t = 0; t < kQRows; ++t) {
+                best[t] = INT_MAX;
+                bidx[t] = 0;
+            }
+            run_scan(0, 1, [&](int t, const int (&k)[4], int r, int c0, int) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int idx = r * Wk + c0 + 4 * g + e;
+                    if (k[e] < best[t] && (k[e] > pk[t] || (k[e] == pk[t] && idx > pi[t]))) {
+                        best[t] = k[e];
+                        bidx[t] = idx;
+                    }
                 }
-            if (m == ~0ull) break;
-            const uint32_t idx = (uint32_t)m;
-            const int ri = (int)(idx / (uint32_t)Wk), rj = (int)(idx % (uint32_t)Wk);
-            res_v[t][q][l] = n * (ri - (i0 + t));
-            res_u[t][q][l] = n * (rj - min(j0 + q, Wk - 1));
-            res_t[t][q][l] = (uint32_t)(m >> 32);
-            prev = m;
-            nl = l + 1;
+            });
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < kQRows; ++t) {
+                const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
+                red[w * 4 + g][t][nq] =
+                    best[t] == INT_MAX ? ~0ull
+                                       : ((unsigned long long)((uint32_t)best[t] + asq) << 32) | (uint32_t)bidx[t];
+            }
+            __syncthreads();
+            if (threadIdx.x < kQRows * 16) {
+                const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
+                unsigned long long m = ~0ull;
+                for (int k = 0; k < kWaves * 4; ++k) m = red[k][t][q] < m ? red[k][t][q] : m;
+                red2[0][t][q] = m;
+                if (m != ~0ull) {
+                    set_leaf(t, q, l, m);
+                    res_n[t][q] = l + 1;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < kQRows; ++t) {
+                const unsigned long long m = red2[0][t][nq];
+                const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
+                pk[t] = m == ~0ull ? INT_MAX : (int)((uint32_t)(m >> 32) - asq);
+                pi[t] = m == ~0ull ? INT_MAX : (int)(uint32_t)m;
+            }
         }
-        res_n[t][q] = nl;
     }
     __syncthreads();
 
