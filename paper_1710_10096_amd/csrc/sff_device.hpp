@@ -8,6 +8,7 @@
 namespace sff {
 
 typedef short short2v __attribute__((ext_vector_type(2)));
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
 // Descriptor records are padded to a power-of-two channel count (1, 2, 4, 4
 // for C = 1..4), so a record is 32, 64 or 128 bytes and, in a map aligned to
@@ -109,8 +110,14 @@ __device__ __forceinline__ BinRef<C> bin_ref(uint4 v) {
     if constexpr (C == 3) {
 #pragma unroll
         for (int m = 0; m < 4; ++m) r.w[m] = t[m] & 0x03FF03FFu;
-        r.w[4] = ((t[0] >> 10) & 0x003F003Fu) | ((t[1] >> 4) & 0x03C003C0u);
-        r.w[5] = ((t[2] >> 10) & 0x003F003Fu) | ((t[3] >> 4) & 0x03C003C0u);
+        // shifts inside the halves leave nothing above bit 9 (bits 14 and 15 of
+        // words 1 and 3 are zero), so one bit select joins the two parts
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const ushort2v lo = __builtin_bit_cast(ushort2v, t[2 * m]) >> 10;
+            const ushort2v hi = __builtin_bit_cast(ushort2v, t[2 * m + 1]) >> 4;
+            r.w[4 + m] = (__builtin_bit_cast(uint32_t, lo) & 0x003F003Fu) | (__builtin_bit_cast(uint32_t, hi) & ~0x003F003Fu);
+        }
     } else {
 #pragma unroll
         for (int m = 0; m < 4; ++m) r.w[m] = t[m];
