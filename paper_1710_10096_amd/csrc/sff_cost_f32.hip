@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "sff_internal.hpp"
 
@@ -182,16 +183,27 @@ __device__ __forceinline__ void preimage(int q, int w, int n, int& lo, int& hi) 
 }
 
 // The gradient entries gather their terms in row_split(CF) parts of
-// consecutive window rows, summed alone and then added in part order: eight
+// consecutive window rows, summed alone and then added in pairs: eight
 // single rows up to 32 channels, four pairs of rows at 64 (the CF / 4 lanes of
 // every part of an entry share one wave).
 constexpr int row_split(int cf) { return cf <= 32 ? 8 : 4; }
 constexpr int kWinN = kWin1 - kWin0 + 1;  // 8 window rows and columns
 
+// The parts of an entry added in pairs, pairs of pairs, ...: into part 0.
+template <int S, int CF>
+__device__ __forceinline__ void pair_sums(float (&acc)[S][CF]) {
+#pragma unroll
+    for (int d = 1; d < S; d *= 2)
+#pragma unroll
+        for (int t = 0; t < S; t += 2 * d)
+#pragma unroll
+            for (int c = 0; c < CF; ++c) acc[t][c] += acc[t + d][c];
+}
+
 // Reference-map gradient, one thread per entry q of R (testing and timing).
 // The terms of q are the (p, w) with clamp(p + w) = q, taken by window row wy,
 // preimage row py, window column wx, preimage column px and correspondence;
-// each part of the window rows is summed alone, then the parts in order.
+// each part of the window rows is summed alone, then the parts in pairs.
 template <int CF>
 __global__ void __launch_bounds__(256) grad_ref_kernel(CostArgs a) {
     const int qx = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -205,10 +217,12 @@ __global__ void __launch_bounds__(256) grad_ref_kernel(CostArgs a) {
     const float* M[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) M[k] = base + (size_t)view(a.s, k + 1) * HW * CF;
-    float fq[CF], acc[CF], sum[CF];
-    load_vec<CF>(base + ((size_t)mR * HW + (size_t)qy * W + qx) * CF, fq);
     constexpr int kSplit = row_split(CF), kPartRows = kWinN / kSplit;
+    float fq[CF], part_acc[kSplit][CF];
+    load_vec<CF>(base + ((size_t)mR * HW + (size_t)qy * W + qx) * CF, fq);
+#pragma unroll
     for (int part = 0; part < kSplit; ++part) {
+        float(&acc)[CF] = part_acc[part];
 #pragma unroll
         for (int c = 0; c < CF; ++c) acc[c] = 0.f;
         for (int wy = kWin0 + part * kPartRows; wy < kWin0 + (part + 1) * kPartRows; ++wy) {
@@ -233,9 +247,9 @@ __global__ void __launch_bounds__(256) grad_ref_kernel(CostArgs a) {
                     }
                 }
         }
-#pragma unroll
-        for (int c = 0; c < CF; ++c) sum[c] = part ? sum[c] + acc[c] : acc[c];
     }
+    pair_sums<kSplit, CF>(part_acc);
+    const float(&sum)[CF] = part_acc[0];
     float4* o = reinterpret_cast<float4*>(a.out + ((size_t)b * 4 * HW + (size_t)mR * HW +
                                                    (size_t)qy * W + qx) * CF);
 #pragma unroll
@@ -408,8 +422,8 @@ __global__ void cell_starts_kernel(const uint32_t* __restrict__ keys, uint32_t* 
 // the canonical order: window row wy ascending, cell row ty of its preimage
 // ascending, window column wx descending (cells by ascending x), cell column
 // tx of its preimage ascending, the pixels grouped at the cell in sorted
-// order.  Term i goes to accumulator i mod row_split(CF); the gradient is the
-// sum of the accumulators in order.  (Dealing the terms round-robin keeps the
+// order.  Term i goes to accumulator i mod row_split(CF); the accumulators are
+// added in pairs.  (Dealing the terms round-robin keeps the
 // tiled kernel's lanes busy however unevenly the pixels crowd the cells.)
 template <int CF>
 __global__ void __launch_bounds__(256) grad_target_kernel(CostArgs a, int k, size_t n,
@@ -459,15 +473,10 @@ __global__ void __launch_bounds__(256) grad_target_kernel(CostArgs a, int k, siz
     }
     float4* o = reinterpret_cast<float4*>(a.out + ((size_t)b * 4 * HW + (size_t)mk * HW +
                                                    (size_t)qy * W + qx) * CF);
+    pair_sums<S, CF>(acc);
 #pragma unroll
-    for (int kk = 0; kk < CF / 4; ++kk) {
-        float4 v = make_float4(acc[0][4 * kk], acc[0][4 * kk + 1], acc[0][4 * kk + 2], acc[0][4 * kk + 3]);
-#pragma unroll
-        for (int t = 1; t < S; ++t)
-            v = make_float4(v.x + acc[t][4 * kk], v.y + acc[t][4 * kk + 1], v.z + acc[t][4 * kk + 2],
-                            v.w + acc[t][4 * kk + 3]);
-        o[kk] = v;
-    }
+    for (int kk = 0; kk < CF / 4; ++kk)
+        o[kk] = make_float4(acc[0][4 * kk], acc[0][4 * kk + 1], acc[0][4 * kk + 2], acc[0][4 * kk + 3]);
 }
 
 // Tiled gradient kernels: a block takes kTileQ consecutive entries of one row
@@ -481,6 +490,13 @@ __global__ void __launch_bounds__(256) grad_target_kernel(CostArgs a, int k, siz
 constexpr int kTileQ = 32;
 constexpr int kTileC = kTileQ + kWinN - 1;  // staged columns: the tile's and the window's
 constexpr int kStageCap = 2048;             // staged pixels per target-gradient tile
+constexpr int kMaxRuns = 15 * 15;           // (window row, cell row) by (window column, cell column) at a corner
+
+__device__ __forceinline__ void grad_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Add the four-channel part of the terms of one pixel: fma(g, x - y, acc).
 __device__ __forceinline__ void fma4(float g, const float4& x, const float4& y, float4& acc) {
@@ -490,10 +506,9 @@ __device__ __forceinline__ void fma4(float g, const float4& x, const float4& y, 
     acc.w = fmaf(g, x.w - y.w, acc.w);
 }
 
-// One image's feature map read 16 bytes per lane.  BUF: a raw buffer with
-// 32-bit offsets (maps below 2 GiB), where a load flagged `skip` reads nothing
-// (its value is filled in by the caller); otherwise plain loads, `skip`
-// ignored.
+// One image's feature map read 16 bytes per lane, at the vector with the given
+// unit: its byte offset (BUF: a raw buffer with 32-bit offsets, maps below 2
+// GiB; kSkipOff reads nothing) or its index in 16-byte pieces.
 constexpr int kSkipOff = 0x7FFFFFF0;
 template <bool BUF>
 struct Vec4Map {
@@ -510,32 +525,34 @@ struct Vec4Map {
                                                    0x00020000);
         }
     }
-    __device__ __forceinline__ float4 ld(uint32_t i, bool skip) const {
+    // Unit of the vector of pixel i, L pieces of 16 bytes per vector.
+    template <int L>
+    __device__ __forceinline__ static uint32_t unit(int i) {
+        return (uint32_t)i * (BUF ? 16u * L : (uint32_t)L);
+    }
+    // Piece `sub` of the vector at unit u.
+    __device__ __forceinline__ float4 ld(uint32_t u, int sub) const {
         if constexpr (BUF) {
-            const uint4 v = __builtin_bit_cast(
-                uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, skip ? kSkipOff : (int)(i * 16u), 0, 0));
+            const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(u + 16u * sub), 0, 0));
             return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
                                __uint_as_float(v.w));
         } else {
-            return p[i];
+            return p[u + sub];
         }
     }
 };
 
-// Sum of the entry's parts, in part order, in the lanes of part 0.
+// Sum of the entry's parts (groups of L lanes), in pairs, in all its lanes.
 template <int kSplit, int L>
-__device__ __forceinline__ float4 sum_parts(const float4& acc) {
-    float4 sum = acc;
-    const int lane = threadIdx.x & 63;
+__device__ __forceinline__ float4 sum_parts(float4 v) {
 #pragma unroll
-    for (int g = 1; g < kSplit; ++g) {
-        const int src = lane + g * L;  // part g of this entry, for the lanes of part 0
-        sum.x += __shfl(acc.x, src);
-        sum.y += __shfl(acc.y, src);
-        sum.z += __shfl(acc.z, src);
-        sum.w += __shfl(acc.w, src);
+    for (int d = 1; d < kSplit; d *= 2) {
+        v.x += __shfl_xor(v.x, d * L);
+        v.y += __shfl_xor(v.y, d * L);
+        v.z += __shfl_xor(v.z, d * L);
+        v.w += __shfl_xor(v.w, d * L);
     }
-    return sum;
+    return v;
 }
 
 // Reference-map gradient: the tile stages 2 g and the three target centres of
@@ -545,8 +562,10 @@ __global__ void __launch_bounds__(256) grad_ref_tile_kernel(CostArgs a, int tile
     constexpr int kSplit = row_split(CF), kPartRows = kWinN / kSplit;
     constexpr int L = CF / 4, G = kSplit * L, EPB = 256 / G;
     static_assert(G <= 64 && 64 % G == 0, "the parts of an entry share one wave");
+    using Map = Vec4Map<BUF>;
     __shared__ float s_g[kWinN][kTileC];
     __shared__ uint32_t s_t[3][kWinN][kTileC];  // (ty << 16) | tx
+    __shared__ uint4 s_d[kWinN][kTileC];        // unit of each centre less the pixel's, and 2 g
     __shared__ float4 s_fq[kTileQ * L];         // the entries' own vectors
     const int H = a.H, W = a.W;
     const size_t HW = (size_t)H * W;
@@ -555,6 +574,7 @@ __global__ void __launch_bounds__(256) grad_ref_tile_kernel(CostArgs a, int tile
     const int qy = rest % H, b = rest / H;
     const int qx0 = tq * kTileQ;
     const int py0 = qy - kWin1, px0 = qx0 - kWin1;  // staged pixel (0, 0)
+    bool clamps = false;  // a window of this thread's pixels leaves the image
     for (int idx = threadIdx.x; idx < kWinN * kTileC; idx += 256) {
         const int r = idx / kTileC, c = idx - r * kTileC;
         const int py = py0 + r, px = px0 + c;
@@ -563,7 +583,14 @@ __global__ void __launch_bounds__(256) grad_ref_tile_kernel(CostArgs a, int tile
         s_g[r][c] = 2.f * a.gcost[pix];
         const Targets t = targets(a.hyp, pix, py, px, a.s, H, W);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) s_t[k][r][c] = ((uint32_t)t.y[k] << 16) | (uint32_t)t.x[k];
+        for (int k = 0; k < 3; ++k) {
+            s_t[k][r][c] = ((uint32_t)t.y[k] << 16) | (uint32_t)t.x[k];
+            clamps = clamps || t.y[k] + kWin0 < 0 || t.y[k] + kWin1 >= H || t.x[k] + kWin0 < 0 || t.x[k] + kWin1 >= W;
+        }
+        const uint32_t self = Map::template unit<L>(py * W + px);
+        s_d[r][c] = make_uint4(Map::template unit<L>(t.y[0] * W + t.x[0]) - self,
+                               Map::template unit<L>(t.y[1] * W + t.x[1]) - self,
+                               Map::template unit<L>(t.y[2] * W + t.x[2]) - self, __float_as_uint(s_g[r][c]));
     }
     const float* base = a.feat + (size_t)b * 4 * HW * CF;
     const int mR = view(a.s, 0);
@@ -572,8 +599,8 @@ __global__ void __launch_bounds__(256) grad_ref_tile_kernel(CostArgs a, int tile
         if (qx < W)
             s_fq[idx] = reinterpret_cast<const float4*>(base + ((size_t)mR * HW + (size_t)qy * W + qx) * CF)[idx % L];
     }
-    __syncthreads();
-    Vec4Map<BUF> M[3];
+    clamps = __syncthreads_or(clamps);
+    Map M[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) M[k].init(base + (size_t)view(a.s, k + 1) * HW * CF, HW * CF * 4);
     const int sub = threadIdx.x % L, part = (threadIdx.x / L) % kSplit;
@@ -586,49 +613,38 @@ __global__ void __launch_bounds__(256) grad_ref_tile_kernel(CostArgs a, int tile
         float4 fq = make_float4(0.f, 0.f, 0.f, 0.f);
         if (live) fq = s_fq[(qx - qx0) * L + sub];
         if (live && qy >= kWin1 && qy <= H - 1 + kWin0 && qx >= kWin1 && qx <= W - 1 + kWin0) {
-            // interior: the preimage of q under w is the one pixel q - w.  A
-            // gathered vector equal to the previous one of the same map (a
-            // locally constant field reads one vector for the whole row) is not
-            // loaded again but copied once all loads are back; the arithmetic
-            // is unchanged.
-            // (half a window row, 12 gathers, at a time: fewer registers, more waves)
+            // interior: the preimage of q under w is the one pixel q - w; half a
+            // window row, 12 gathers, at a time: fewer registers, more waves
             constexpr int JH = kWinN / 2;
-            int pidx[3] = {-1, -1, -1};
-            float4 pv[3];
+            const uint32_t uq = Map::template unit<L>((int)q);
             for (int wy = wy0; wy < wy0 + kPartRows; ++wy) {
                 const int r = qy - wy - py0;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     float4 tg[JH][3];
                     float g2[JH];
-                    int idx[JH][3];
+                    if (!clamps) {
+                        // no window of the tile's pixels leaves the image: the target of
+                        // q is q moved as the pixel's centre, one add per gather
 #pragma unroll
-                    for (int jj = 0; jj < JH; ++jj) {  // wx = kWin0 + j
-                        const int j = h * JH + jj, wx = kWin0 + j, c = qx - wx - px0;
-                        g2[jj] = s_g[r][c];
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            const uint32_t t = s_t[k][r][c];
-                            idx[jj][k] = clampi((int)(t >> 16) + wy, 0, H - 1) * W +
-                                         clampi((int)(t & 0xFFFFu) + wx, 0, W - 1);
+                        for (int jj = 0; jj < JH; ++jj) {  // wx = kWin0 + j
+                            const uint4 d = s_d[r][qx - (kWin0 + h * JH + jj) - px0];
+                            tg[jj][0] = M[0].ld(uq + d.x, sub);
+                            tg[jj][1] = M[1].ld(uq + d.y, sub);
+                            tg[jj][2] = M[2].ld(uq + d.z, sub);
+                            g2[jj] = __uint_as_float(d.w);
                         }
-                    }
+                    } else {
 #pragma unroll
-                    for (int jj = 0; jj < JH; ++jj)
+                        for (int jj = 0; jj < JH; ++jj) {
+                            const int wx = kWin0 + h * JH + jj, c = qx - wx - px0;
+                            g2[jj] = s_g[r][c];
 #pragma unroll
-                        for (int k = 0; k < 3; ++k)
-                            tg[jj][k] = M[k].ld((uint32_t)idx[jj][k] * L + sub,
-                                                idx[jj][k] == (jj ? idx[jj - 1][k] : pidx[k]));
-                    if constexpr (BUF) {
-#pragma unroll
-                        for (int jj = 0; jj < JH; ++jj)
-#pragma unroll
-                            for (int k = 0; k < 3; ++k)
-                                if (idx[jj][k] == (jj ? idx[jj - 1][k] : pidx[k])) tg[jj][k] = jj ? tg[jj - 1][k] : pv[k];
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            pidx[k] = idx[JH - 1][k];
-                            pv[k] = tg[JH - 1][k];
+                            for (int k = 0; k < 3; ++k) {
+                                const uint32_t t = s_t[k][r][c];
+                                tg[jj][k] = M[k].ld(Map::template unit<L>(clampi((int)(t >> 16) + wy, 0, H - 1) * W +
+                                                                          clampi((int)(t & 0xFFFFu) + wx, 0, W - 1)), sub);
+                            }
                         }
                     }
 #pragma unroll
@@ -652,7 +668,7 @@ __global__ void __launch_bounds__(256) grad_ref_tile_kernel(CostArgs a, int tile
                             for (int k = 0; k < 3; ++k) {
                                 const uint32_t t = s_t[k][r][c];
                                 const int ty = (int)(t >> 16), tx = (int)(t & 0xFFFFu);
-                                const float4 tg = M[k].ld((uint32_t)(clampi(ty + wy, 0, H - 1) * W + clampi(tx + wx, 0, W - 1)) * L + sub, false);
+                                const float4 tg = M[k].ld(Map::template unit<L>(clampi(ty + wy, 0, H - 1) * W + clampi(tx + wx, 0, W - 1)), sub);
                                 fma4(g2, fq, tg, acc);
                             }
                         }
@@ -687,6 +703,10 @@ __global__ void __launch_bounds__(256) grad_target_tile_kernel(CostArgs a, int t
     __shared__ float s_g[kStageCap];
     __shared__ uint8_t s_cx[kStageCap];           // cell column - tx_lo
     __shared__ float4 s_fq[kTileQ * L];           // the entries' own vectors
+    __shared__ uint2 s_term[4][64];               // terms of a wave's block: unit of the gathered vector, -2 g
+    // runs of a border entry: first term, staged (or sorted) position, window offset
+    __shared__ uint32_t s_rt[4][kMaxRuns], s_re[4][kMaxRuns];
+    __shared__ uint16_t s_rw[4][kMaxRuns];
     const int H = a.H, W = a.W;
     const size_t HW = (size_t)H * W;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -747,12 +767,62 @@ __global__ void __launch_bounds__(256) grad_target_tile_kernel(CostArgs a, int t
                 base + ((size_t)view(a.s, k + 1) * HW + (size_t)qy * W + qx) * CF)[idx % L];
     }
     __syncthreads();
-    Vec4Map<BUF> R;
+    using Map = Vec4Map<BUF>;
+    Map R;
     R.init(base + (size_t)view(a.s, 0) * HW * CF, HW * CF * 4);
     const int mk = view(a.s, k + 1);
     const int sub = threadIdx.x % L, part = (threadIdx.x / L) % kSplit;  // part = accumulator
-    auto rvec = [&](int py, int px, int wy, int wx) {
-        return R.ld((uint32_t)(clampi(py + wy, 0, H - 1) * W + clampi(px + wx, 0, W - 1)) * L + sub, false);
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    uint2* term = s_term[wv];
+    // term at staged (or sorted) position e, gathered at window offset (wy, wx) of its pixel
+    auto term_at = [&](uint32_t e, int wy, int wx) {
+        int py, px;
+        float g2;
+        if (staged) {
+            const uint32_t pos = s_pos[e];
+            py = (int)(pos >> 16);
+            px = (int)(pos & 0xFFFFu);
+            g2 = s_g[e];
+        } else {
+            const uint32_t pix = svals[e];
+            const int pl = (int)(pix - (size_t)b * HW);
+            py = pl / W;
+            px = pl - py * W;
+            g2 = 2.f * a.gcost[pix];
+        }
+        return make_uint2(Map::template unit<L>(clampi(py + wy, 0, H - 1) * W + clampi(px + wx, 0, W - 1)),
+                          __float_as_uint(-g2));
+    };
+    // The N U-th terms of this lane's accumulator in the block starting at term i0 of
+    // the table at `tab`, all loads in flight together; m terms in all.
+    auto add_terms = [&](auto count, const uint2* tab, uint32_t i0, uint32_t m, const float4& fq, float4& acc) {
+        constexpr int N = decltype(count)::value;
+        uint2 tt[N];
+        float4 rv[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) tt[u] = tab[u * kSplit + part];
+#pragma unroll
+        for (int u = 0; u < N; ++u) rv[u] = R.ld(tt[u].x, sub);
+        if (__all(i0 + (uint32_t)(N * kSplit) <= m)) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) fma4(__uint_as_float(tt[u].y), rv[u], fq, acc);
+        } else {
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (i0 + (uint32_t)(u * kSplit + part) < m) fma4(__uint_as_float(tt[u].y), rv[u], fq, acc);
+        }
+    };
+    // A block of B terms: as many rounds as the longest of the wave's entries needs.
+    auto add_block = [&](auto block, const uint2* tab, uint32_t i0, uint32_t m, uint32_t mmax, const float4& fq,
+                         float4& acc) {
+        constexpr int U = decltype(block)::value / kSplit;
+        const uint32_t left = mmax - i0;
+        if (U >= 4 && left <= (uint32_t)(U / 4 * kSplit))
+            add_terms(std::integral_constant<int, (U >= 4 ? U / 4 : 1)>{}, tab, i0, m, fq, acc);
+        else if (U >= 2 && left <= (uint32_t)(U / 2 * kSplit))
+            add_terms(std::integral_constant<int, (U >= 2 ? U / 2 : 1)>{}, tab, i0, m, fq, acc);
+        else
+            add_terms(std::integral_constant<int, U>{}, tab, i0, m, fq, acc);
     };
     for (int e0 = 0; e0 < kTileQ; e0 += EPB) {
         const int qx = qx0 + e0 + (int)threadIdx.x / G;
@@ -762,18 +832,15 @@ __global__ void __launch_bounds__(256) grad_target_tile_kernel(CostArgs a, int t
         float4 fq = make_float4(0.f, 0.f, 0.f, 0.f);
         if (live) fq = s_fq[(qx - qx0) * L + sub];
         const bool interior = qy >= kWin1 && qy <= H - 1 + kWin0 && qx >= kWin1 && qx <= W - 1 + kWin0;
-        // the whole wave takes the interior path or none of it does (shuffles); a tile too
-        // crowded to stage reads the same terms from the sorted lists in global memory
+        const int lg = (int)threadIdx.x % G, gbase = lane - lg;
+        bool any = true;  // (wave-uniform) some entry of the wave has terms
+        // the whole wave takes the interior path or none of it does; a tile too crowded to
+        // stage reads the same terms from the sorted lists in global memory
         if (__all(!live || interior)) {
             // the terms are the runs of the window rows wy = -3 .. 4 (cells (qy - wy, qx - 4 ..
             // qx + 3)), one after the other, in blocks of G: lane lg of the entry's G lanes
-            // finds term i0 + lg (row, staged pixel, gathered vector, 2 g) once, and the lanes of
-            // accumulator `part` take terms i0 + part, i0 + part + kSplit, ... from them by
-            // shuffles, all their loads in flight together.  A vector equal to the accumulator's
-            // previous one (a locally constant field reads one vector for the whole window) is not
-            // loaded again but copied once all loads are back; the arithmetic is unchanged.
-            constexpr int U = G / kSplit;  // terms per accumulator and block
-            const int lg = (int)threadIdx.x % G, gbase = ((int)threadIdx.x & 63) - lg;
+            // finds term i0 + lg (row, staged pixel, gathered vector, 2 g) once and leaves it
+            // in LDS, where the lanes of accumulator `part` take terms part, part + kSplit, ...
             const int j0 = qx - kWin1 - tx_lo;
             uint32_t rb[kWinN], rend[kWinN];
             uint32_t m = 0;
@@ -793,95 +860,122 @@ __global__ void __launch_bounds__(256) grad_target_tile_kernel(CostArgs a, int t
                 m += b1 - b0;
                 rend[t] = m;
             }
-            int pidx = -1;
-            float4 pv = make_float4(0.f, 0.f, 0.f, 0.f);
-            const uint32_t mmax = (uint32_t)__reduce_max_sync(~0ull, m);
+            const uint32_t mmax = G == 64 ? (uint32_t)__builtin_amdgcn_readfirstlane(m) : (uint32_t)__reduce_max_sync(~0ull, m);
+            any = mmax > 0;
             for (uint32_t i0 = 0; i0 < mmax; i0 += G) {
                 const uint32_t it = i0 + (uint32_t)lg;
-                int tidx = 0;
-                float tg2 = 0.f;
+                uint2 tm = make_uint2(0u, 0u);
                 if (it < m) {
                     int t = 0;
+                    uint32_t e = rb[0];
 #pragma unroll
-                    for (int tt = 0; tt < kWinN - 1; ++tt) t += it >= rend[tt] ? 1 : 0;
-                    const uint32_t e = rb[t] + it;
+                    for (int tt = 0; tt < kWinN - 1; ++tt) {
+                        const bool past = it >= rend[tt];
+                        t += past ? 1 : 0;
+                        e = past ? rb[tt + 1] : e;
+                    }
+                    e += it;
                     const int wy = kWin0 + t;
-                    int py, px, wx;
-                    if (staged) {
-                        const uint32_t pos = s_pos[e];
-                        tg2 = s_g[e];
-                        py = (int)(pos >> 16);
-                        px = (int)(pos & 0xFFFFu);
-                        wx = qx - tx_lo - (int)s_cx[e];
-                    } else {
-                        const uint32_t pix = svals[e];
-                        const int cc = (int)((size_t)skeys[e] - cbase - (size_t)(qy - wy) * W);
-                        const int pl = (int)(pix - (size_t)b * HW);
-                        py = pl / W;
-                        px = pl - py * W;
-                        tg2 = 2.f * a.gcost[pix];
-                        wx = qx - cc;
-                    }
-                    tidx = clampi(py + wy, 0, H - 1) * W + clampi(px + wx, 0, W - 1);
+                    const int wx = staged ? qx - tx_lo - (int)s_cx[e]
+                                          : qx - (int)((size_t)skeys[e] - cbase - (size_t)(qy - wy) * W);
+                    tm = term_at(e, wy, wx);
                 }
-                float4 rv[U];
-                float gv[U];
-                int idx[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int src = gbase + u * kSplit + part;
-                    idx[u] = __shfl(tidx, src);
-                    gv[u] = __shfl(tg2, src);
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    rv[u] = R.ld((uint32_t)idx[u] * L + sub, idx[u] == (u ? idx[u - 1] : pidx));
-                if constexpr (BUF) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (idx[u] == (u ? idx[u - 1] : pidx)) rv[u] = u ? rv[u - 1] : pv;
-                    pidx = idx[U - 1];
-                    pv = rv[U - 1];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (i0 + (uint32_t)(u * kSplit + part) < m) fma4(-gv[u], rv[u], fq, acc);
+                term[lane] = tm;
+                grad_wave_sync();
+                add_block(std::integral_constant<int, G>{}, term + gbase, i0, m, mmax, fq, acc);
+                grad_wave_sync();
             }
-        } else if (live) {
-            // the canonical order term by term; this lane adds terms part, part + kSplit, ...
-            uint32_t i = 0;
-            for (int wy = kWin0; wy <= kWin1; ++wy) {
-                int ylo, yhi;
-                preimage(qy, wy, H, ylo, yhi);
-                for (int ty = ylo; ty <= yhi; ++ty)
-                    for (int wx = kWin1; wx >= kWin0; --wx) {  // target cells in ascending x
-                        int xlo, xhi;
-                        preimage(qx, wx, W, xlo, xhi);
-                        for (int tx = xlo; tx <= xhi; ++tx) {
-                            if (staged) {
-                                const int r = ty - ty0, j = tx - tx_lo;
-                                const uint32_t e0 = s_st[r][j], e1 = s_st[r][j + 1];
-                                for (uint32_t e = e0 + (part + kSplit - i % kSplit) % kSplit; e < e1; e += kSplit) {
-                                    const uint32_t pos = s_pos[e];
-                                    fma4(-s_g[e], rvec((int)(pos >> 16), (int)(pos & 0xFFFFu), wy, wx), fq, acc);
-                                }
-                                i += e1 - e0;
-                            } else {
-                                const size_t cell = cbase + (size_t)ty * W + tx;
-                                const uint32_t e0 = start[cell], e1 = start[cell + 1];
-                                for (uint32_t e = e0 + (part + kSplit - i % kSplit) % kSplit; e < e1; e += kSplit) {
-                                    const uint32_t pix = svals[e];
-                                    const int pl = (int)(pix - (size_t)b * HW);
-                                    const int py = pl / W, px = pl - py * W;
-                                    fma4(-2.f * a.gcost[pix], rvec(py, px, wy, wx), fq, acc);
-                                }
-                                i += e1 - e0;
+        } else {
+            // entries at the border have more cells in their preimage: the wave lists the
+            // runs of its entries one entry after the other (window row, cell row, window
+            // column descending, cell column) and deals their terms the same way
+#pragma unroll 1
+            for (int en = 0; en < 64 / G; ++en) {
+                const int ex = __shfl(qx, en * G);
+                if (ex >= W) break;  // wave-uniform
+                int nr = 0, nc = 0;
+                for (int w = kWin0; w <= kWin1; ++w) {
+                    int lo, hi;
+                    preimage(qy, w, H, lo, hi);
+                    nr += max(hi - lo + 1, 0);
+                    preimage(ex, w, W, lo, hi);
+                    nc += max(hi - lo + 1, 0);
+                }
+                const int nrun = nr * nc;
+                uint32_t m = 0;
+                for (int s0 = 0; s0 < nrun; s0 += 64) {
+                    const int sg = s0 + lane;
+                    uint32_t len = 0, pos = 0;
+                    int wy = kWin0, wx = kWin1, ty = 0, tx = 0;
+                    if (sg < nrun) {
+                        int ri = sg / nc, ci = sg - ri * nc;
+                        for (; wy <= kWin1; ++wy) {
+                            int lo, hi;
+                            preimage(qy, wy, H, lo, hi);
+                            const int cnt = max(hi - lo + 1, 0);
+                            if (ri < cnt) {
+                                ty = lo + ri;
+                                break;
                             }
+                            ri -= cnt;
                         }
+                        for (; wx >= kWin0; --wx) {
+                            int lo, hi;
+                            preimage(ex, wx, W, lo, hi);
+                            const int cnt = max(hi - lo + 1, 0);
+                            if (ci < cnt) {
+                                tx = lo + ci;
+                                break;
+                            }
+                            ci -= cnt;
+                        }
+                        uint32_t p1;
+                        if (staged) {
+                            pos = s_st[ty - ty0][tx - tx_lo];
+                            p1 = s_st[ty - ty0][tx - tx_lo + 1];
+                        } else {
+                            const size_t cell = cbase + (size_t)ty * W + tx;
+                            pos = start[cell];
+                            p1 = start[cell + 1];
+                        }
+                        len = p1 - pos;
                     }
+                    uint32_t incl = len;  // inclusive sum over the lanes
+#pragma unroll
+                    for (int d = 1; d < 64; d *= 2) {
+                        const uint32_t o = (uint32_t)__shfl_up((int)incl, d);
+                        if (lane >= d) incl += o;
+                    }
+                    if (sg < nrun) {
+                        s_rt[wv][sg] = m + incl - len;
+                        s_re[wv][sg] = pos;
+                        s_rw[wv][sg] = (uint16_t)((wy - kWin0) * kWinN + (wx - kWin0));
+                    }
+                    m += (uint32_t)__shfl((int)incl, 63);
+                }
+                grad_wave_sync();
+                const bool mine = (int)threadIdx.x / G % (64 / G) == en;
+                for (uint32_t i0 = 0; i0 < m; i0 += 64) {
+                    const uint32_t it = i0 + (uint32_t)lane;
+                    uint2 tm = make_uint2(0u, 0u);
+                    if (it < m) {
+                        int lo = 0, hi = nrun;  // the last run that starts at or before the term
+                        while (hi - lo > 1) {
+                            const int mid = (lo + hi) >> 1;
+                            if (s_rt[wv][mid] <= it) lo = mid;
+                            else hi = mid;
+                        }
+                        const int wo = s_rw[wv][lo];
+                        tm = term_at(s_re[wv][lo] + (it - s_rt[wv][lo]), kWin0 + wo / kWinN, kWin0 + wo % kWinN);
+                    }
+                    term[lane] = tm;
+                    grad_wave_sync();
+                    if (mine) add_block(std::integral_constant<int, 64>{}, term, i0, m, m, fq, acc);
+                    grad_wave_sync();
+                }
             }
         }
-        const float4 sum = sum_parts<kSplit, L>(acc);
+        const float4 sum = any ? sum_parts<kSplit, L>(acc) : acc;
         if (live && part == 0)
             reinterpret_cast<float4*>(a.out + ((size_t)b * 4 * HW + (size_t)mk * HW + q) * CF)[sub] = sum;
     }
