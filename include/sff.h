@@ -326,7 +326,7 @@ sff_status sff_sparsify(const sff_params* p, int32_t batch, const uint8_t* keep,
                         const uint32_t* err, int32_t* seeds, void* stream);
 
 /* Device workspace (bytes) that sff_sgm_disparity needs for `batch` pairs
- * (about 10 + 1024 / W + 8 (dmax + 1) bytes per pixel); 0 for invalid
+ * (about 10 + 1024 / W + 8 D bytes per pixel, D = dmax + 1 rounded up to 8); 0 for invalid
  * arguments. */
 size_t sff_sgm_workspace_bytes(const sff_params* p, int32_t batch);
 

@@ -7,12 +7,13 @@
 //   L(p, d) = C(p, d) + min(L(q, d), L(q, d +- 1) + P1, min_k L(q, k) + P2)
 //             - min_k L(q, k),   q = p - r,
 // summed over the paths; the disparity minimises the sum (smallest d on ties).
-// One wave per path line, four disparities per lane: the line is walked
-// sequentially, neighbouring disparities exchanged by DPP lane moves and the
-// minimum over d by a DPP reduction; the cost of a pixel is recomputed from
-// the census words, so no cost volume is stored; each direction's costs (at
-// most 24 + P2 <= 255) are written as uint8 and summed per pixel at the end.
+// 8, 16 or 32 lanes walk a path line sequentially, eight disparities per lane in
+// packed 16-bit halves, neighbouring disparities exchanged by DPP lane moves and
+// the minimum over d by a DPP reduction; each direction's costs (at most 24 + P2 <= 255) are written as
+// uint8 and summed per pixel at the end.
+#include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "sff_internal.hpp"
 
@@ -59,49 +60,89 @@ __global__ void __launch_bounds__(256) census_kernel(const uint8_t* __restrict__
 }
 
 struct PathArgs {
-    const uint32_t* cl;  // [batch][H][W] census of the left images
-    const uint32_t* cr;  // [batch][H][kPad + W] census of the right images, padded rows
-    uint8_t* L;          // [8][batch][H][W][Dp] path costs per direction, Dp = D rounded to 4
-    int H, W, D, Dp, P1, P2, batch;
+    const uint32_t *cl, *cr;  // census words; cr rows have kPad words of pad
+    uint8_t* L;               // [8][batch][H][W][Dp] path costs per direction
+    int H, W, D, Dp, P1, P2, batch;  // Dp = D rounded up to 8
 };
 
 __constant__ int kDirs[8][2] = {{1, 0}, {-1, 0}, {0, 1}, {0, -1}, {1, 1}, {-1, -1}, {1, -1}, {-1, 1}};
 
-// Lane moves by DPP: the value of lane l - 1 (wave_shr:1) or l + 1 (wave_shl:1),
-// and the minimum over the wave (quad, half-row and row mirrors, then the four
-// rows by readlane), so the per-step chain never goes through the LDS crossbar.
-__device__ __forceinline__ int from_lane_below(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, false);
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as2(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
+__device__ __forceinline__ uint32_t as1(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+
+// The value of lane l - 1 (lane l + 1) of a group of LPL lanes, `edge` in the
+// group's first (last) lane, and the minimum over the group, by DPP (and
+// exchanges of 16- and 32-lane rows): the per-step chain never goes through the
+// LDS crossbar.
+template <int LPL>
+__device__ __forceinline__ uint32_t from_lane_below(uint32_t v, bool first, uint32_t edge) {
+    if constexpr (LPL == 16) {
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+    } else {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x138, 0xF, 0xF, false);
+        return LPL < 64 && first ? edge : o;
+    }
 }
-__device__ __forceinline__ int from_lane_above(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, false);
+template <int LPL>
+__device__ __forceinline__ uint32_t from_lane_above(uint32_t v, bool last, uint32_t edge) {
+    if constexpr (LPL == 16) {
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x101, 0xF, 0xF, false);  // row_shl:1
+    } else {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x130, 0xF, 0xF, false);
+        return LPL < 64 && last ? edge : o;
+    }
 }
+template <int LPL>
+__device__ __forceinline__ uint32_t group_min(uint32_t m) {
+    m = min(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
+    m = min(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
+    m = min(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x141, 0xF, 0xF, false));  // row_half_mirror
+    if constexpr (LPL >= 16)
+        m = min(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x140, 0xF, 0xF, false));  // row_mirror
+    if constexpr (LPL >= 32) {
+        // both rows of a pair: one result has each pair's even row twice, the other its odd row
+        const auto r = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+        m = min((uint32_t)r[0], (uint32_t)r[1]);
+    }
+    if constexpr (LPL == 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+        m = min((uint32_t)r[0], (uint32_t)r[1]);
+    }
+    return m;
+}
+
 __device__ __forceinline__ int wave_min_uniform(int m) {
-    m = min(m, __builtin_amdgcn_update_dpp(0, m, 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
-    m = min(m, __builtin_amdgcn_update_dpp(0, m, 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
-    m = min(m, __builtin_amdgcn_update_dpp(0, m, 0x141, 0xF, 0xF, false));  // row_half_mirror
-    m = min(m, __builtin_amdgcn_update_dpp(0, m, 0x140, 0xF, 0xF, false));  // row_mirror
+    m = (int)group_min<16>((uint32_t)m);
     return min(min(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
                min(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
 }
 
-// One wave per path line (4 lines per block; blockIdx.y = batch element,
-// blockIdx.z = direction); lane l holds disparities 4l .. 4l + 3, so the
-// neighbours d - 1 and d + 1 across lanes come from DPP lane moves and the
-// minimum over d from a DPP reduction: no block barrier.  The census words are
-// loaded kAhead - 1 steps ahead into a register ring.  The walk starts from
-// zero costs, which makes the first step L = C (P1, P2 >= 0).
-__global__ void __launch_bounds__(256) sgm_path_kernel(PathArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int H = a.H, W = a.W, D = a.D;
-    const int r = blockIdx.z, dx = kDirs[r][0], dy = kDirs[r][1];
-    // the horizontal lines are the longest chains (W steps): they get the
-    // issue slots first, the shorter lines fill the gaps
-    if (dy == 0) __builtin_amdgcn_s_setprio(2);
+// The smallest of three per half.  The halves are whole numbers below 0x7C00,
+// which order as the fp16 numbers of the same bits do.
+__device__ __forceinline__ u16x2 min3(u16x2 a, u16x2 b, u16x2 c) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    auto h = [](u16x2 v) { return __builtin_bit_cast(h2, v); };
+    return __builtin_bit_cast(u16x2, __builtin_elementwise_minimum(__builtin_elementwise_minimum(h(a), h(b)), h(c)));
+}
+
+// One wave walks 64 / LPL path lines of direction r; lane l of a line holds
+// disparities 2 NP l .. 2 NP l + 2 NP - 1 as NP packed pairs, their census words
+// NP / 2 16-byte loads kAhead - 1 steps ahead in a register ring.  The line's left
+// words are loaded LPL steps at a time, one step per lane, and broadcast through
+// the LDS crossbar a step ahead.  The walk starts from zero costs, which makes
+// the first step L = C (P1, P2 >= 0).
+// A disparity past the range has 255 added to its cost: its L is at least 255
+// and the line's minimum at most 24 (some disparity takes the previous minimum),
+// so it is no minimum, and as a neighbour it offers 255 + P1, no less than the
+// minimum plus P2 <= 24 + 231 that every disparity may take.
+template <int LPL, int NP>
+__device__ __forceinline__ void walk_lines(const PathArgs& a, int r, int dx, int dy, int line0, int lines) {
+    const int lane = threadIdx.x & 63, ll = lane % LPL;
+    const int H = a.H, W = a.W, d0 = 2 * NP * ll;
     const int ncol = dx != 0 ? H : 0;
-    const int lines = ncol + (dy != 0 ? W - (dx != 0 ? 1 : 0) : 0);
-    const int line = blockIdx.x * 4 + wave_id();
-    if (line >= lines) return;  // whole wave
+    const bool live = line0 + lane / LPL < lines;
+    const int line = min(line0 + lane / LPL, lines - 1);
     int x0, y0;
     if (line < ncol) {
         x0 = dx > 0 ? 0 : W - 1;
@@ -114,66 +155,167 @@ __global__ void __launch_bounds__(256) sgm_path_kernel(PathArgs a) {
     const int nx = dx > 0 ? W - x0 : (dx < 0 ? x0 + 1 : INT_MAX);
     const int ny = dy > 0 ? H - y0 : (dy < 0 ? y0 + 1 : INT_MAX);
     const int len = min(nx, ny);
-    const size_t base = (size_t)blockIdx.y * H * W;
-    const uint32_t* cl = a.cl + base;
-    const uint32_t* cr = a.cr + (size_t)blockIdx.y * H * (W + kPad) + kPad;
-    uint8_t* L8 = a.L + ((size_t)r * a.batch + blockIdx.y) * H * W * a.Dp;
-    constexpr int kBig = 1 << 28;
-    constexpr int kAhead = 4;  // 8 measured no faster
-    const int d0 = 4 * lane, lane_off = 252 - d0;
-    // right word for disparity d0 + k: row[x - d0 - k] = (row + x - 255)[lane_off + 3 - k],
-    // a uniform base plus a fixed lane offset
-    auto load = [&](int t, uint32_t& wl, uint32_t (&wr)[4]) {
-        const int x = x0 + t * dx, y = y0 + t * dy;
-        const uint32_t* rb = cr + (size_t)y * (W + kPad) + x - 255;
-        wl = cl[(size_t)y * W + x];
+    const int maxlen = __builtin_amdgcn_readfirstlane((int)__reduce_max_sync(~0ull, (unsigned)len));
+    const int minlen = __builtin_amdgcn_readfirstlane((int)__reduce_min_sync(~0ull, (unsigned)len));
+    const size_t vol = (size_t)H * W * a.Dp;
+    bool put[(NP + 3) / 4];  // Dp is a multiple of 8
 #pragma unroll
-        for (int k = 0; k < 4; ++k) wr[k] = rb[lane_off + 3 - k];
+    for (int j = 0; j < (NP + 3) / 4; ++j) put[j] = live && d0 + 8 * j < a.Dp;
+    const long stride = (long)(dy * W + dx) * a.Dp;
+    uint8_t* dst = a.L + ((size_t)r * a.batch + blockIdx.y) * vol + ((size_t)y0 * W + x0) * a.Dp + d0;
+    const int Wr = W + kPad;
+    // words x - d0 - 2 NP + 1 .. x - d0 of the right row: at least x - 255, inside the pad
+    const uint32_t* src = a.cr + ((size_t)blockIdx.y * H + y0) * Wr + kPad + x0 - d0 - (2 * NP - 1);
+    const long rstride = (long)dy * Wr + dx;
+    const uint32_t* lsrc = a.cl + ((size_t)blockIdx.y * H + y0) * W + x0;
+    const long lstride = (long)dy * W + dx;
+    constexpr int kAhead = NP == 2 ? 8 : 6;
+    constexpr uint32_t kEdge = 0x3FFF3FFFu;  // above every cost, and so with P1 or P2 added
+    const u16x2 P1 = as2((uint32_t)a.P1 * 0x10001u), P2 = as2((uint32_t)a.P2 * 0x10001u);
+    const bool firstl = ll == 0, lastl = ll == LPL - 1;
+    uint32_t past[2 * NP];
+#pragma unroll
+    for (int k = 0; k < 2 * NP; ++k) past[k] = d0 + k < a.D ? 0u : 255u;
+    struct Words {
+        uint32_t w[2 * NP];
     };
-    int Lp[4] = {0, 0, 0, 0}, prev_min = 0;
-    auto step = [&](int t, uint32_t wl, const uint32_t (&wr)[4]) {
-        int up = from_lane_below(Lp[3]), dn = from_lane_above(Lp[0]);
-        up = lane == 0 ? kBig : up;
-        dn = lane == 63 ? kBig : dn;
-        int L[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int c = __popc(wl ^ wr[k]);
-            const int lm = k == 0 ? up : Lp[k - 1];
-            const int lp = k == 3 ? dn : Lp[k + 1];
-            int m = min(Lp[k], min(lm, lp) + a.P1);
-            m = min(m, prev_min + a.P2);
-            L[k] = d0 + k < D ? c + m - prev_min : kBig;  // kBig never wins a minimum
-        }
-        if (d0 < D) {
-            const size_t p = (size_t)(y0 + t * dy) * W + x0 + t * dx;
-            uint32_t packed = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) packed |= (uint32_t)(L[k] & 0xFF) << (8 * k);
-            *reinterpret_cast<uint32_t*>(L8 + p * a.Dp + d0) = packed;
-        }
-        prev_min = wave_min_uniform(min(min(L[0], L[1]), min(L[2], L[3])));
-#pragma unroll
-        for (int k = 0; k < 4; ++k) Lp[k] = L[k];
+    auto left = [&](int t) { return lsrc[(long)min(t + ll, len - 1) * lstride]; };
+    uint32_t lw = left(0), lnext = left(LPL);
+    const int lane0 = (lane - ll) * 4;
+    auto left_word = [&](int t) {
+        return (uint32_t)__builtin_amdgcn_ds_bpermute(lane0 + 4 * (t % LPL), (int)lw);
     };
+    u16x2 L[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) L[j] = as2(0u);
+    u16x2 pm = as2(0u);  // previous minimum, in both halves
+    uint32_t wl = left_word(0);
     // ring slot i holds step t + i at the top of each group of kAhead steps;
-    // the loads never depend on a branch (steps past the end reload the last
-    // pixel), so their waits stay kAhead - 1 steps behind the issue
-    uint32_t ql[kAhead], qr[kAhead][4];
+    // GUARD: a line of the wave may end here (steps past its end reload its last pixel)
+    Words ring[kAhead];
+    int loaded = 0;  // step the next load is for
+    auto load = [&](Words& c, auto guard) {
+        __builtin_memcpy(&c, src, sizeof(Words));  // 16-byte loads, 4-byte aligned
+        if constexpr (decltype(guard)::value) {
+            src += loaded + 1 < len ? rstride : 0;
+        } else {
+            src += rstride;
+        }
+        ++loaded;
+    };
+    auto step = [&](int t, const Words& cw, auto guard) {
+        u16x2 c[NP];
 #pragma unroll
-    for (int j = 0; j < kAhead - 1; ++j) load(min(j, len - 1), ql[j], qr[j]);
+        for (int j = 0; j < NP; ++j) {
+            const uint32_t lo = __popc(wl ^ cw.w[2 * NP - 1 - 2 * j]) + past[2 * j];
+            const uint32_t hi = __popc(wl ^ cw.w[2 * NP - 2 - 2 * j]) + past[2 * j + 1];
+            c[j] = as2(hi << 16 | lo);
+        }
+        if ((t + 1) % LPL == 0) {  // uniform
+            lw = lnext;
+            lnext = left(t + 1 + LPL);
+        }
+        wl = left_word(t + 1);
+        const uint32_t below = from_lane_below<LPL>(as1(L[NP - 1]), firstl, kEdge);
+        const uint32_t above = from_lane_above<LPL>(as1(L[0]), lastl, kEdge);
+        // q[j] = disparities (2j - 1, 2j): the lower neighbours of pair j, the upper ones of pair j - 1
+        u16x2 q[NP + 1];
+        q[0] = as2(__builtin_amdgcn_alignbit(as1(L[0]), below, 16));
+#pragma unroll
+        for (int j = 1; j < NP; ++j) q[j] = as2(__builtin_amdgcn_alignbit(as1(L[j]), as1(L[j - 1]), 16));
+        q[NP] = as2(__builtin_amdgcn_alignbit(above, as1(L[NP - 1]), 16));
+        const u16x2 jump = pm + P2;
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+            L[j] = min3(__builtin_elementwise_min(q[j], q[j + 1]) + P1, L[j], jump) - pm + c[j];
+        if (!decltype(guard)::value || t < len) {
+#pragma unroll
+            for (int i = 0; i < NP; i += 4) {
+                uint32_t o[NP < 4 ? 1 : 2];
+#pragma unroll
+                for (int j = 0; j < std::min(NP, 4); j += 2)
+                    o[j / 2] = __builtin_amdgcn_perm(as1(L[i + j + 1]), as1(L[i + j]), 0x06040200u);
+                if (put[i / 4]) {  // non-temporal: wta_kernel reads them only after the last line (177 -> 132 us)
+                    if constexpr (NP == 2)
+                        __builtin_nontemporal_store(o[0], reinterpret_cast<uint32_t*>(dst));
+                    else
+                        __builtin_nontemporal_store((uint64_t)o[1] << 32 | o[0], reinterpret_cast<uint64_t*>(dst + 2 * i));
+                }
+            }
+        }
+        dst += stride;
+        u16x2 m2 = __builtin_elementwise_min(L[0], L[1]);
+#pragma unroll
+        for (int j = 2; j < NP; j += 2) m2 = min3(m2, L[j], L[j + 1]);
+        pm = as2(group_min<LPL>(min(as1(m2) & 0xFFFFu, as1(m2) >> 16)) * 0x10001u);
+    };
+    using Open = std::integral_constant<bool, false>;
+    using Guard = std::integral_constant<bool, true>;
+#pragma unroll
+    for (int j = 0; j < kAhead - 1; ++j) load(ring[j], Guard{});
     int t = 0;
-    for (; t + kAhead <= len; t += kAhead) {
+    // every load's successor, step t + 2 kAhead - 1, is inside every line
+    for (; t + 2 * kAhead <= minlen; t += kAhead) {
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
-            const int jn = (j + kAhead - 1) % kAhead;
-            load(min(t + j + kAhead - 1, len - 1), ql[jn], qr[jn]);
-            step(t + j, ql[j], qr[j]);
+            load(ring[(j + kAhead - 1) % kAhead], Open{});
+            step(t + j, ring[j], Open{});
+        }
+    }
+    for (; t + kAhead <= maxlen; t += kAhead) {
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            load(ring[(j + kAhead - 1) % kAhead], Guard{});
+            step(t + j, ring[j], Guard{});
         }
     }
 #pragma unroll
     for (int j = 0; j < kAhead - 1; ++j)
-        if (t + j < len) step(t + j, ql[j], qr[j]);
+        if (t + j < maxlen) step(t + j, ring[j], Guard{});
+}
+
+// Blocks per direction: horizontal, vertical, diagonal.
+struct PathBlocks {
+    int h, v, d;
+};
+
+// 4 waves per block, blockIdx.y = batch element; LPL lanes per line with 2 NP
+// disparities each, HL lanes with four disparities each for a horizontal line.
+// The horizontal lines are the longest chains (W serial steps): they take the
+// fewest operations per step, the first blocks (which lie on different CUs; alone
+// 178 us against 248 us with other blocks between them) and the issue slots first.
+// Bound: the vector ALU (about 275 us of issue for the case below); with the
+// stores left out it takes 318 us.
+// 375 x 1242, D = 193: 334 us.  Measured against it: four disparities per lane in
+// 32 bits with one wave per line and four 4-byte loads of right words per step,
+// 471 us (vector ALU and texture data path 80 % busy); all lines with eight
+// disparities per lane, 382 us; costs formed once and read as bytes, 550 us;
+// sixteen disparities per lane, 335 us.
+template <int LPL, int NP, int HL>
+__global__ void __launch_bounds__(256, 4) sgm_path_kernel(PathArgs a, PathBlocks n) {
+    const int b = blockIdx.x;
+    if (b < 2 * n.h) {
+        const int r = b >= n.h, line0 = ((b - r * n.h) * 4 + wave_id()) * (64 / HL);
+        if (line0 >= a.H) return;  // whole wave
+        __builtin_amdgcn_s_setprio(2);
+        walk_lines<HL, 2>(a, r, kDirs[r][0], 0, line0, a.H);
+        return;
+    }
+    const int vd = b - 2 * n.h - 2 * n.v;  // first block of the diagonals: 0
+    const int r = vd < 0 ? 2 + (vd + n.v >= 0) : 4 + vd / n.d;
+    const int i = vd < 0 ? vd + (r == 2 ? 2 : 1) * n.v : vd % n.d;
+    const int dx = kDirs[r][0], dy = kDirs[r][1];
+    const int lines = dx != 0 ? a.H + a.W - 1 : a.W, line0 = (i * 4 + wave_id()) * (64 / LPL);
+    if (line0 >= lines) return;
+    walk_lines<LPL, NP>(a, r, dx, dy, line0, lines);
+}
+
+template <int LPL, int NP, int HL>
+void launch_paths(const PathArgs& a, hipStream_t st) {
+    constexpr int per = 4 * (64 / LPL), hper = 4 * (64 / HL);  // lines per block
+    const PathBlocks n{(a.H + hper - 1) / hper, (a.W + per - 1) / per, (a.H + a.W - 1 + per - 1) / per};
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(sgm_path_kernel<LPL, NP, HL>), dim3(2 * n.h + 2 * n.v + 4 * n.d, a.batch),
+                       dim3(256), 0, st, a, n);
 }
 
 // Winner-take-all over the summed path costs: one wave per pixel, lane l
@@ -230,6 +372,9 @@ __global__ void __launch_bounds__(256) fill_kernel(const int16_t* __restrict__ h
     fill[o] = (valid[o] || (x - d0 >= 0 && e <= tau && e >= -tau)) ? 1 : 0;
 }
 
+// Disparities of a pixel in the path costs: D rounded up to 8.
+inline int sgm_dp(int D) { return (D + 7) & ~7; }
+
 struct SgmWs {
     size_t grey, census, census_r, S, total;
 };
@@ -242,7 +387,7 @@ SgmWs sgm_ws(const sff_params& p, int batch) {
     L.census = al(2 * n * npx);
     L.census_r = L.census + al(n * npx * sizeof(uint32_t));
     L.S = L.census_r + al(n * p.H * (p.W + (size_t)kPad) * sizeof(uint32_t));
-    L.total = L.S + al(8 * n * npx * (size_t)((p.dmax + 4) & ~3));
+    L.total = L.S + al(8 * n * npx * (size_t)sgm_dp(p.dmax + 1));
     return L;
 }
 
@@ -284,9 +429,15 @@ extern "C" sff_status sff_sgm_disparity(const sff_params* p, int32_t batch, cons
     hipLaunchKernelGGL(census_kernel, pgrid, dim3(256), 0, st, gl, cl, H, W, 0);
     hipLaunchKernelGGL(census_kernel, dim3((H * (W + kPad) + 255) / 256, batch), dim3(256), 0, st, gr, cr,
                        H, W, kPad);
-    const int Dp = (D + 3) & ~3;
+    const int Dp = sgm_dp(D);
     PathArgs a{cl, cr, L8, H, W, D, Dp, P1, P2, batch};
-    hipLaunchKernelGGL(sgm_path_kernel, dim3((H + W - 1 + 3) / 4, batch, 8), dim3(256), 0, st, a);
+    // the fewest lanes per line that hold all disparities: the most lines per wave
+    if (Dp <= 64)
+        launch_paths<8, 4, 16>(a, st);
+    else if (Dp <= 128)
+        launch_paths<16, 4, 32>(a, st);
+    else
+        launch_paths<32, 4, 64>(a, st);
     hipLaunchKernelGGL(wta_kernel, dim3((npx + 4 * kWtaPix - 1) / (4 * kWtaPix), batch), dim3(256), 0, st,
                        reinterpret_cast<const uint32_t*>(L8), disp, npx, D, Dp / 4, batch);
     return launch_status();
