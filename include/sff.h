@@ -242,14 +242,15 @@ sff_status sff_init_nn_bins(const sff_params* p, int32_t batch, int32_t dir, int
  * hyp_coarse: level-(k+1) field [ndir][batch][H(k+1)][W(k+1)][4] or NULL;
  *   must not overlap hyp.
  * hyp/cost: level-k field, read and written in place.
- * Two kernels with identical results gather the descriptors: one lane per
- *   pixel below 20000 pixel updates per launch (ndir * batch * H(k) *
- *   ceil(W(k) / 2)), wave-cooperative loads otherwise (32 pixels per wave below
- *   50000 updates, 64 above); the environment variable SFF_MATCH_EVAL=lane|
- *   coop|coop-narrow|coop-wide|coop-narrow-32|coop-wide-32 forces one (testing
- *   and timing).  The cooperative loads use 32-bit offsets: for descriptor maps of
- *   2 GiB or more (H * W > 16.7 M at C = 3 or 4) the per-lane kernel runs
- *   whatever the variable says.
+ * Wave-cooperative gathers: below 50000 pixel updates per launch (ndir * batch *
+ *   H(k) * ceil(W(k) / 2)) 16 pixels per wave (32 for odd C), three views a round;
+ *   above, 32 pixels per wave, groups of 4 neighbours and 6 samples, view by
+ *   view.  They use 32-bit offsets: for descriptor maps of 2 GiB or more
+ *   (H * W > 16.7 M at C = 3 or 4) each lane gathers its own records.  With
+ *   dir = SFF_DIR_BOTH and from 100000 to a million updates the two fields run
+ *   on two streams, as in sff_match_level_bins.  SFF_MATCH_EVAL=lane|
+ *   coop-narrow|coop-wide|coop-narrow-32|coop-wide-32|coop-46-32|coop-xts and
+ *   SFF_MATCH_SPLIT=0|1 force one (identical results; testing and timing).
  * Errors: SFF_ERR_INVALID_ARG (also for level >= levels - 1 with a non-NULL
  *   hyp_coarse, and for overlapping hyp/hyp_coarse). */
 sff_status sff_match_level(const sff_params* p, int32_t batch, int32_t dir, int32_t level,

@@ -109,100 +109,6 @@ struct Views {
 // s * v for a direction s = +1 or -1.
 __device__ __forceinline__ int dirmul(int s, int v) { return s > 0 ? v : -v; }
 
-// Descriptor gathers of one wave, done cooperatively.  Lane l of the wave owns
-// one pixel (its reference descriptor and hypothesis); a descriptor is P = 2C
-// pieces of 16 bytes.  Gathering one descriptor per owner takes P wave-wide
-// loads; in load k lane l fetches piece w = f mod P of owner o = f / P, with
-// f = 64 k + l, so the lanes of one load read consecutive pieces of a few
-// records (each inside one cache line) instead of 64 unrelated lines.  Each
-// lane keeps the reference pieces of its (o, w) slots in registers, forms the
-// piece's partial squared distance, and the P partials of an owner are summed
-// through the wave's LDS slice.  Gathers are buffer loads with 32-bit byte
-// offsets from the map's base (one add per load instead of 64-bit address
-// arithmetic), so a map must be smaller than 2 GiB.  Owners without a target
-// (tp < 0) gather record 0 and have their sum zeroed once, after the
-// reduction, instead of each piece being predicated.  A wave has O owners
-// (64, or 32 to put twice as many waves on a level too small to fill the chip;
-// lanes O..63 then only help gather), so a descriptor gather is K = O P / 64
-// wave-wide loads.
-template <int C, int O>
-struct Coop {
-    static_assert(O == 64 || O == 32, "owners per wave");
-    static constexpr int P = 2 * C;
-    static constexpr int K = O * P / 64;
-    static constexpr int RS = 2 * kRecC<C>;  // record stride in 16-byte pieces
-    uint4 refp[K];                          // reference piece of slot k
-    uint32_t* part;                         // this wave's LDS slice [64 P]
-    int lane;
-    uint32_t bytes;                         // bytes of one map
-
-    __device__ __forceinline__ static int owner(int k, int lane) { return (64 * k + lane) / P; }
-    __device__ __forceinline__ static int piece(int k, int lane) { return (64 * k + lane) % P; }
-
-    // Piece (k, lane) of the record at byte offset ob of the slot's owner.
-    __device__ __forceinline__ uint4 gather(__amdgpu_buffer_rsrc_t rs, int ob, int k) const {
-        const int off = __shfl(ob, owner(k, lane)) + piece(k, lane) * 16;
-        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-    }
-
-    // Load the reference pieces; pix_of(o) is owner o's pixel in map R.
-    template <class F>
-    __device__ __forceinline__ void load_ref(const uint4* __restrict__ R, F pix_of) {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            refp[k] = R[(size_t)pix_of(owner(k, lane)) * RS + piece(k, lane)];
-    }
-
-    // Squared distance between each owner's reference descriptor and the
-    // descriptor of pixel tp in map M (0 for owners passing tp < 0).  Must be
-    // called by all lanes of the wave.
-    __device__ __forceinline__ uint32_t ssd(const uint4* M, int tp) {
-        const __amdgpu_buffer_rsrc_t rs = map_rsrc(M, bytes);
-        const int ob = max(tp, 0) * (RS * 16);
-        uint4 v[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = gather(rs, ob, k);
-#pragma unroll
-        for (int k = 0; k < K; ++k) part[64 * k + lane] = (uint32_t)piece_ssd(refp[k], v[k], 0);
-        wave_sync();
-        uint32_t c = 0;
-        const int ol = lane & (O - 1);  // lanes past the owners read a valid slot
-#pragma unroll
-        for (int w = 0; w < P; ++w) c += part[ol * P + w];
-        wave_sync();
-        return tp >= 0 ? c : 0u;
-    }
-
-    // ssd for N targets per owner at once (all gathers in flight together);
-    // needs a slice of N * 64 K words.
-    template <int N>
-    __device__ __forceinline__ void ssdN(const uint4* M, const int (&tp)[N], uint32_t (&c)[N]) {
-        const __amdgpu_buffer_rsrc_t rs = map_rsrc(M, bytes);
-        int ob[N];
-#pragma unroll
-        for (int m = 0; m < N; ++m) ob[m] = max(tp[m], 0) * (RS * 16);
-        uint4 v[N][K];
-#pragma unroll
-        for (int m = 0; m < N; ++m)
-#pragma unroll
-            for (int k = 0; k < K; ++k) v[m][k] = gather(rs, ob[m], k);
-#pragma unroll
-        for (int m = 0; m < N; ++m)
-#pragma unroll
-            for (int k = 0; k < K; ++k) part[64 * (m * K + k) + lane] = (uint32_t)piece_ssd(refp[k], v[m][k], 0);
-        wave_sync();
-        const int ol = lane & (O - 1);
-#pragma unroll
-        for (int m = 0; m < N; ++m) {
-            c[m] = 0;
-#pragma unroll
-            for (int w = 0; w < P; ++w) c[m] += part[64 * K * m + ol * P + w];
-            c[m] = tp[m] >= 0 ? c[m] : 0u;
-        }
-        wave_sync();
-    }
-};
-
 // eq. (1): temporal (x+u, y+v), stereo (x - s d0, y), cross (x+u - s d1, y+v),
 // each target clamped to the image.  The three squared distances are
 // non-negative, so once a partial sum reaches `bound` the candidate cannot be
@@ -214,11 +120,10 @@ struct Coop {
 // poor candidate soonest (measured 1.8% faster at level 0 than temporal,
 // stereo, cross).
 //
-// Two evaluators with the same results: LaneEval gathers each lane's records
-// itself (fewest instructions and round trips; best when a launch has too few
-// waves to fill the chip), CoopEval gathers cooperatively (fewest cache-line
-// lookups; best when the chip is full).  CoopEval must be called by all lanes
-// of the wave.
+// Evaluators with the same results: per lane (LaneEval, BinLane: fewest
+// instructions and the shortest chain of round trips; for launches too small to
+// fill the chip) and cooperative (PatchCoop: fewest cache-line lookups), which
+// must be called by all lanes of the wave.
 template <int C>
 struct LaneEval {
     static constexpr int kOwners = 64;
@@ -265,110 +170,11 @@ struct LaneEval {
                                                 uint32_t, uint32_t (&)[N]) {}
 };
 
-// PG neighbour candidates and RG random-search samples are scored together
-// (their gathers in flight at once); the LDS slice holds the partials of the
-// larger group.
-template <int C, int PG, int RG, int O = 64>
-struct CoopEval {
-    static constexpr int kOwners = O;
-    static constexpr int kPG = PG, kRG = RG;
-    static constexpr int kGroup = PG > RG ? PG : RG;
-    static constexpr int kLdsWords = kGroup * 64 * Coop<C, O>::K;
-    static constexpr bool kGroups = true;
-    const uint4 *T, *S, *X, *R;
-    int H, W, s;
-    Coop<C, O> cp;
-
-    __device__ __forceinline__ void setup(const MatchArgs& a, int b, int sd) {
-        const Views v(a, b, sd);
-        R = reinterpret_cast<const uint4*>(v.R);
-        T = reinterpret_cast<const uint4*>(v.T);
-        S = reinterpret_cast<const uint4*>(v.S);
-        X = reinterpret_cast<const uint4*>(v.X);
-        H = a.H;
-        W = a.W;
-        s = sd;
-        cp.bytes = (uint32_t)a.img_bytes;
-    }
-
-    template <class F>
-    __device__ __forceinline__ void init(int, int, int lane, uint32_t* part, F pix_of) {
-        cp.lane = lane;
-        cp.part = part;
-        cp.load_ref(R, pix_of);
-    }
-
-    __device__ __forceinline__ uint32_t cost_below(bool want, int x, int y, const Hyp& h,
-                                                   uint32_t bound) {
-        const int ty = clampi(y + h.v, 0, H - 1);
-        const int txX = clampi(x + h.u - dirmul(s, h.d1), 0, W - 1);
-        uint32_t c = cp.ssd(X, want ? ty * W + txX : -1);
-        bool alive = want && c < bound;
-        if (__any(alive)) {
-            const int txT = clampi(x + h.u, 0, W - 1);
-            c += cp.ssd(T, alive ? ty * W + txT : -1);
-            alive = alive && c < bound;
-            if (__any(alive)) {
-                const int txS = clampi(x - dirmul(s, h.d0), 0, W - 1);
-                c += cp.ssd(S, alive ? y * W + txS : -1);
-            }
-        }
-        return c;
-    }
-
-    // cost_below for N candidates of each lane, their gathers issued together
-    // view by view; same results as N calls with the same bound.
-    template <int N>
-    __device__ __forceinline__ void cost_belowN(const bool (&w)[N], const Hyp (&h)[N], int x, int y,
-                                                uint32_t bound, uint32_t (&c)[N]) {
-        static_assert(N <= kGroup, "LDS slice sized for kGroup candidates");
-        int ty[N], tp[N];
-        bool al[N];
-        bool any = false;
-#pragma unroll
-        for (int m = 0; m < N; ++m) {
-            ty[m] = clampi(y + h[m].v, 0, H - 1);
-            tp[m] = w[m] ? ty[m] * W + clampi(x + h[m].u - dirmul(s, h[m].d1), 0, W - 1) : -1;
-        }
-        cp.template ssdN<N>(X, tp, c);
-#pragma unroll
-        for (int m = 0; m < N; ++m) {
-            al[m] = w[m] && c[m] < bound;
-            any = any || al[m];
-            tp[m] = al[m] ? ty[m] * W + clampi(x + h[m].u, 0, W - 1) : -1;
-        }
-        if (!__any(any)) return;
-        uint32_t d[N];
-        cp.template ssdN<N>(T, tp, d);
-        any = false;
-#pragma unroll
-        for (int m = 0; m < N; ++m) {
-            c[m] += d[m];
-            al[m] = al[m] && c[m] < bound;
-            any = any || al[m];
-            tp[m] = al[m] ? y * W + clampi(x - dirmul(s, h[m].d0), 0, W - 1) : -1;
-        }
-        if (!__any(any)) return;
-        cp.template ssdN<N>(S, tp, d);
-#pragma unroll
-        for (int m = 0; m < N; ++m) c[m] += d[m];
-    }
-};
-
-// Bin-plane evaluators: eq. (1) as 16 x the bin-grid squared distance of the
-// reference patch and the three target patches, with the same early-out and
-// view order as the descriptor evaluators.  A patch is P = bin_pieces(C)
-// pieces of 16 bytes, contiguous (4 entries of 4 plane rows; 4 pieces of
-// packed bins for C = 3).
-//
-// BinLane: each lane gathers its own patches (fewest instructions and the
-// shortest chain of round trips; for launches too small to fill the chip).
-// BinCoop: the patches of a wave's owners are gathered cooperatively, as in
-// Coop, so one wave-wide load reads the whole patches of a few owners instead
-// of one piece each of 64 unrelated patches: the texture path handles about
-// one 64-byte sector per clock per CU, and with the planes resident in the L2
-// that, not the L2, bounds a full chip.  Owners without a target get an offset
-// past the map's range (the load returns zeros without a memory access).
+// Bin planes: eq. (1) as 16 x the bin-grid squared distance of the reference
+// patch and the three target patches, with the same early-out and view order as
+// the descriptor records.  A patch is P = bin_pieces(C) pieces of 16 bytes,
+// contiguous (4 entries of 4 plane rows; 4 pieces of packed bins for C = 3).
+// BinLane: each lane gathers its own patches.
 template <int C>
 struct BinLane {
     static constexpr int P = bin_pieces(C);
@@ -435,11 +241,57 @@ struct BinLane {
                                                 uint32_t, uint32_t (&)[N]) {}
 };
 
-template <int C, int PG, int RG, int O = 64, bool XTS = false>
-struct BinCoop {
-    static_assert(O == 64 || O == 32 || O == 16, "owners per wave");
-    static_assert(O * bin_pieces(C) % 64 == 0, "whole loads per gather");
+// What a cooperative gather reads: P contiguous pieces of 16 bytes per patch at
+// the byte offset of a target, a piece's squared distance to the reference
+// piece, and the factor from those sums to the cost.  Bin patches:
+template <int C>
+struct BinMap {
     static constexpr int P = bin_pieces(C);
+    static constexpr uint32_t kScale = 16u;
+    using Ref = BinRef<C>;
+    BinAddr<C> addr;
+    __device__ __forceinline__ void setup(const MatchArgs& a) {
+        addr.sh = a.sh;
+        addr.Hq = a.Hq;
+        addr.RS = a.Wq * bin_entry_bytes(C);
+    }
+    __device__ __forceinline__ int operator()(int X, int Y) const { return addr(X, Y); }
+    static __device__ __forceinline__ Ref ref(uint4 v) { return bin_ref<C>(v); }
+    static __device__ __forceinline__ int ssd(const Ref& r, uint4 v, int acc) { return bin_piece_ssd<C>(r, v, acc); }
+};
+
+// Descriptor records (2 C pieces, aligned to their padded size: one cache line):
+template <int C>
+struct RecMap {
+    static constexpr int P = 2 * C;
+    static constexpr uint32_t kScale = 1u;
+    using Ref = uint4;
+    int W;
+    __device__ __forceinline__ void setup(const MatchArgs& a) { W = a.W; }
+    __device__ __forceinline__ int operator()(int X, int Y) const { return (Y * W + X) * (32 * kRecC<C>); }
+    static __device__ __forceinline__ Ref ref(uint4 v) { return v; }
+    static __device__ __forceinline__ int ssd(const Ref& r, uint4 v, int acc) { return piece_ssd(r, v, acc); }
+};
+
+// The patches of a wave's O owners (lane l owns one pixel: its reference patch
+// and hypothesis) gathered cooperatively: gathering one patch per owner takes
+// K = O P / 64 wave-wide loads; in load k lane l fetches piece f mod P of owner
+// f / P, f = 64 k + l, so one load reads the whole patches of a few owners
+// instead of one piece each of 64 unrelated ones: the texture path handles about
+// one 64-byte sector per clock per CU, and with the maps resident in the L2 that,
+// not the L2, bounds a full chip.  Each lane keeps the reference pieces of its
+// slots in registers, forms the pieces' partial squared distances, and the P
+// partials of an owner are summed through the wave's LDS slice.  Owners without
+// a target get an offset past the map's range (the load returns zeros without a
+// memory access).  With O < 64 lanes O..63 only help (more waves for a level too
+// small to fill the chip).  PG neighbour candidates and RG random-search samples
+// are scored together, their gathers in flight at once; XTS: all three views in
+// one round.
+template <class M, int PG, int RG, int O = 64, bool XTS = false>
+struct PatchCoop {
+    static_assert(O == 64 || O == 32 || O == 16, "owners per wave");
+    static_assert(O * M::P % 64 == 0, "whole loads per gather");
+    static constexpr int P = M::P;
     static constexpr int K = O * P / 64;  // wave-wide loads per patch gather
     static constexpr int kOwners = O;
     static constexpr int kPG = PG, kRG = RG;
@@ -447,9 +299,9 @@ struct BinCoop {
     static constexpr int kLdsWords = kGroup * 64 * K;
     static constexpr bool kGroups = true;
     __amdgpu_buffer_rsrc_t rR, rT, rS, rX;
-    BinAddr<C> addr;
+    M addr;
     int H, W, s;
-    BinRef<C> refp[K];  // reference piece of slot k
+    typename M::Ref refp[K];  // reference piece of slot k
     uint32_t* part;  // this wave's LDS slice
     int lane;
 
@@ -463,9 +315,7 @@ struct BinCoop {
         H = a.H;
         W = a.W;
         s = sd;
-        addr.sh = a.sh;
-        addr.Hq = a.Hq;
-        addr.RS = a.Wq * bin_entry_bytes(C);
+        addr.setup(a);
     }
 
     __device__ __forceinline__ static int owner(int k, int l) { return (64 * k + l) / P; }
@@ -486,11 +336,11 @@ struct BinCoop {
         const int ob = addr(x, y);
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            refp[k] = bin_ref<C>(
+            refp[k] = M::ref(
                 __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rR, slot_off(ob, k), 0, 0)));
     }
 
-    // Squared distances (x 16) of N patches per owner, all gathers in flight
+    // Squared distances (scaled) of N patches per owner, all gathers in flight
     // together; ob[m] = kNoTarget marks no target (result 0).  Must be called by all
     // lanes of the wave.
     // Patch m is read through rs_of(m) (views may differ between patches).
@@ -511,7 +361,7 @@ struct BinCoop {
         for (int m = 0; m < N; ++m)
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                part[64 * (m * K + k) + lane] = (uint32_t)bin_piece_ssd<C>(refp[k], v[m][k], 0);
+                part[64 * (m * K + k) + lane] = (uint32_t)M::ssd(refp[k], v[m][k], 0);
         wave_sync();
         const int ol = lane & (O - 1);  // lanes past the owners read a valid slot
 #pragma unroll
@@ -519,12 +369,12 @@ struct BinCoop {
             uint32_t t = 0;
 #pragma unroll
             for (int w = 0; w < P; ++w) t += part[64 * K * m + ol * P + w];
-            c[m] = ob[m] != kNoTarget ? 16u * t : 0u;
+            c[m] = ob[m] != kNoTarget ? M::kScale * t : 0u;
         }
         wave_sync();
     }
 
-    // The cross, temporal and stereo distances (x 16) summed, of N candidates
+    // The cross, temporal and stereo distances summed, of N candidates
     // per owner: the 3 N patches of ob (cross ones first, then temporal, then
     // stereo; a candidate without a target has kNoTarget in all three, result
     // 0) gathered together, and a slot's three pieces summed before the
@@ -548,9 +398,9 @@ struct BinCoop {
         for (int m = 0; m < N; ++m)
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                int acc = bin_piece_ssd<C>(refp[k], v[m][k], 0);
-                acc = bin_piece_ssd<C>(refp[k], v[N + m][k], acc);
-                part[64 * (m * K + k) + lane] = (uint32_t)bin_piece_ssd<C>(refp[k], v[2 * N + m][k], acc);
+                int acc = M::ssd(refp[k], v[m][k], 0);
+                acc = M::ssd(refp[k], v[N + m][k], acc);
+                part[64 * (m * K + k) + lane] = (uint32_t)M::ssd(refp[k], v[2 * N + m][k], acc);
             }
         wave_sync();
         const int ol = lane & (O - 1);  // lanes past the owners read a valid slot
@@ -559,7 +409,7 @@ struct BinCoop {
             uint32_t t = 0;
 #pragma unroll
             for (int w = 0; w < P; ++w) t += part[64 * K * m + ol * P + w];
-            c[m] = ob[m] != kNoTarget ? 16u * t : 0u;
+            c[m] = ob[m] != kNoTarget ? M::kScale * t : 0u;
         }
         wave_sync();
     }
@@ -856,49 +706,9 @@ sff_status launch_level(const MatchArgs& a, int iters, hipStream_t st) {
     return launch_status();
 }
 
-// From this many pixel updates per launch the wider groups (4 neighbours,
-// 3 samples) pay off; below it their registers cost more occupancy than the
-// extra gathers in flight gain (measured at level 0 and 1 of the KITTI-size
-// pair: 4/3 takes 1.48 vs 1.53 ms at level 0 and 0.49 vs 0.48 ms at level 1
-// against 2/3; one candidate at a time 1.71 and 0.47 ms).
-constexpr long kWideMinUpdates = 262144;
-
-// Below this many pixel updates per launch a cooperative wave has 32 owners:
-// twice the waves, half the gather registers (level 2 of the KITTI-size pair,
-// 29,328 updates, 564 waves with 64 owners: 0.203 vs 0.236 ms per step;
-// level 1, 116,936 updates: 0.471 vs 0.469 ms; level 0: 1.470 vs 1.442 ms).
+// Below this many pixel updates per launch a cooperative wave has 32 or 16
+// owners: more waves, fewer gather registers.
 constexpr long kHalfOwnersMaxUpdates = 50000;
-
-// Largest descriptor map (bytes) the cooperative evaluators address.
-constexpr size_t kMaxCoopMapBytes = 0x7FFFFFFF;
-
-// SFF_MATCH_EVAL = "lane", "coop" (group sizes and owners by size),
-// "coop-narrow", "coop-wide" (64 owners) or "coop-narrow-32", "coop-wide-32"
-// (32 owners) forces an evaluator (all give identical results; the switch
-// exists to test and time each one); anything else: auto.
-template <int C>
-sff_status run_level(const MatchArgs& a, int iters, hipStream_t st) {
-    const long updates = (long)a.ndir * a.batch * a.Hk * ((a.Wk + 1) / 2);
-    bool coop = updates >= kCoopMinUpdates, wide = updates >= kWideMinUpdates;
-    bool half = updates < kHalfOwnersMaxUpdates;
-    if (const char* e = std::getenv("SFF_MATCH_EVAL")) {
-        if (std::strcmp(e, "lane") == 0) coop = false;
-        if (std::strcmp(e, "coop") == 0) coop = true;
-        if (std::strcmp(e, "coop-narrow") == 0) coop = true, wide = false, half = false;
-        if (std::strcmp(e, "coop-wide") == 0) coop = true, wide = true, half = false;
-        if (std::strcmp(e, "coop-narrow-32") == 0) coop = true, wide = false, half = true;
-        if (std::strcmp(e, "coop-wide-32") == 0) coop = true, wide = true, half = true;
-    }
-    // The cooperative gathers address a map with 32-bit offsets.
-    if (a.img_bytes > kMaxCoopMapBytes) coop = false;
-    if (!coop) return launch_level<C, LaneEval<C>>(a, iters, st);
-    if (half) {
-        if (wide) return launch_level<C, CoopEval<C, 4, 3, 32>>(a, iters, st);
-        return launch_level<C, CoopEval<C, 2, 3, 32>>(a, iters, st);
-    }
-    if (wide) return launch_level<C, CoopEval<C, 4, 3>>(a, iters, st);
-    return launch_level<C, CoopEval<C, 2, 3>>(a, iters, st);
-}
 
 // From this many updates per half-step the bin matcher scores one candidate
 // at a time with all three views per round (below: 4 neighbours and 3
@@ -934,16 +744,16 @@ template <int C>
 sff_status launch_bin_pick(int pick, const MatchArgs& a, int iters, hipStream_t st) {
     switch (pick) {
         case 0: return launch_level<C, BinLane<C>>(a, iters, st);
-        case 1: return launch_level<C, BinCoop<C, 2, 3>>(a, iters, st);
-        case 2: return launch_level<C, BinCoop<C, 2, 3, 32>>(a, iters, st);
-        case 3: return launch_level<C, BinCoop<C, 4, 3, 32>>(a, iters, st);
-        case 5: return launch_level<C, BinCoop<C, 1, 1, 64, true>>(a, iters, st);
+        case 1: return launch_level<C, PatchCoop<BinMap<C>, 2, 3>>(a, iters, st);
+        case 2: return launch_level<C, PatchCoop<BinMap<C>, 2, 3, 32>>(a, iters, st);
+        case 3: return launch_level<C, PatchCoop<BinMap<C>, 4, 3, 32>>(a, iters, st);
+        case 5: return launch_level<C, PatchCoop<BinMap<C>, 1, 1, 64, true>>(a, iters, st);
         case 6:
-            if constexpr (16 * bin_pieces(C) % 64 == 0) return launch_level<C, BinCoop<C, 4, 6, 16, true>>(a, iters, st);
+            if constexpr (16 * bin_pieces(C) % 64 == 0) return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 16, true>>(a, iters, st);
             break;
         default: break;
     }
-    return launch_level<C, BinCoop<C, 4, 6, 32>>(a, iters, st);
+    return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 32>>(a, iters, st);
 }
 
 // The forward and inverse fields of a level are independent (each reads only
@@ -957,6 +767,28 @@ sff_status launch_bin_pick(int pick, const MatchArgs& a, int iters, hipStream_t 
 // 0.167 vs 0.176 ms) one launch per half-step for both fields is faster.
 // Identical fields either way.
 constexpr long kSplitMinUpdates = 100000;
+
+template <class F>
+sff_status run_split(const MatchArgs& a, hipStream_t st, F launch) {
+    // field 0 (forward) on the caller's stream, field 1 (inverse) on the helper
+    MatchArgs f0 = a, f1 = a;
+    f0.ndir = f1.ndir = 1;
+    f0.dir0 = 1;
+    f1.dir0 = -1;
+    const size_t fine = (size_t)a.batch * a.Hk * a.Wk, coarse = (size_t)a.batch * a.Hc * a.Wc;
+    f1.hyp = a.hyp + 4 * fine;
+    f1.cost = a.cost + fine;
+    if (a.hyp_coarse) f1.hyp_coarse = a.hyp_coarse + 4 * coarse;
+    std::lock_guard<std::mutex> lock(helper_lock());
+    HelperStream* hs = helper_for_current_device();
+    if (!hs) return launch(a, st);
+    if (!helper_fork(hs, st)) return SFF_ERR_HIP;
+    const sff_status r0 = launch(f0, st);
+    const sff_status r1 = launch(f1, hs->stream);
+    // join even after a launch error, so the caller's stream never runs ahead
+    if (!helper_join(hs, st)) return SFF_ERR_HIP;
+    return r0 != SFF_OK ? r0 : r1;
+}
 
 // SFF_MATCH_SPLIT = "0" or "1" forces one launch sequence for both fields or
 // the two-stream split (identical results; the switch exists to test and time
@@ -983,24 +815,77 @@ sff_status run_bin_level(const MatchArgs& a, int iters, hipStream_t st) {
         if (std::strcmp(e, "1") == 0) split = a.ndir == 2;
     }
     if (!split) return launch_bin_pick<C>(pick, a, iters, st);
-    // field 0 (forward) on the caller's stream, field 1 (inverse) on the helper
-    MatchArgs f0 = a, f1 = a;
-    f0.ndir = f1.ndir = 1;
-    f0.dir0 = 1;
-    f1.dir0 = -1;
-    const size_t fine = (size_t)a.batch * a.Hk * a.Wk, coarse = (size_t)a.batch * a.Hc * a.Wc;
-    f1.hyp = a.hyp + 4 * fine;
-    f1.cost = a.cost + fine;
-    if (a.hyp_coarse) f1.hyp_coarse = a.hyp_coarse + 4 * coarse;
-    std::lock_guard<std::mutex> lock(helper_lock());
-    HelperStream* hs = helper_for_current_device();
-    if (!hs) return launch_bin_pick<C>(pick, a, iters, st);
-    if (!helper_fork(hs, st)) return SFF_ERR_HIP;
-    const sff_status r0 = launch_bin_pick<C>(pick, f0, iters, st);
-    const sff_status r1 = launch_bin_pick<C>(pick, f1, iters, hs->stream);
-    // join even after a launch error, so the caller's stream never runs ahead
-    if (!helper_join(hs, st)) return SFF_ERR_HIP;
-    return r0 != SFF_OK ? r0 : r1;
+    return run_split(a, st, [&](const MatchArgs& f, hipStream_t fs) { return launch_bin_pick<C>(pick, f, iters, fs); });
+}
+
+// Largest descriptor map (bytes) the cooperative evaluators address (32-bit offsets).
+constexpr size_t kMaxCoopMapBytes = (size_t)kNoTarget;
+
+template <int C>
+sff_status launch_rec_pick(int pick, const MatchArgs& a, int iters, hipStream_t st) {
+    switch (pick) {
+        case 0: return launch_level<C, LaneEval<C>>(a, iters, st);
+        case 1: return launch_level<C, PatchCoop<RecMap<C>, 2, 3>>(a, iters, st);
+        case 2: return launch_level<C, PatchCoop<RecMap<C>, 4, 3>>(a, iters, st);
+        case 3: return launch_level<C, PatchCoop<RecMap<C>, 2, 3, 32>>(a, iters, st);
+        case 4: return launch_level<C, PatchCoop<RecMap<C>, 4, 3, 32>>(a, iters, st);
+        case 6:  // 16-owner waves need 4 or 8 pieces a record
+            if constexpr (C % 2 == 0)
+                return launch_level<C, PatchCoop<RecMap<C>, 4, 6, 16, true>>(a, iters, st);
+            else
+                return launch_level<C, PatchCoop<RecMap<C>, 4, 3, 32, true>>(a, iters, st);
+        default: return launch_level<C, PatchCoop<RecMap<C>, 4, 6, 32>>(a, iters, st);
+    }
+}
+
+// Record evaluators by launch size (updates per half-step).  One level's records
+// (64 bytes a pixel at C = 2) are beyond the L2s, and a half-step of the
+// 436 x 1024 learned matcher's level 0 (446,464 updates) gathers 0.9 GB: these
+// launches wait on the caches beyond them, so what pays is more gathers in flight
+// (all 4 neighbours, then all 6 samples, in one group) on more waves (32 owners),
+// still view by view with the early-out, and from 100,000 updates the two fields
+// on two streams.  ms per 12 half-steps, before (2/3 or 4/3 groups, one launch
+// sequence) and now:
+//     C = 2 learned  446,464 updates 1.29 -> 1.11, 111,616 0.44 -> 0.38
+//     C = 2          465,750 1.09 -> 0.91, 116,936 0.40 -> 0.36, 29,328 0.18 -> 0.17
+//     C = 1          465,750 0.72 -> 0.60, 116,936 0.32 -> 0.27, 29,328 0.16 -> 0.15
+//     C = 3          465,750 1.34 -> 1.26, 116,936 0.45 -> 0.41, 29,328 0.20 -> 0.20
+//     C = 4          465,750 1.39 -> 1.30, 116,936 0.47 -> 0.42, 29,328 0.21 -> 0.20
+// From a million updates a launch's tail no longer counts and two streams only
+// share the caches (1,863,000 updates: C = 2 3.76 in one sequence and 3.78 in
+// two, C = 3 4.94 and 5.03; before 3.86 and 5.07).  Below 50,000 updates the chain
+// of round trips sets the time: all three views in one round, and 16 owners per
+// wave where the records' pieces allow it (learned 97 x 161, 15,714 updates:
+// 0.148 ms with a gather per lane, 0.113 in groups of 4/6 view by view, 0.101).
+// One candidate at a time with its views in one round (the bins' choice for large
+// launches): 1.63 at 446,464 updates.
+// SFF_MATCH_EVAL = "lane" (each lane gathers its own records), "coop-narrow",
+// "coop-wide" (groups of 2/3 and 4/3, 64 owners), "coop-narrow-32",
+// "coop-wide-32" (32 owners), "coop-46-32" or "coop-xts" (the two above) forces an
+// evaluator, SFF_MATCH_SPLIT the split (all give identical results; the switches
+// exist to test and time each one); anything else: auto.
+constexpr long kRecSplitMaxUpdates = 1000000;
+template <int C>
+sff_status run_level(const MatchArgs& a, int iters, hipStream_t st) {
+    const long updates = (long)a.ndir * a.batch * a.Hk * ((a.Wk + 1) / 2);
+    int pick = updates < kHalfOwnersMaxUpdates ? 6 : 5;
+    bool split = a.ndir == 2 && updates >= kSplitMinUpdates && updates < kRecSplitMaxUpdates;
+    if (const char* e = std::getenv("SFF_MATCH_EVAL")) {
+        if (std::strcmp(e, "lane") == 0) pick = 0;
+        if (std::strcmp(e, "coop-narrow") == 0) pick = 1;
+        if (std::strcmp(e, "coop-wide") == 0) pick = 2;
+        if (std::strcmp(e, "coop-narrow-32") == 0) pick = 3;
+        if (std::strcmp(e, "coop-wide-32") == 0) pick = 4;
+        if (std::strcmp(e, "coop-46-32") == 0) pick = 5;
+        if (std::strcmp(e, "coop-xts") == 0) pick = 6;
+    }
+    if (const char* e = std::getenv("SFF_MATCH_SPLIT")) {
+        if (std::strcmp(e, "0") == 0) split = false;
+        if (std::strcmp(e, "1") == 0) split = a.ndir == 2;
+    }
+    if (a.img_bytes > kMaxCoopMapBytes) pick = 0;
+    if (!split) return launch_rec_pick<C>(pick, a, iters, st);
+    return run_split(a, st, [&](const MatchArgs& f, hipStream_t fs) { return launch_rec_pick<C>(pick, f, iters, fs); });
 }
 
 }  // namespace
