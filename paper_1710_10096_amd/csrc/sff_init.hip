@@ -36,11 +36,14 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int kQRows = 4;    // query rows per block (one 16-query MFMA tile each)
 constexpr int kWaves = 4;    // waves per block, splitting the candidate rows
+constexpr int kParts = 256 / (16 * kQRows);  // threads per query in the epipolar searches
 constexpr int kKBytes = 64;  // MFMA K: 16 C int8 values, zero padded (C <= 4)
 
 // Split planes of the coarsest-level grid of all four views:
 //   hi[z][p][64], lo[z][p][64] int8 (the split of desc), nhi, nlo (the split
-//   of -desc) and sq[z][p] = |desc|^2, z = pair * 4 + view, p = i * Wk + j.
+//   of -desc) and sq[z][p] = |desc|^2, z = pair * 4 + view, p = i * Wk + j;
+//   for C <= 2 (kPacked) hi and nhi hold both halves, a_h in bytes 0..31 and
+//   a_l in 32..63, and lo and nlo are not written.
 // sqx[z][i][wx] holds the same norms with column j at offx + j and the edge
 // values repeated over 16+ columns on either side, so the 4 candidates of a
 // lane (columns c0 + 4g .. c0 + 4g + 3, never beyond -15 .. Wk + 14) are one
@@ -55,6 +58,13 @@ struct SplitPlanes {
     uint32_t* sqx;
     int wx, offx;
 };
+
+// 16 C int8 values leave at least half of the MFMA's K free for C <= 2: both
+// halves of a descriptor then fit one operand, and the four partial products
+// take three MFMAs and one candidate load: (b_h | b_l) against (a_l | a_h),
+// (a_h | 0) and (0 | a_l).
+template <int C>
+constexpr bool kPacked = 16 * C <= kKBytes / 2;
 
 __host__ __device__ inline int sqx_offset(int F) { return 16 + (F & 3); }
 __host__ __device__ inline int sqx_width(int F, int Wk) { return (sqx_offset(F) + Wk + 16 + 3) & ~3; }
@@ -90,8 +100,11 @@ __global__ void __launch_bounds__(256) split_kernel(const int16_t* __restrict__ 
     const size_t o = (size_t)z * Hk * Wk + p;
     int8_t* const dst[4] = {P.hi, P.lo, P.nhi, P.nlo};
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
+    for (int m = 0; m < 4; m += kPacked<C> ? 2 : 1) {
         const uint32_t* src = (m & 1) ? lw[m >> 1] : hw[m >> 1];
+        if constexpr (kPacked<C>)
+#pragma unroll
+            for (int q = 0; q < kKBytes / 8; ++q) hw[m >> 1][kKBytes / 8 + q] = lw[m >> 1][q];
         uint4* out = reinterpret_cast<uint4*>(dst[m] + o * kKBytes);
 #pragma unroll
         for (int q = 0; q < kKBytes / 16; ++q)
@@ -125,18 +138,30 @@ __device__ __forceinline__ v4i load16(const int8_t* p) {
 // equal key, which have smaller indices); the lists are merged per query in
 // LDS, each leaf gets its own cross-row search, and the combination with the
 // smallest T + S + X distance wins (the earlier leaf on ties).
+//
+// Bound: per 16 x 16 tile 3 (packed) or 4 MFMAs of 16 cycles and 18 vector
+// operations, which overlap little, and the loads of a tile for every kQRows
+// tiles (2 query rows per block 500 us, 1 row 821).  Learned records, 109 x 256
+// grid, F = 100: 435 us; 554 with 4 MFMAs, four operations to a key and two
+// 64-bit lane addresses a tile.  Finding ll only for tiles whose 512 hc + |b|^2 can
+// still win: 523 (random features leave few tiles out).
 template <int C, int K>
 __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P) {
     __shared__ unsigned long long red[kWaves * 4][kQRows][16][K];
     __shared__ int res_u[kQRows][16][K], res_v[kQRows][16][K];
     __shared__ uint32_t res_t[kQRows][16][K];
     __shared__ int res_n[kQRows][16];
-    __shared__ unsigned long long red2[4][kQRows][16];
-    __shared__ unsigned long long redx[K][4][kQRows][16];
+    __shared__ unsigned long long red2[kParts][kQRows][16];
+    __shared__ unsigned long long redx[K][kParts][kQRows][16];
     const int lane = threadIdx.x & 63, w = wave_id();
     const int nq = lane & 15, g = lane >> 4;
-    const int j0 = blockIdx.x * 16, i0 = blockIdx.y * kQRows;
     const int z = blockIdx.z;  // dir_index * batch + b
+    // Blocks of the outer columns have about half the candidates.  Where the
+    // columns are a multiple of the XCDs, every CU would get the same columns in
+    // each row; they are rotated by row (109 x 256 grid, F = 100: 461 -> 435 us,
+    // 2 leaves 834 -> 726; other widths mix by themselves).
+    const int row = blockIdx.y + gridDim.y * z, rot = gridDim.x % 8 == 0 ? 7 * row + 5 * (row >> 4) : 0;
+    const int j0 = (int)((blockIdx.x + rot) % gridDim.x) * 16, i0 = blockIdx.y * kQRows;
     const int di = z / a.batch, b = z - di * a.batch;
     const int s = (a.ndir == 2) ? (di == 0 ? 1 : -1) : a.dir0;
     const int Hk = a.Hk, Wk = a.Wk, n = a.n;
@@ -151,7 +176,7 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
     const int16_t* base = a.desc + (size_t)b * 4 * mapsz;
 
     // queries (B operands, negated), one 16-column tile per query row
-    v4i qh[kQRows], ql[kQRows];
+    v4i qh[kQRows], ql[kQRows], qx[kQRows];  // packed: (a_h | 0), (0 | a_l), (a_l | a_h)
     int best[kQRows], btile[kQRows];   // K = 1: minimum key and its first tile
     int tk[kQRows][K], ti[kQRows][K];  // K > 1: sorted keys and target indices
     const int jq = min(j0 + nq, Wk - 1);
@@ -159,7 +184,13 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
     for (int t = 0; t < kQRows; ++t) {
         const size_t o = zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq;
         qh[t] = load16(P.nhi + o * kKBytes + 16 * g);
-        ql[t] = load16(P.nlo + o * kKBytes + 16 * g);
+        if constexpr (kPacked<C>) {
+            qx[t] = load16(P.nhi + o * kKBytes + 16 * (g ^ 2));
+            ql[t] = g < 2 ? v4i{0, 0, 0, 0} : qh[t];
+            if (g >= 2) qh[t] = v4i{0, 0, 0, 0};
+        } else {
+            ql[t] = load16(P.nlo + o * kKBytes + 16 * g);
+        }
         best[t] = INT_MAX;
         btile[t] = 0;
 #pragma unroll
@@ -190,12 +221,15 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
     // scores the current one.
     auto load_tile = [&](int r, int ct) {
         Tile T;
-        const size_t rowT = zT + (size_t)r * Wk;
         const int c0 = j0 - F + 16 * ct;
-        const size_t oa = rowT + clampi(c0 + nq, 0, Wk - 1);
-        T.ah = load16(P.hi + oa * kKBytes + 16 * g);
-        T.al = load16(P.lo + oa * kKBytes + 16 * g);
-        const uint4 q = *reinterpret_cast<const uint4*>(P.sqx + (zTx + (size_t)r) * P.wx + P.offx + c0 + 4 * g);
+        // wave-uniform tile address and a lane offset, a constant for tiles inside the image
+        const long t0 = ((long)zT + (long)r * Wk + c0) * kKBytes;
+        uint32_t lo = (uint32_t)(nq * kKBytes + 16 * g);
+        if (c0 < 0 || c0 + 15 >= Wk) lo = (uint32_t)((clampi(c0 + nq, 0, Wk - 1) - c0) * kKBytes + 16 * g);
+        T.ah = load16(P.hi + t0 + lo);
+        if constexpr (!kPacked<C>) T.al = load16(P.lo + t0 + lo);
+        const char* sq0 = reinterpret_cast<const char*>(P.sqx + (zTx + (size_t)r) * P.wx + P.offx + c0);
+        const uint4 q = *reinterpret_cast<const uint4*>(sq0 + (uint32_t)(16 * g));
         T.bsq[0] = (int)q.x;
         T.bsq[1] = (int)q.y;
         T.bsq[2] = (int)q.z;
@@ -241,16 +275,25 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
                     if (iq >= Hk || r < iq - F || r > iq + F) continue;
                 }
                 const v4i hh = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.ah, qh[t], zero, 0, 0, 0);
-                v4i cr = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.ah, ql[t], zero, 0, 0, 0);
-                cr = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.al, qh[t], cr, 0, 0, 0);
-                const v4i ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.al, ql[t], zero, 0, 0, 0);
+                v4i cr, ll;
+                if constexpr (kPacked<C>) {
+                    cr = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.ah, qx[t], zero, 0, 0, 0);
+                    ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.ah, ql[t], zero, 0, 0, 0);
+                } else {
+                    cr = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.ah, ql[t], zero, 0, 0, 0);
+                    cr = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.al, qh[t], cr, 0, 0, 0);
+                    ll = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.al, ql[t], zero, 0, 0, 0);
+                }
                 int k[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     // |b|^2 + 2 (-a.b), -a.b = 256 (256 hh + cr) + ll  (mod 2^32),
-                    // nested so that each step is one shift-add
-                    const uint32_t hc = ((uint32_t)hh[e] << 8) + (uint32_t)cr[e];
-                    const uint32_t ab = (hc << 8) + (uint32_t)ll[e];
+                    // nested so that each step is one shift-add (the empty asm keeps
+                    // the compiler from regrouping them into four operations)
+                    uint32_t hc = ((uint32_t)hh[e] << 8) + (uint32_t)cr[e];
+                    asm("" : "+v"(hc));
+                    uint32_t ab = (hc << 8) + (uint32_t)ll[e];
+                    asm("" : "+v"(ab));
                     const uint32_t key = (ab << 1) + (uint32_t)cur.bsq[e];
                     k[e] = (int)key;
                     if constexpr (!kInterior) k[e] = ok[e] ? k[e] : INT_MAX;
@@ -365,8 +408,8 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
     }
     __syncthreads();
 
-    // epipolar searches: 4 threads per query, candidates interleaved
-    const int q = threadIdx.x & 15, t = (threadIdx.x >> 4) & 3, part = threadIdx.x >> 6;
+    // epipolar searches: kParts threads per query, candidates interleaved
+    const int q = threadIdx.x & 15, t = (threadIdx.x >> 4) % kQRows, part = threadIdx.x / (16 * kQRows);
     const int iq = i0 + t, jqq = j0 + q;
     const bool live = iq < Hk && jqq < Wk;
     const int x = n * min(jqq, Wk - 1), y = n * min(iq, Hk - 1);
@@ -378,7 +421,7 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
     if (live) {
         const int txlo = s > 0 ? x - min(a.dm, x) : x;
         const int txhi = s > 0 ? x : x + min(a.dm, ((W - 1 - x) / n) * n);
-        for (int tx = txlo + n * part; tx <= txhi; tx += 4 * n) {
+        for (int tx = txlo + n * part; tx <= txhi; tx += kParts * n) {
             const uint32_t e = desc_ssd<C>(qd, load_desc<C>(Sm, (size_t)y * W + tx));
             const unsigned long long k = ((unsigned long long)e << 32) | (uint32_t)tx;
             kS = k < kS ? k : kS;
@@ -388,7 +431,7 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
     __syncthreads();
     unsigned long long mS = red2[0][t][q];
 #pragma unroll
-    for (int k = 1; k < 4; ++k) mS = red2[k][t][q] < mS ? red2[k][t][q] : mS;
+    for (int k = 1; k < kParts; ++k) mS = red2[k][t][q] < mS ? red2[k][t][q] : mS;
     __syncthreads();
     // cross partner of each temporal leaf on row y + v: target tx = x + u - s d1,
     // increasing tx
@@ -400,7 +443,7 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
             const int xc = x + res_u[t][q][l], yc = y + res_v[t][q][l];
             const int txlo = s > 0 ? xc - min(a.dm, xc) : xc;
             const int txhi = s > 0 ? xc : xc + min(a.dm, ((W - 1 - xc) / n) * n);
-            for (int tx = txlo + n * part; tx <= txhi; tx += 4 * n) {
+            for (int tx = txlo + n * part; tx <= txhi; tx += kParts * n) {
                 const uint32_t e = desc_ssd<C>(qd, load_desc<C>(Xm, (size_t)yc * W + tx));
                 const unsigned long long k = ((unsigned long long)e << 32) | (uint32_t)tx;
                 kX = k < kX ? k : kX;
@@ -418,7 +461,7 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
     for (int l = 0; l < nl; ++l) {
         unsigned long long mX = redx[l][0][t][q];
 #pragma unroll
-        for (int k = 1; k < 4; ++k) mX = redx[l][k][t][q] < mX ? redx[l][k][t][q] : mX;
+        for (int k = 1; k < kParts; ++k) mX = redx[l][k][t][q] < mX ? redx[l][k][t][q] : mX;
         const uint64_t joint = (uint64_t)res_t[t][q][l] + eS + (uint32_t)(mX >> 32);
         if (joint < bestJ) {
             bestJ = joint;
