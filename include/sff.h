@@ -562,6 +562,15 @@ sff_status sff_smooth_level(const sff_params* p, int32_t nimg, int32_t level, co
 sff_status sff_quantise_features(int32_t n, int32_t H, int32_t W, const uint16_t* feat, float scale,
                                  int16_t* desc, void* stream);
 
+/* The network's last layer with its output as descriptor records: the 32 -> 32
+ * convolution of sff_conv3x3_bf16_fwd without ReLU, its BF16 result normalised,
+ * scaled and rounded as by sff_quantise_features (the same records as the two
+ * calls, without the features in memory).  x and desc 16-byte aligned.
+ * Errors: SFF_ERR_INVALID_ARG. */
+sff_status sff_conv3x3_bf16_records(int32_t n, int32_t H, int32_t W, int32_t dil, const uint16_t* x,
+                                    const uint16_t* w, const float* bias, float scale, int16_t* desc,
+                                    void* stream);
+
 /* Triplet loss on normalised 32-channel BF16 features feat [npx][32]: for
  * triple t = (a, p, n) of pixel indices (triplets [ntrip][3] int32, device),
  * loss[t] = max(0, margin + |a^ - p^|^2 - |a^ - n^|^2); weight * dloss/dfeat

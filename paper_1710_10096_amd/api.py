@@ -529,6 +529,22 @@ def sff_conv3x3_bf16_fwd(x: torch.Tensor, w: torch.Tensor, bias: torch.Tensor | 
     return y
 
 
+def sff_conv3x3_bf16_records(x: torch.Tensor, w: torch.Tensor, bias: torch.Tensor | None, dil: int = 1,
+                             scale: float = 4096.0, desc=None, stream=None):
+    """The 32 -> 32 layer without ReLU and sff_quantise_features of its output in
+    one pass: x bf16 [n][H][W][32] -> int16 records [n][H][W][2][16]."""
+    n, H, W, cin = x.shape
+    if cin != 32 or w.shape[0] != 32:
+        raise ValueError("x and the layer's output must have 32 channels")
+    if desc is None:
+        desc = torch.empty((n, H, W, 2, 16), dtype=torch.int16, device=x.device)
+    _check(lib().sff_conv3x3_bf16_records(n, H, W, dil, _ptr(x, torch.bfloat16, "x"), _ptr(w, torch.bfloat16, "w"),
+                                          _ptr(bias, torch.float32, "bias"), float(scale),
+                                          _ptr(desc, torch.int16, "desc"), _stream(stream)),
+           "sff_conv3x3_bf16_records")
+    return desc
+
+
 def sff_featnet_fwd_bf16(x: torch.Tensor, ws, bs, dil: int = 1, y=None, stream=None):
     """The four-layer network in one launch: x bf16 [n][H][W][3], ws four bf16
     weight tensors ([32][3][3][3], then [32][3][3][32]), bs four f32 biases (or

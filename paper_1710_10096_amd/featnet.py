@@ -58,6 +58,16 @@ class FeatNet:
             acts.append(h)
         return (h, acts) if keep else h
 
+    def records(self, x: torch.Tensor, dil: int, scale: float, desc: torch.Tensor, wb=None):
+        """The quantised features of `forward` (sff_quantise_features) into desc
+        int16 [n][H][W][2][16]; the last layer writes them without the features in
+        memory."""
+        wb = wb if wb is not None else self.weights_bf16()
+        h = x
+        for l in range(3):
+            h = api.sff_conv3x3_bf16_fwd(h, wb[l], self.params[2 * l + 1], dil, relu=True)
+        return api.sff_conv3x3_bf16_records(h, wb[3], self.params[7], dil, scale, desc)
+
     def backward(self, acts, dout: torch.Tensor, dil: int = 1, wb=None):
         """Gradients (dw, db) of every layer given dL/d(output) in bf16."""
         wb = wb if wb is not None else self.weights_bf16()
@@ -180,8 +190,11 @@ class LearnedMatcher:
         top = p.levels - 1
         for k in range(top, -1, -1):
             sm = api.sff_smooth_level(p, flat, k, self.smoothed, self.ws_img)
-            feat = self.net.forward(images_bf16(sm), 1 << k, wb=wb)
-            api.sff_quantise_features(feat, self.SCALE, desc)
+            if getattr(self.net.forward, "__func__", None) is FeatNet.forward:
+                self.net.records(images_bf16(sm), 1 << k, self.SCALE, desc, wb=wb)
+            else:  # a network of the caller's own
+                feat = self.net.forward(images_bf16(sm), 1 << k, wb=wb)
+                api.sff_quantise_features(feat, self.SCALE, desc)
             if k == top:
                 api.sff_init_nn(m.p, m.desc, api.DIR_BOTH, m.hyp[k], m.cost[k], m.ws)
                 api.sff_match_level(m.p, m.desc, api.DIR_BOTH, k, seeds, m.hyp[k], m.cost[k])
