@@ -677,13 +677,6 @@ __global__ void __launch_bounds__(64) half_step_kernel(MatchArgs a, int it, int 
     }
 }
 
-// Below this many pixel updates per launch (about a third of a wave per SIMD)
-// each wave's chain of dependent gathers sets the time and the per-lane
-// evaluator has the shorter chain.  Above it the cooperative one wins even
-// with the chip far from full: level 2 of the KITTI-size pair (29,328 updates)
-// takes 0.232 ms per step with it and 0.261 ms per lane.
-constexpr long kCoopMinUpdates = 20000;
-
 template <int C, class E>
 sff_status launch_level(const MatchArgs& a, int iters, hipStream_t st) {
     const int nz = a.ndir * a.batch;
@@ -706,8 +699,9 @@ sff_status launch_level(const MatchArgs& a, int iters, hipStream_t st) {
     return launch_status();
 }
 
-// Below this many pixel updates per launch a cooperative wave has 32 or 16
-// owners: more waves, fewer gather registers.
+// Below this many pixel updates per launch (about a wave per SIMD) the chain of
+// dependent round trips sets the time: all three views in one round and 16 owners
+// per wave (32 where a patch has fewer than four pieces).
 constexpr long kHalfOwnersMaxUpdates = 50000;
 
 // From this many updates per half-step the bin matcher scores one candidate
@@ -733,13 +727,18 @@ constexpr long kBinXtsMinUpdates = 262144;
 //    (unpacking and squared distances of the gathered pieces), and the
 //    early-out rejects only ~15 % of candidates at the cross view, so a round
 //    per view saves little.
+// The shortest chain wins down to the smallest calls, where each lane gathering
+// its own patches (fewest instructions) had been taken below 20,000 updates; us
+// per matching stage: 96 x 160, C = 1 (15,360 updates; 32 owners, three views a
+// round) 170 -> 145, 16 x 16 108 -> 81, 97 x 161, C = 3, two levels 364 -> 256,
+// C = 4 252 -> 214, 30 x 40, C = 3 188 -> 126.  C = 1 keeps it to twice the
+// updates (240 x 320, two levels, 76,800: 250 against 277 with 43-32).
 // Other tile orders were slower (row-major 1.10 ms at level 0, no XCD
-// grouping 1.37 ms, with unpacked patches).  Below 20,000 updates each lane
-// gathers its own patches.  SFF_MATCH_EVAL = "lane", "coop" (2/3, 64 owners,
-// early-out), "coop-32", "coop-43-32", "coop-46-32" (32 owners, early-out),
-// "coop-xts" (1/1, 64 owners, three views a round) or "coop-46-16-xts" forces
-// one (all give identical results; 16-owner shapes need 4 pieces a patch,
-// C >= 2, and fall back to "coop-46-32" otherwise); anything else: auto.
+// grouping 1.37 ms, with unpacked patches).  SFF_MATCH_EVAL = "lane" (each lane
+// gathers its own patches), "coop" (2/3, 64 owners, early-out), "coop-32",
+// "coop-43-32", "coop-46-32" (32 owners, early-out), "coop-xts" (1/1, 64 owners,
+// three views a round) or "coop-46-16-xts" (32 owners for C = 1) forces one (all
+// give identical results); anything else: auto.
 template <int C>
 sff_status launch_bin_pick(int pick, const MatchArgs& a, int iters, hipStream_t st) {
     switch (pick) {
@@ -749,8 +748,10 @@ sff_status launch_bin_pick(int pick, const MatchArgs& a, int iters, hipStream_t 
         case 3: return launch_level<C, PatchCoop<BinMap<C>, 4, 3, 32>>(a, iters, st);
         case 5: return launch_level<C, PatchCoop<BinMap<C>, 1, 1, 64, true>>(a, iters, st);
         case 6:
-            if constexpr (16 * bin_pieces(C) % 64 == 0) return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 16, true>>(a, iters, st);
-            break;
+            if constexpr (16 * bin_pieces(C) % 64 == 0)
+                return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 16, true>>(a, iters, st);
+            else
+                return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 32, true>>(a, iters, st);
         default: break;
     }
     return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 32>>(a, iters, st);
@@ -796,10 +797,7 @@ sff_status run_split(const MatchArgs& a, hipStream_t st, F launch) {
 template <int C>
 sff_status run_bin_level(const MatchArgs& a, int iters, hipStream_t st) {
     const long updates = (long)a.ndir * a.batch * a.Hk * ((a.Wk + 1) / 2);
-    int pick = updates < kCoopMinUpdates         ? 0
-               : updates < kHalfOwnersMaxUpdates ? 6
-               : updates < kBinXtsMinUpdates     ? 3
-                                                 : 5;
+    int pick = updates < (C == 1 ? 2 : 1) * kHalfOwnersMaxUpdates ? 6 : updates < kBinXtsMinUpdates ? 3 : 5;
     bool split = a.ndir == 2 && updates >= kSplitMinUpdates;
     if (const char* e = std::getenv("SFF_MATCH_EVAL")) {
         if (std::strcmp(e, "lane") == 0) pick = 0;
