@@ -263,7 +263,7 @@ sff_status sff_match_level(const sff_params* p, int32_t batch, int32_t dir, int3
  * descriptors).  bins: level-k planes of the 4 views of each pair,
  * [batch][4] images of sff_bin_bytes(p, level) bytes (sff_wht_features),
  * 16-byte aligned.  Other arguments as for sff_match_level.  Wave-cooperative
- * gathers (below 50000 pixel updates per launch, 100000 for C = 1: 16 pixels per
+ * gathers (below 50000 pixel updates per launch, 80000 for C = 1: 16 pixels per
  * wave, 32 for C = 1, groups of 4 neighbours and 6 samples, three views a round; below
  * 262144: 32 pixels per wave, groups of 4 neighbours and 3 samples, view by
  * view; above: 64 pixels per wave, one candidate at a time, three views a

@@ -702,7 +702,7 @@ sff_status launch_level(const MatchArgs& a, int iters, hipStream_t st) {
 // Below this many pixel updates per launch (about a wave per SIMD) the chain of
 // dependent round trips sets the time: all three views in one round and 16 owners
 // per wave (32 where a patch has fewer than four pieces).
-constexpr long kHalfOwnersMaxUpdates = 50000;
+constexpr long kHalfOwnersMaxUpdates = 50000, kBinC1MaxUpdates = 80000;
 
 // From this many updates per half-step the bin matcher scores one candidate
 // at a time with all three views per round (below: 4 neighbours and 3
@@ -731,8 +731,9 @@ constexpr long kBinXtsMinUpdates = 262144;
 // its own patches (fewest instructions) had been taken below 20,000 updates; us
 // per matching stage: 96 x 160, C = 1 (15,360 updates; 32 owners, three views a
 // round) 170 -> 145, 16 x 16 108 -> 81, 97 x 161, C = 3, two levels 364 -> 256,
-// C = 4 252 -> 214, 30 x 40, C = 3 188 -> 126.  C = 1 keeps it to twice the
-// updates (240 x 320, two levels, 76,800: 250 against 277 with 43-32).
+// C = 4 252 -> 214, 30 x 40, C = 3 188 -> 126.  C = 1 keeps it to 80,000
+// updates (240 x 320, two levels, 76,800: 250 against 277 with 43-32; six 96 x 160
+// pairs, 92,160: 309 against 305).
 // Other tile orders were slower (row-major 1.10 ms at level 0, no XCD
 // grouping 1.37 ms, with unpacked patches).  SFF_MATCH_EVAL = "lane" (each lane
 // gathers its own patches), "coop" (2/3, 64 owners, early-out), "coop-32",
@@ -797,7 +798,7 @@ sff_status run_split(const MatchArgs& a, hipStream_t st, F launch) {
 template <int C>
 sff_status run_bin_level(const MatchArgs& a, int iters, hipStream_t st) {
     const long updates = (long)a.ndir * a.batch * a.Hk * ((a.Wk + 1) / 2);
-    int pick = updates < (C == 1 ? 2 : 1) * kHalfOwnersMaxUpdates ? 6 : updates < kBinXtsMinUpdates ? 3 : 5;
+    int pick = updates < (C == 1 ? kBinC1MaxUpdates : kHalfOwnersMaxUpdates) ? 6 : updates < kBinXtsMinUpdates ? 3 : 5;
     bool split = a.ndir == 2 && updates >= kSplitMinUpdates;
     if (const char* e = std::getenv("SFF_MATCH_EVAL")) {
         if (std::strcmp(e, "lane") == 0) pick = 0;
