@@ -7,10 +7,11 @@
 // every union hooks the larger root under the smaller one with a
 // compare-and-swap, so a component's final root is its smallest pixel index
 // whatever the order of the unions.  The edges inside a 16 x 64 tile are
-// united first in LDS, one block per tile; only the edges that cross tile
-// borders are united in global memory.  Then each component's size is counted
-// and it is flagged when an inconsistent 4-neighbour of one of its pixels is
-// within tau of that pixel's vector.  A flagged component with fewer than s_c
+// united first in LDS, one block per tile (the runs of a row by a ballot, then the
+// vertical edges that join two runs for the first time); only the edges that
+// cross tile borders are united in global memory.  Then each component's size is
+// counted and it is flagged when an inconsistent 4-neighbour of one of its pixels
+// is within tau of that pixel's vector.  A flagged component with fewer than s_c
 // pixels is dropped.  The result is independent of thread order.
 #include "sff_internal.hpp"
 
@@ -50,13 +51,14 @@ __device__ int find_root(int32_t* parent, int x) {
     return x;
 }
 
-// Read-only walk, for use once the unions are complete (the forest is static
-// then apart from pixels being pointed straight at their roots).
+// Read-only walk, for use once the unions are complete: the forest is static then
+// apart from pixels being pointed straight at their roots, so a CU's cached copy
+// of a parent is an ancestor as well.
 __device__ int find_root_ro(const int32_t* parent, int x) {
-    int p = ld(parent + x);
+    int p = __hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     while (p != x) {
         x = p;
-        p = ld(parent + x);
+        p = __hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     return x;
 }
@@ -77,9 +79,7 @@ __device__ void unite(int32_t* parent, int a, int b, int n) {
     }
 }
 
-__device__ __forceinline__ bool similar(const int16_t* h, int p, int q, int tau) {
-    const uint2 a = reinterpret_cast<const uint2*>(h)[p];
-    const uint2 b = reinterpret_cast<const uint2*>(h)[q];
+__device__ __forceinline__ bool similar(uint2 a, uint2 b, int tau) {
     const int d0 = (int)(int16_t)(a.x & 0xFFFFu) - (int)(int16_t)(b.x & 0xFFFFu);
     const int d1 = (int)(int16_t)(a.x >> 16) - (int)(int16_t)(b.x >> 16);
     const int d2 = (int)(int16_t)(a.y & 0xFFFFu) - (int)(int16_t)(b.y & 0xFFFFu);
@@ -87,14 +87,8 @@ __device__ __forceinline__ bool similar(const int16_t* h, int p, int q, int tau)
     return abs(d0) <= tau && abs(d1) <= tau && abs(d2) <= tau && abs(d3) <= tau;
 }
 
-// blockIdx.y = batch element; one thread per pixel.
-__global__ void __launch_bounds__(256) rf_init_kernel(RegionArgs a) {
-    const int n = a.H * a.W;
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= n) return;
-    const size_t o = (size_t)blockIdx.y * n + p;
-    a.size[o] = 0;
-    a.flag[o] = 0;
+__device__ __forceinline__ bool similar(const int16_t* h, int p, int q, int tau) {
+    return similar(reinterpret_cast<const uint2*>(h)[p], reinterpret_cast<const uint2*>(h)[q], tau);
 }
 
 constexpr int kTH = 16, kTW = 64;  // tile of the local pass
@@ -122,35 +116,67 @@ __device__ void lunite(int* lp, int a, int b) {
     }
 }
 
-// One block per 16 x 64 tile (blockIdx.x = tile, blockIdx.y = batch element):
-// unions of the edges inside the tile in LDS; every pixel's global parent
-// becomes the global index of its tile-local root (tile rows and image rows
-// are both row-major, so the smallest local index is the smallest global one).
+// One block per 16 x 64 tile (blockIdx.x = tile, blockIdx.y = batch element), a
+// wave per row, four rows each: every pixel's global parent becomes the global
+// index of its tile-local root (tile rows and image rows are both row-major, so
+// the smallest local index is the smallest global one); sizes and flags are
+// cleared.  A lane starts at the first pixel of its run of joined pixels of the
+// row.  A vertical edge is left out where the pixels to the left have one too and
+// both are joined to this one's: it adds nothing.
+// Bound: the latency of the few chained unions; 375 x 1242: 12 us, with a union
+// per edge in both directions and a pass of its own for the clearing 28 + 5 us.
 __global__ void __launch_bounds__(256) rf_local_kernel(RegionArgs a) {
+    static_assert(kTW == 64, "a wave per row");
     __shared__ int lp[kTH * kTW];
-    __shared__ uint8_t lv[kTH * kTW];
+    __shared__ uint2 lh[kTH][kTW];
+    __shared__ unsigned long long lv[kTH], ll[kTH];  // valid pixels, pixels joined to their left neighbour
     const int tiles_x = (a.W + kTW - 1) / kTW;
     const int ty0 = (blockIdx.x / tiles_x) * kTH, tx0 = (blockIdx.x % tiles_x) * kTW;
     const size_t base = (size_t)blockIdx.y * a.H * a.W;
-    const int16_t* h = a.hyp + base * 4;
-    for (int i = threadIdx.x; i < kTH * kTW; i += 256) {
-        const int y = ty0 + i / kTW, x = tx0 + i % kTW;
-        lp[i] = i;
-        lv[i] = (y < a.H && x < a.W) ? a.valid[base + (size_t)y * a.W + x] : 0;
+    const uint2* h = reinterpret_cast<const uint2*>(a.hyp) + base;
+    const int lane = threadIdx.x & 63, w = wave_id(), x = tx0 + lane;
+    constexpr int kRows = kTH / 4;
+    uint2 own[kRows];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int r = w + 4 * k, y = ty0 + r;
+        const bool in = y < a.H && x < a.W;
+        const size_t o = base + (size_t)y * a.W + x;
+        const bool v = in && a.valid[o];
+        own[k] = in ? h[(size_t)y * a.W + x] : make_uint2(0u, 0u);
+        if (in) {
+            a.size[o] = 0;
+            a.flag[o] = 0;
+        }
+        const uint2 left = make_uint2(__shfl_up(own[k].x, 1), __shfl_up(own[k].y, 1));
+        const unsigned long long vm = __ballot(v);
+        const bool join = v && lane > 0 && ((vm >> (lane - 1)) & 1) && similar(own[k], left, a.tau);
+        const unsigned long long jm = __ballot(join);
+        lp[r * kTW + lane] = r * kTW + 63 - __clzll(~jm & (~0ull >> (63 - lane)));  // bit 0 of ~jm is set
+        lh[r][lane] = own[k];
+        if (lane == 0) {
+            lv[r] = vm;
+            ll[r] = jm;
+        }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kTH * kTW; i += 256) {
-        if (!lv[i]) continue;
-        const int r = i / kTW, c = i % kTW;
-        const int p = (ty0 + r) * a.W + tx0 + c;
-        if (c + 1 < kTW && lv[i + 1] && similar(h, p, p + 1, a.tau)) lunite(lp, i, i + 1);
-        if (r + 1 < kTH && lv[i + kTW] && similar(h, p, p + a.W, a.tau)) lunite(lp, i, i + kTW);
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int r = w + 4 * k;
+        if (r + 1 < kTH) {
+            const unsigned long long both = lv[r] & lv[r + 1];
+            const bool edge = ((both >> lane) & 1) && similar(own[k], lh[r + 1][lane], a.tau);
+            const unsigned long long em = __ballot(edge);
+            const bool known = ((em << 1) & ll[r] & ll[r + 1]) >> lane & 1;
+            if (edge && !known) lunite(lp, r * kTW + lane, (r + 1) * kTW + lane);
+        }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kTH * kTW; i += 256) {
-        const int y = ty0 + i / kTW, x = tx0 + i % kTW;
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int y = ty0 + w + 4 * k;
         if (y >= a.H || x >= a.W) continue;
-        const int r = lfind(lp, i);
+        const int r = lfind(lp, (w + 4 * k) * kTW + lane);
         a.parent[base + (size_t)y * a.W + x] = (ty0 + r / kTW) * a.W + tx0 + r % kTW;
     }
 }
@@ -170,8 +196,18 @@ __global__ void __launch_bounds__(256) rf_union_kernel(RegionArgs a) {
     if (!v[p]) return;
     const int16_t* h = a.hyp + base * 4;
     int32_t* parent = a.parent + base;
-    if (right && v[p + 1] && similar(h, p, p + 1, a.tau)) unite(parent, p, p + 1, n);
-    if (down && v[p + a.W] && similar(h, p, p + a.W, a.tau)) unite(parent, p, p + a.W, n);
+    // Joins p and q across the border, unless the pixels back pixels before them
+    // (of the same two tiles) join too and are joined to p and q (375 x 1242:
+    // 18 -> 14 us).
+    auto cross = [&](int q, int back, bool has) {
+        if (!v[q] || !similar(h, p, q, a.tau)) return;
+        if (has && v[p - back] && v[q - back] && similar(h, p - back, q - back, a.tau) &&
+            similar(h, p - back, p, a.tau) && similar(h, q - back, q, a.tau))
+            return;
+        unite(parent, p, q, n);
+    };
+    if (right) cross(p + 1, a.W, y % kTH != 0);
+    if (down) cross(p + a.W, 1, x % kTW != 0);
 }
 
 // Adds `val` of every active lane into arr[key], one atomic per distinct key
@@ -194,46 +230,44 @@ __device__ void wave_add_by_key(int32_t* arr, int key, bool active, int val) {
     }
 }
 
-// After all unions: every consistent pixel's parent becomes its root, and the
-// root's pixel count is accumulated.
-__global__ void __launch_bounds__(256) rf_count_kernel(RegionArgs a) {
+// After all unions: every consistent pixel's parent becomes its root, the root's
+// pixel count is accumulated, and inconsistent pixels flag every neighbouring
+// region they could join (walking to its root themselves: a parent met on the
+// way is an ancestor, whether or not it has been replaced by the root).  Flags
+// only go from 0 to 1, so a plain store does.  375 x 1242: 24 us; counts and flags
+// each in a pass of their own 12 + 27, stores without the look at the cached flag
+// (one line takes them all) and walks past the caches 76.
+__global__ void __launch_bounds__(256) rf_count_flag_kernel(RegionArgs a) {
     const int n = a.H * a.W;
     const int p = blockIdx.x * 256 + threadIdx.x;
-    const size_t base = (size_t)blockIdx.y * n;
-    const bool act = p < n && a.valid[base + p];
-    int r = 0;
-    if (act) {
-        int32_t* parent = a.parent + base;
-        r = find_root_ro(parent, p);
-        st(parent + p, r);
-    }
-    wave_add_by_key(a.size + base, r, act, 1);
-}
-
-// Inconsistent pixels flag every neighbouring region they could join.  Runs
-// after rf_count_kernel, so a consistent pixel's parent is its root.  Flags
-// only go from 0 to 1: a flag already seen set needs no atomic.
-__global__ void __launch_bounds__(256) rf_flag_kernel(RegionArgs a) {
-    const int n = a.H * a.W;
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= n) return;
     const size_t base = (size_t)blockIdx.y * n;
     const uint8_t* v = a.valid + base;
-    if (v[p]) return;
-    const int16_t* h = a.hyp + base * 4;
-    const int32_t* parent = a.parent + base;
-    int32_t* flag = a.flag + base;
-    const int x = p % a.W, y = p / a.W;
-    const int nb[4] = {x > 0 ? p - 1 : -1, x + 1 < a.W ? p + 1 : -1, y > 0 ? p - a.W : -1,
-                       y + 1 < a.H ? p + a.W : -1};
+    int32_t* parent = a.parent + base;
+    const bool act = p < n && v[p];
+    int r = 0;
+    if (act) {
+        r = find_root_ro(parent, p);
+        st(parent + p, r);
+    } else if (p < n) {
+        const int16_t* h = a.hyp + base * 4;
+        int32_t* flag = a.flag + base;
+        const int x = p % a.W, y = p / a.W;
+        const int nb[4] = {x > 0 ? p - 1 : -1, x + 1 < a.W ? p + 1 : -1, y > 0 ? p - a.W : -1,
+                           y + 1 < a.H ? p + a.W : -1};
+        int last = -1;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int q = nb[k];
-        if (q >= 0 && v[q] && similar(h, p, q, a.tau)) {
-            const int r = parent[q];
-            if (flag[r] == 0) atomicOr(flag + r, 1);  // a stale 0 costs one extra atomic
+        for (int k = 0; k < 4; ++k) {
+            const int q = nb[k];
+            if (q >= 0 && v[q] && similar(h, p, q, a.tau)) {
+                const int f = find_root_ro(parent, q);
+                // a stale 0 costs one extra store
+                if (f != last && __hip_atomic_load(flag + f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
+                    st(flag + f, 1);
+                last = f;
+            }
         }
     }
+    wave_add_by_key(a.size + base, r, act, 1);
 }
 
 __global__ void __launch_bounds__(256) rf_keep_kernel(RegionArgs a) {
@@ -316,11 +350,9 @@ extern "C" sff_status sff_region_filter(const sff_params* p, int32_t batch, int3
     const dim3 grid((p->H * p->W + 255) / 256, batch);
     hipStream_t st = as_stream(stream);
     const int tiles = ((p->H + kTH - 1) / kTH) * ((p->W + kTW - 1) / kTW);
-    hipLaunchKernelGGL(rf_init_kernel, grid, dim3(256), 0, st, a);
     hipLaunchKernelGGL(rf_local_kernel, dim3(tiles, batch), dim3(256), 0, st, a);
     hipLaunchKernelGGL(rf_union_kernel, grid, dim3(256), 0, st, a);
-    hipLaunchKernelGGL(rf_count_kernel, grid, dim3(256), 0, st, a);
-    hipLaunchKernelGGL(rf_flag_kernel, grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL(rf_count_flag_kernel, grid, dim3(256), 0, st, a);
     hipLaunchKernelGGL(rf_keep_kernel, grid, dim3(256), 0, st, a);
     return launch_status();
 }
