@@ -492,7 +492,7 @@ __device__ __forceinline__ void chol_inverse(const double (*Gs)[kSub], double (*
             double s = Gs[i][j];
 #pragma unroll
             for (int k = 0; k < i; ++k) s -= R[k][i] * R[k][j];
-            R[i][j] = s / R[i][i];
+            R[i][j] = s * Ri[i][i];
         }
         double s = Gs[j][j];
 #pragma unroll
@@ -504,18 +504,18 @@ __device__ __forceinline__ void chol_inverse(const double (*Gs)[kSub], double (*
             for (int i = 0; i < j; ++i) R[i][j] = 0.0;
             R[j][j] = 1.0;
         }
+        Ri[j][j] = 1.0 / R[j][j];
     }
 #pragma unroll
     for (int j = 0; j < kSub; ++j) {
 #pragma unroll
-        for (int i = 0; i < kSub; ++i) Ri[i][j] = 0.0;
-        Ri[j][j] = 1.0 / R[j][j];
+        for (int i = j + 1; i < kSub; ++i) Ri[i][j] = 0.0;
 #pragma unroll
         for (int i = j - 1; i >= 0; --i) {
             double s = 0.0;
 #pragma unroll
             for (int k = i + 1; k <= j; ++k) s += R[i][k] * Ri[k][j];
-            Ri[i][j] = -s / R[i][i];
+            Ri[i][j] = -s * Ri[i][i];
         }
     }
 #pragma unroll
@@ -524,90 +524,63 @@ __device__ __forceinline__ void chol_inverse(const double (*Gs)[kSub], double (*
         for (int j = 0; j < kSub; ++j) Rinv_out[i][j] = Ri[i][j];
 }
 
-// Eigenpairs of the symmetric part of Ts by cyclic Jacobi rotations, sorted by
+// Eigenpairs of the symmetric part of Ts by Jacobi rotations, sorted by
 // eigenvalue, largest first: values to th_out, vectors to the columns of S_out.
+// Called by one wave: lane l holds element (l / 8, l % 8) of the matrix and of the
+// vectors, and a sweep is seven rounds of four disjoint rotations (the pairs of a
+// round-robin of eight), so the divisions and roots of four angles run side by
+// side.  Bound: that serial chain; the 28 rotations of a sweep one after the other
+// in one lane took 12 us more.
 __device__ __forceinline__ void ritz_small(const double (*Ts)[kSub], double* th_out, double (*S_out)[kSub]) {
-    double A[kSub][kSub], V[kSub][kSub];
-#pragma unroll
-    for (int i = 0; i < kSub; ++i)
-#pragma unroll
-        for (int j = 0; j < kSub; ++j) {
-            A[i][j] = 0.5 * (Ts[i][j] + Ts[j][i]);
-            V[i][j] = i == j ? 1.0 : 0.0;
-        }
+    static_assert(kSub == 8, "a lane per element");
+    const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+    double a = 0.5 * (Ts[i][j] + Ts[j][i]), v = i == j ? 1.0 : 0.0;
     for (int sweep = 0; sweep < 40; ++sweep) {
-        double off = 0.0, tot = 0.0;
+        double tot = a * a, off = i == j ? 0.0 : tot;
 #pragma unroll
-        for (int i = 0; i < kSub; ++i)
-#pragma unroll
-            for (int j = 0; j < kSub; ++j) {
-                tot += A[i][j] * A[i][j];
-                if (i != j) off += A[i][j] * A[i][j];
-            }
-        if (off <= 1e-32 * tot) break;
-#pragma unroll
-        for (int p = 0; p < kSub - 1; ++p)
-#pragma unroll
-            for (int q = p + 1; q < kSub; ++q) {
-                const double apq = A[p][q];
-                if (apq != 0.0) {
-                    const double th = (A[q][q] - A[p][p]) / (2.0 * apq);
-                    const double tt = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                    const double c = 1.0 / sqrt(tt * tt + 1.0), s = tt * c;
-#pragma unroll
-                    for (int k = 0; k < kSub; ++k) {
-                        const double akp = A[k][p], akq = A[k][q];
-                        A[k][p] = c * akp - s * akq;
-                        A[k][q] = s * akp + c * akq;
-                    }
-#pragma unroll
-                    for (int k = 0; k < kSub; ++k) {
-                        const double apk = A[p][k], aqk = A[q][k];
-                        A[p][k] = c * apk - s * aqk;
-                        A[q][k] = s * apk + c * aqk;
-                    }
-#pragma unroll
-                    for (int k = 0; k < kSub; ++k) {
-                        const double vkp = V[k][p], vkq = V[k][q];
-                        V[k][p] = c * vkp - s * vkq;
-                        V[k][q] = s * vkp + c * vkq;
-                    }
-                }
-            }
-    }
-    double d[kSub];
-#pragma unroll
-    for (int i = 0; i < kSub; ++i) d[i] = A[i][i];
-    // selection order, largest first (columns swapped along)
-#pragma unroll
-    for (int i = 0; i < kSub; ++i)
-#pragma unroll
-        for (int j = i + 1; j < kSub; ++j) {
-            const bool sw = d[j] > d[i];
-            const double di = d[i], dj = d[j];
-            d[i] = sw ? dj : di;
-            d[j] = sw ? di : dj;
-#pragma unroll
-            for (int k = 0; k < kSub; ++k) {
-                const double vi = V[k][i], vj = V[k][j];
-                V[k][i] = sw ? vj : vi;
-                V[k][j] = sw ? vi : vj;
-            }
+        for (int m = 1; m < 64; m <<= 1) {
+            tot += __shfl_xor(tot, m);
+            off += __shfl_xor(off, m);
         }
-#pragma unroll
-    for (int i = 0; i < kSub; ++i) {
-        th_out[i] = d[i];
-#pragma unroll
-        for (int j = 0; j < kSub; ++j) S_out[i][j] = V[i][j];
+        if (off <= 1e-32 * tot) break;
+#pragma unroll 1
+        for (int r = 0; r < 7; ++r) {
+            // players x and y of round r meet: x + y = 2 r (mod 7), r meets 7
+            auto partner = [&](int x) { return x == 7 ? r : x == r ? 7 : (2 * r + 7 - x) % 7; };
+            const int pi = partner(i), pj = partner(j), p = min(j, pj), q = max(j, pj);
+            const double app = __shfl(a, 9 * p), aqq = __shfl(a, 9 * q), apq = __shfl(a, 8 * p + q);
+            double c = 1.0, sn = 0.0;
+            if (apq != 0.0) {
+                const double th = (aqq - app) / (2.0 * apq);
+                const double tt = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
+                c = 1.0 / sqrt(tt * tt + 1.0);
+                sn = j == p ? -(tt * c) : tt * c;
+            }
+            const double ci = __shfl(c, i), si = __shfl(sn, i);  // of the row's pair
+            const double t = c * a + sn * __shfl(a, 8 * i + pj);
+            a = ci * t + si * __shfl(t, 8 * pi + j);
+            if (j == pi) a = 0.0;
+            v = c * v + sn * __shfl(v, 8 * i + pj);
+        }
     }
+    const double d = __shfl(a, 9 * j);
+    int rank = 0;
+#pragma unroll
+    for (int k = 0; k < kSub; ++k) {
+        const double dk = __shfl(a, 9 * k);
+        rank += dk > d || (dk == d && k < j);
+    }
+    if (i == 0) th_out[rank] = d;
+    S_out[i][rank] = v;
 }
 
-// Sum over the block (256 threads) of one double per thread.
+// Sum over the block (N threads) of one double per thread.
+template <int N>
 __device__ double block_sum(double v, double* red) {
     const int t = threadIdx.x;
     red[t] = v;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
+    for (int s = N / 2; s > 0; s >>= 1) {
         if (t < s) red[t] += red[t + s];
         __syncthreads();
     }
@@ -632,10 +605,12 @@ __device__ double block_sum(double v, double* red) {
 // the projection.
 constexpr int kSquare = 6;  // A^64: KITTI-size pair 1.68 ms of features vs 1.78 with A^32 (A^128: no gain)
 
-// One 16 x 16 tile of C = B B / trace(B B) per block, for a symmetric B:
-// trace(B B) = |B|_F^2, summed by every block in the same order (so all tiles
-// share one scale), and C[r][c] = sum_k B[k][r] B[k][c] with the two factors
-// of a term commuting in fma, so C is exactly symmetric again.
+// One 16 x 16 tile of C = B B / trace(B)^2 per block, for a symmetric positive
+// semidefinite B (trace(C) is in [1 / 128, 1]): every block sums the diagonal in
+// the same order, so all tiles share one scale, and C[r][c] = sum_k B[k][r] B[k][c]
+// with the two factors of a term commuting in fma, so C is exactly symmetric again.
+// Bound: latency (a load, a block sum and a chain of 128 fma): 5.9 us; 9.9 with
+// trace(B B), which every block took from all of B.
 __global__ void __launch_bounds__(256) square_kernel(const double* __restrict__ B_all, size_t b_stride,
                                                      double* __restrict__ C_all, size_t c_stride) {
     __shared__ double colr[kDesc][16], colc[kDesc][16];
@@ -643,13 +618,7 @@ __global__ void __launch_bounds__(256) square_kernel(const double* __restrict__ 
     const int t = threadIdx.x, ti = blockIdx.x >> 3, tj = blockIdx.x & 7;
     const double* B = B_all + (size_t)blockIdx.y * b_stride;
     double* C = C_all + (size_t)blockIdx.y * c_stride;
-    // four independent partial sums so the 64 loads of a thread are in flight together
-    double f4[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int e = t; e < kDesc * kDesc; e += 1024)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) f4[u] = fma(B[e + 256 * u], B[e + 256 * u], f4[u]);
-    const double f = block_sum((f4[0] + f4[1]) + (f4[2] + f4[3]), red);
+    const double tr = block_sum<256>(t < kDesc ? B[(size_t)t * (kDesc + 1)] : 0.0, red);
 #pragma unroll
     for (int e = t; e < kDesc * 16; e += 256) {
         const int k = e >> 4, c = e & 15;
@@ -660,28 +629,35 @@ __global__ void __launch_bounds__(256) square_kernel(const double* __restrict__ 
     const int r = t >> 4, c = t & 15;
     double acc = 0.0;
     for (int k = 0; k < kDesc; ++k) acc = fma(colr[k][r], colc[k][c], acc);
-    const double sc = f > 0.0 ? 1.0 / f : 1.0;
-    C[(size_t)(16 * ti + r) * kDesc + 16 * tj + c] = acc * sc;
+    const double sc = tr > 0.0 ? 1.0 / tr : 1.0;
+    C[(size_t)(16 * ti + r) * kDesc + 16 * tj + c] = acc * sc * sc;
 }
 
-__global__ void __launch_bounds__(256) eig_kernel(const double* __restrict__ cov_all,
+// Bound: latency: four products (each 128 KB from beyond the L2s by one CU), seven
+// small factorisations in one thread, one small eigenproblem.  KITTI-size pair: 62 us;
+// 118 with 256 threads that each summed a row with 16 loads in flight (16 us a
+// product).
+constexpr int kEigParts = 4, kEigThreads = kEigParts * kDesc;
+__global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* __restrict__ cov_all,
                                                   const double* __restrict__ mean_all,
                                                   double* __restrict__ sq_all, double* __restrict__ eigval,
                                                   double* __restrict__ axes, float* __restrict__ ax32) {
-    __shared__ double Q[kSub][kDesc], Z[kSub][kDesc];
+    constexpr int kRow = kDesc + 4;  // the rows' bank offsets differ
+    __shared__ double Q[kSub][kRow], Z[kSub][kRow];
+    __shared__ double part[kEigParts][kSub][kDesc];
     __shared__ double G[kSub][kSub], Rinv[kSub][kSub], S[kSub][kSub], th[kSub];
-    __shared__ double red[256];
+    __shared__ double red[kEigThreads];
     __shared__ int done;
     const int t = threadIdx.x, pair = blockIdx.x;
     const double* A = cov_all + (size_t)pair * kDesc * kDesc;
     double* sq = sq_all + (size_t)pair * 2 * kDesc * kDesc;
-    const int r = t & (kDesc - 1), h = t >> 7;  // row and vector half (4 vectors)
+    const int r = t & (kDesc - 1), h = t >> 7;  // row; part of a product's sum, pair of vectors
 
     // M = A^(2^kSquare), trace-normalised at each squaring (square_kernel)
     const double* M = sq + (size_t)((kSquare - 1) & 1) * kDesc * kDesc;
 
     // deterministic pseudo-random start
-    for (int i = t; i < kSub * kDesc; i += 256) {
+    for (int i = t; i < kSub * kDesc; i += kEigThreads) {
         uint32_t z = (uint32_t)(i + 1) * 2654435761u;
         z ^= z >> 15;
         z *= 2246822519u;
@@ -690,15 +666,21 @@ __global__ void __launch_bounds__(256) eig_kernel(const double* __restrict__ cov
     }
     __syncthreads();
 
+    // G[i][j] = X_i . Y_j, four lanes to an entry
+    auto inner = [&](const double (*X)[kRow], const double (*Y)[kRow]) {
+        if (t >= 4 * kSub * kSub) return;
+        const int i = t / (4 * kSub), j = t / 4 % kSub, q = t & 3;
+        double s = 0.0;
+#pragma unroll 8
+        for (int k = q; k < kDesc; k += 4) s = fma(X[i][k], Y[j][k], s);
+        s += __shfl_xor(s, 1);
+        s += __shfl_xor(s, 2);
+        if (q == 0) G[i][j] = s;
+    };
     // Q = orth(Z) by Cholesky QR, twice
     auto orth = [&]() {
         for (int pass = 0; pass < 2; ++pass) {
-            if (t < kSub * kSub) {
-                const int i = t / kSub, j = t % kSub;
-                double s = 0.0;
-                for (int k = 0; k < kDesc; ++k) s = fma(Z[i][k], Z[j][k], s);
-                G[i][j] = s;
-            }
+            inner(Z, Z);
             __syncthreads();
             if (t == 0) chol_inverse(G, Rinv);
             __syncthreads();
@@ -707,8 +689,8 @@ __global__ void __launch_bounds__(256) eig_kernel(const double* __restrict__ cov
             for (int u = 0; u < kSub; ++u) z[u] = Z[u][r];
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int vv = 4 * h + u;
+            for (int u = 0; u < kSub / kEigParts; ++u) {
+                const int vv = kSub / kEigParts * h + u;
                 double s = 0.0;
 #pragma unroll
                 for (int w = 0; w < kSub; ++w)
@@ -718,7 +700,10 @@ __global__ void __launch_bounds__(256) eig_kernel(const double* __restrict__ cov
             __syncthreads();
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) Q[4 * h + u][r] = Z[4 * h + u][r];
+        for (int u = 0; u < kSub / kEigParts; ++u) {
+            const int vv = kSub / kEigParts * h + u;
+            Q[vv][r] = Z[vv][r];
+        }
         __syncthreads();
     };
     orth();
@@ -727,26 +712,34 @@ __global__ void __launch_bounds__(256) eig_kernel(const double* __restrict__ cov
         const bool check = it % kCheck == 0 || it == kMaxIter;
         const double* Mi = check ? A : M;
         {
-            double s[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int k = 0; k < kDesc; ++k) {
-                const double mk = Mi[(size_t)k * kDesc + r];
+            // thread (r, h): rows 32 h .. 32 h + 31 of the sum for all vectors, so the
+            // loads of a product are in flight together
+            constexpr int kn = kDesc / kEigParts;
+            double m[kn], s[kSub] = {};
 #pragma unroll
-                for (int u = 0; u < 4; ++u) s[u] = fma(mk, Q[4 * h + u][k], s[u]);
+            for (int i = 0; i < kn; ++i) m[i] = Mi[(size_t)(kn * h + i) * kDesc + r];
+#pragma unroll
+            for (int i = 0; i < kn; ++i)
+#pragma unroll
+                for (int u = 0; u < kSub; ++u) s[u] = fma(m[i], Q[u][kn * h + i], s[u]);
+#pragma unroll
+            for (int u = 0; u < kSub; ++u) part[h][u][r] = s[u];
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kSub / kEigParts; ++u) {
+                const int vv = kSub / kEigParts * h + u;
+                double z = part[0][vv][r];
+#pragma unroll
+                for (int i = 1; i < kEigParts; ++i) z += part[i][vv][r];
+                Z[vv][r] = z;
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) Z[4 * h + u][r] = s[u];
         }
         __syncthreads();
         if (check) {
             // Rayleigh-Ritz on A: T = Q^T (A Q)
-            if (t < kSub * kSub) {
-                const int i = t / kSub, j = t % kSub;
-                double s = 0.0;
-                for (int k = 0; k < kDesc; ++k) s = fma(Q[i][k], Z[j][k], s);
-                G[i][j] = s;
-            }
+            inner(Q, Z);
             __syncthreads();
-            if (t == 0) ritz_small(G, th, S);
+            if (t < 64) ritz_small(G, th, S);
             __syncthreads();
             double res[3];
             for (int k = 0; k < 3; ++k) {
@@ -759,7 +752,7 @@ __global__ void __launch_bounds__(256) eig_kernel(const double* __restrict__ cov
                     }
                 }
                 const double e = az - th[k] * y;
-                res[k] = sqrt(block_sum(t < kDesc ? e * e : 0.0, red));
+                res[k] = sqrt(block_sum<kEigThreads>(t < kDesc ? e * e : 0.0, red));
             }
             if (t == 0) {
                 const double tol = 1e-12 * fabs(th[0]);
@@ -1521,7 +1514,7 @@ extern "C" sff_status sff_sift_pca(const sff_params* p, int32_t batch, const uin
         hipLaunchKernelGGL(square_kernel, dim3(64, batch), dim3(256), 0, st, src, src_stride,
                            sqm + (size_t)(i & 1) * kDesc * kDesc, (size_t)2 * kDesc * kDesc);
     }
-    hipLaunchKernelGGL(eig_kernel, dim3(batch), dim3(256), 0, st, cov, mean, sqm, eigval, axes, ax32);
+    hipLaunchKernelGGL(eig_kernel, dim3(batch), dim3(kEigThreads), 0, st, cov, mean, sqm, eigval, axes, ax32);
     const long total = 4L * (long)g.npx;
     const long groups = (total + kGramPx - 1) / kGramPx;
     hipLaunchKernelGGL(project_kernel, dim3((unsigned)std::min<long>(groups, kProjBlocks), batch), dim3(256), 0,
