@@ -256,28 +256,37 @@ __global__ void __launch_bounds__(256) grad_ref_kernel(CostArgs a) {
     for (int k = 0; k < CF / 4; ++k) o[k] = make_float4(sum[4 * k], sum[4 * k + 1], sum[4 * k + 2], sum[4 * k + 3]);
 }
 
+__device__ __forceinline__ void grad_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Grouping of the pixels by target centre, all three correspondences in one
 // list: element k * n + i (pixel i of the batch, n pixels) has the key
 // k * n + (centre cell of correspondence k) and the value i.  After a stable
 // sort by key, the pixels of each centre cell are in ascending pixel order.
-__global__ void target_keys_kernel(const int16_t* __restrict__ hyp, uint32_t* __restrict__ keys,
-                                   uint32_t* __restrict__ vals, int H, int W, int s, uint32_t n) {
-    const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= 3 * (size_t)n) return;
-    const uint32_t k = (uint32_t)(e / n), i = (uint32_t)(e - (size_t)k * n);
-    const size_t HW = (size_t)H * W;
-    const int b = (int)(i / HW);
-    const int pix = (int)(i - (size_t)b * HW);
-    const int y = pix / W, x = pix - y * W;
+// A thread takes a pixel and writes its three elements (375 x 1242: 6 us; a thread
+// per element with 64-bit divisions 38).
+__global__ void __launch_bounds__(256) target_keys_kernel(const int16_t* __restrict__ hyp, uint32_t* __restrict__ keys,
+                                                          uint32_t* __restrict__ vals, int H, int W, int s, uint32_t n) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t HW = (uint32_t)H * W, b = i / HW, pix = i - b * HW;
+    const int y = (int)(pix / W), x = (int)(pix - (uint32_t)y * W);
     const Targets t = targets(hyp, i, y, x, s, H, W);
-    keys[e] = k * n + (uint32_t)((size_t)b * HW + (size_t)t.y[k] * W + t.x[k]);
-    vals[e] = i;
+#pragma unroll
+    for (uint32_t k = 0; k < 3; ++k) {
+        const size_t e = (size_t)k * n + i;
+        keys[e] = k * n + b * HW + (uint32_t)t.y[k] * W + t.x[k];
+        vals[e] = i;
+    }
 }
 
 // Least-significant-digit radix sort of (key, value) pairs, 8-bit digits, one
 // pass = histogram per block, exclusive scan over (digit, block), stable
-// scatter.  Blocks of 256 threads take 16 rounds of 256 consecutive elements.
-constexpr int kSortTile = 4096;
+// scatter.  A block of 4 waves takes kSortTile consecutive elements.
+constexpr int kSortTile = 2048;
 
 __global__ void __launch_bounds__(256) sort_hist_kernel(const uint32_t* __restrict__ keys, size_t N,
                                                         int sh, uint32_t* __restrict__ hist,
@@ -349,8 +358,13 @@ __global__ void __launch_bounds__(1024) sort_scan_sums_kernel(uint32_t* __restri
     }
 }
 
-// Stable scatter of one pass: element order is (round, wave, lane), the input
-// order; the rank inside a wave comes from the lanes with the same digit.
+// Stable scatter of one pass.  A wave takes a run of kSortTile / 4 consecutive
+// elements, 64 at a time and all loaded at the start: it counts its digits, and
+// after one barrier knows where each of its digits begins; the rank among 64
+// comes from the lanes with the same digit.  Bound: the scattered stores and a
+// chain of ballots per 64 elements.  375 x 1242 (1.4 M elements), beside the
+// reference gradient: 31 us a pass; 49 with
+// 256 elements of the block a round between three barriers and their loads.
 __global__ void __launch_bounds__(256) sort_scatter_kernel(const uint32_t* __restrict__ kin,
                                                            const uint32_t* __restrict__ vin,
                                                            uint32_t* __restrict__ kout,
@@ -358,25 +372,41 @@ __global__ void __launch_bounds__(256) sort_scatter_kernel(const uint32_t* __res
                                                            int sh, const uint32_t* __restrict__ scan,
                                                            const uint32_t* __restrict__ sums,
                                                            uint32_t nblk) {
-    __shared__ uint32_t off[256];
-    __shared__ uint32_t wc[4][256];
+    constexpr int kRounds = kSortTile / 256;
+    __shared__ uint32_t wc[4][256];  // counts, then positions, of a wave's digits
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const size_t hi = (size_t)t * nblk + blockIdx.x;
-    off[t] = scan[hi] + sums[hi / 1024];
+    const uint32_t start = scan[hi] + sums[hi / 1024];
+    const size_t base = (size_t)blockIdx.x * kSortTile + (size_t)w * (kSortTile / 4) + lane;
+    uint32_t key[kRounds], val[kRounds];
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) {
+        const size_t i = base + 64 * j;
+        key[j] = i < N ? kin[i] : 0u;
+        val[j] = i < N ? vin[i] : 0u;
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) wc[q][t] = 0;
     __syncthreads();
-    const size_t base = (size_t)blockIdx.x * kSortTile;
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int j = 0; j < kSortTile / 256; ++j) {
-        const size_t i = base + (size_t)j * 256 + t;
-        const bool ok = i < N;
-        uint32_t key = 0, val = 0, d = 0;
-        if (ok) {
-            key = kin[i];
-            val = vin[i];
-            d = (key >> sh) & 255u;
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j)
+        if (base + 64 * j < N) atomicAdd(&wc[w][(key[j] >> sh) & 255u], 1u);
+    __syncthreads();
+    {
+        uint32_t p = start;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t c = wc[q][t];
+            wc[q][t] = p;
+            p += c;
         }
+    }
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) {
+        const bool ok = base + 64 * j < N;
+        const uint32_t d = (key[j] >> sh) & 255u;
         uint64_t m = __ballot(ok);
 #pragma unroll
         for (int bit = 0; bit < 8; ++bit) {
@@ -384,31 +414,44 @@ __global__ void __launch_bounds__(256) sort_scatter_kernel(const uint32_t* __res
             const uint64_t bb = __ballot(on);
             m &= on ? bb : ~bb;
         }
-        const uint32_t rank = (uint32_t)__popcll(m & below);
-        const uint32_t cnt = (uint32_t)__popcll(m);
-        if (ok && rank == cnt - 1) wc[w][d] = cnt;  // the group's last lane
-        __syncthreads();
+        const uint32_t rank = (uint32_t)__popcll(m & below), cnt = (uint32_t)__popcll(m);
+        const uint32_t at = wc[w][d];
+        grad_wave_sync();
         if (ok) {
-            uint32_t pos = off[d] + rank;
-            for (int q = 0; q < w; ++q) pos += wc[q][d];
-            kout[pos] = key;
-            vout[pos] = val;
+            kout[at + rank] = key[j];
+            vout[at + rank] = val[j];
+            if (rank == cnt - 1) wc[w][d] = at + cnt;  // the group's last lane
         }
-        __syncthreads();
-        off[t] += wc[0][t] + wc[1][t] + wc[2][t] + wc[3][t];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) wc[q][t] = 0;
-        __syncthreads();
+        grad_wave_sync();
     }
 }
 
-// start[c] = first position of a sorted key >= c, for every cell c in [0, N]
-// (binary search; any run of empty cells costs nothing extra).
-__global__ void cell_starts_kernel(const uint32_t* __restrict__ keys, uint32_t* __restrict__ start,
-                                   size_t N) {
-    const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
+// start[c] = first position of a sorted key >= c, for every cell c in [0, N].  A
+// block of 256 cells first finds the positions of its first cell and of the cell
+// past its last (64 probes a step), then each cell searches between them.
+// 375 x 1242: 37 us; 51 with a binary search over all keys per cell.
+__global__ void __launch_bounds__(256) cell_starts_kernel(const uint32_t* __restrict__ keys, uint32_t* __restrict__ start,
+                                                          size_t N) {
+    __shared__ size_t ends[2];
+    const size_t c0 = (size_t)blockIdx.x * 256, c = c0 + threadIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (w < 2) {
+        const size_t want = c0 + 256 * (size_t)w;
+        size_t lo = 0, hi = N;  // the answer is in [lo, hi]
+        while (lo < hi) {
+            // probe l is the last of the first (l + 1) / 64 of the range
+            const size_t len = hi - lo, p = lo + (len * (size_t)(lane + 1) + 63) / 64 - 1;
+            const uint64_t less = __ballot((size_t)keys[p] < want);  // a prefix of the lanes
+            const int k = __popcll(less);
+            const size_t l0 = lo;
+            if (k > 0) lo = l0 + (len * (size_t)k + 63) / 64;
+            if (k < 64) hi = l0 + (len * (size_t)(k + 1) + 63) / 64 - 1;
+        }
+        if (lane == 0) ends[w] = lo;
+    }
+    __syncthreads();
     if (c > N) return;
-    size_t lo = 0, hi = N;
+    size_t lo = ends[0], hi = ends[1];
     while (lo < hi) {
         const size_t mid = lo + (hi - lo) / 2;
         if ((size_t)keys[mid] < c) lo = mid + 1;
@@ -491,12 +534,6 @@ constexpr int kTileQ = 32;
 constexpr int kTileC = kTileQ + kWinN - 1;  // staged columns: the tile's and the window's
 constexpr int kStageCap = 2048;             // staged pixels per target-gradient tile
 constexpr int kMaxRuns = 15 * 15;           // (window row, cell row) by (window column, cell column) at a corner
-
-__device__ __forceinline__ void grad_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Add the four-channel part of the terms of one pixel: fma(g, x - y, acc).
 __device__ __forceinline__ void fma4(float g, const float4& x, const float4& y, float4& acc) {
@@ -1146,7 +1183,7 @@ extern "C" sff_status sff_cost_f32_bwd(int32_t batch, int32_t H, int32_t W, int3
         launch_cf<RefTileWideK>(cf, dim3((unsigned)((size_t)batch * H * tiles_x)), sr, a, tiles_x);
     // group the pixels by target centre: keys, then a stable radix sort
     const size_t N = L.N;
-    hipLaunchKernelGGL(target_keys_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, hyp,
+    hipLaunchKernelGGL(target_keys_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, hyp,
                        ka, va, H, W, dir, (uint32_t)n);
     int bits = 1;
     while (bits < 32 && (1ull << bits) < N) ++bits;
