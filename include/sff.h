@@ -265,11 +265,11 @@ sff_status sff_match_level(const sff_params* p, int32_t batch, int32_t dir, int3
  * 16-byte aligned.  Other arguments as for sff_match_level.  Wave-cooperative
  * gathers (below 50000 pixel updates per launch, 80000 for C = 1: 16 pixels per
  * wave, 32 for C = 1, groups of 4 neighbours and 6 samples, three views a round; below
- * 262144: 32 pixels per wave, groups of 4 neighbours and 3 samples, view by
- * view; above: 64 pixels per wave, one candidate at a time, three views a
- * round);
- * SFF_MATCH_EVAL=lane|coop|coop-32|coop-43-32|coop-46-32|coop-xts|
- * coop-46-16-xts forces one (identical results).  With dir = SFF_DIR_BOTH
+ * 200000 (262144 at level 0 for C = 3 and 4): 32 pixels per wave, groups of 4 and 3,
+ * view by view; above: 64 pixels per
+ * wave, view by view, groups of 4 and 3, or 2 and 2 at level 0 for C = 3 and 4);
+ * SFF_MATCH_EVAL=lane|coop|coop-32|coop-43-32|coop-46-32|coop-22|coop-43|
+ * coop-xts|coop-46-16-xts forces one (identical results).  With dir = SFF_DIR_BOTH
  * and 100000 or more updates the two fields run on two streams: `stream` and
  * a helper stream of the library, which waits for the work enqueued on
  * `stream` before the call, and which `stream` waits for after it (so the

@@ -704,10 +704,10 @@ sff_status launch_level(const MatchArgs& a, int iters, hipStream_t st) {
 // per wave (32 where a patch has fewer than four pieces).
 constexpr long kHalfOwnersMaxUpdates = 50000, kBinC1MaxUpdates = 80000;
 
-// From this many updates per half-step the bin matcher scores one candidate
-// at a time with all three views per round (below: 4 neighbours and 3
-// samples per group, 32 owners, view by view).
-constexpr long kBinXtsMinUpdates = 262144;
+// From this many updates per half-step a wave of the bin matcher has 64 owners
+// (below: 32, groups of 4 neighbours and 3 samples, view by view); the second at
+// level 0 for C >= 3.
+constexpr long kBinFullMinUpdates = 200000, kBinFullMinUpdates0 = 262144;
 
 // Bin-plane evaluators by launch size (updates per half-step), measured on the
 // KITTI-size pair (C = 3, packed bins, fields on two streams from 100,000
@@ -721,12 +721,20 @@ constexpr long kBinXtsMinUpdates = 262144;
 //  - level 1 (116,936 updates): groups of 4 neighbours and 3 samples, view by
 //    view, 32 owners: 0.29 (one candidate with three views a round, 64
 //    owners: 0.31);
-//  - level 0 (465,750 updates): one candidate at a time with its three views
-//    in one round, 64 owners: 0.73 (groups of 2 and 3 with the early-out:
-//    0.73; 32 owners: 0.88-0.97).  This level is bound by the vector ALU
-//    (unpacking and squared distances of the gathered pieces), and the
-//    early-out rejects only ~15 % of candidates at the cross view, so a round
-//    per view saves little.
+//  - level 0 (465,750 updates): groups of 2 and 2, view by view, 64 owners: 0.70
+//    (one candidate with its three views a round 0.70, groups of 2 and 3 0.71, of
+//    4 and 3 0.72; 32 owners: 0.90).
+// With the chip full the early-out between the views saves gathers, which set the
+// time (texture data path 92 % busy), the more the coarser the level, whose patches
+// lie further apart: ms per level of 16 KITTI-size pairs with one candidate and three
+// views a round and now: level 2 (469,248 updates) 1.85 -> 1.29, level 1
+// (1,870,976) 4.64 -> 3.66, both with groups of 4 and 3; level 0 (7,452,000) 12.4 ->
+// 11.5 with 2 and 2 (4 and 3: 11.9).  C = 1 and 2 prefer 4 and 3 at level 0 too
+// (3,726,000 updates, C = 1: 3.86 -> 3.20, 2 and 2 3.37; 1,863,000, C = 2: 2.61 ->
+// 2.24, 2.31), C = 4 2 and 2 (1,863,000: 4.27 -> 3.77; 4 and 3 4.20).
+// 64 against 32 owners, groups of 4 and 3: 233,872 updates (level 1, C = 3) 0.44 against
+// 0.49, 117,312 (level 2) 0.37 against 0.32, 116,936 (level 1) 0.29 against 0.30; 2 and 2
+// against them, 251,424 updates (sixteen 97 x 161 pairs, level 0) 0.57 against 0.55.
 // The shortest chain wins down to the smallest calls, where each lane gathering
 // its own patches (fewest instructions) had been taken below 20,000 updates; us
 // per matching stage: 96 x 160, C = 1 (15,360 updates; 32 owners, three views a
@@ -737,8 +745,9 @@ constexpr long kBinXtsMinUpdates = 262144;
 // Other tile orders were slower (row-major 1.10 ms at level 0, no XCD
 // grouping 1.37 ms, with unpacked patches).  SFF_MATCH_EVAL = "lane" (each lane
 // gathers its own patches), "coop" (2/3, 64 owners, early-out), "coop-32",
-// "coop-43-32", "coop-46-32" (32 owners, early-out), "coop-xts" (1/1, 64 owners,
-// three views a round) or "coop-46-16-xts" (32 owners for C = 1) forces one (all
+// "coop-43-32", "coop-46-32" (32 owners, early-out), "coop-22", "coop-43"
+// (64 owners, early-out), "coop-xts" (1/1, 64 owners, three views a round) or
+// "coop-46-16-xts" (32 owners for C = 1) forces one (all
 // give identical results); anything else: auto.
 template <int C>
 sff_status launch_bin_pick(int pick, const MatchArgs& a, int iters, hipStream_t st) {
@@ -748,6 +757,8 @@ sff_status launch_bin_pick(int pick, const MatchArgs& a, int iters, hipStream_t 
         case 2: return launch_level<C, PatchCoop<BinMap<C>, 2, 3, 32>>(a, iters, st);
         case 3: return launch_level<C, PatchCoop<BinMap<C>, 4, 3, 32>>(a, iters, st);
         case 5: return launch_level<C, PatchCoop<BinMap<C>, 1, 1, 64, true>>(a, iters, st);
+        case 7: return launch_level<C, PatchCoop<BinMap<C>, 2, 2>>(a, iters, st);
+        case 8: return launch_level<C, PatchCoop<BinMap<C>, 4, 3>>(a, iters, st);
         case 6:
             if constexpr (16 * bin_pieces(C) % 64 == 0)
                 return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 16, true>>(a, iters, st);
@@ -798,7 +809,11 @@ sff_status run_split(const MatchArgs& a, hipStream_t st, F launch) {
 template <int C>
 sff_status run_bin_level(const MatchArgs& a, int iters, hipStream_t st) {
     const long updates = (long)a.ndir * a.batch * a.Hk * ((a.Wk + 1) / 2);
-    int pick = updates < (C == 1 ? kBinC1MaxUpdates : kHalfOwnersMaxUpdates) ? 6 : updates < kBinXtsMinUpdates ? 3 : 5;
+    const bool unpack = C >= 3 && a.level == 0;  // bound by unpacking as much as by gathers
+    int pick = updates < (C == 1 ? kBinC1MaxUpdates : kHalfOwnersMaxUpdates)            ? 6
+               : updates < (unpack ? kBinFullMinUpdates0 : kBinFullMinUpdates) ? 3
+               : unpack                                                                 ? 7
+                                                                                        : 8;
     bool split = a.ndir == 2 && updates >= kSplitMinUpdates;
     if (const char* e = std::getenv("SFF_MATCH_EVAL")) {
         if (std::strcmp(e, "lane") == 0) pick = 0;
@@ -808,6 +823,8 @@ sff_status run_bin_level(const MatchArgs& a, int iters, hipStream_t st) {
         if (std::strcmp(e, "coop-46-32") == 0) pick = 4;
         if (std::strcmp(e, "coop-xts") == 0) pick = 5;
         if (std::strcmp(e, "coop-46-16-xts") == 0) pick = 6;
+        if (std::strcmp(e, "coop-22") == 0) pick = 7;
+        if (std::strcmp(e, "coop-43") == 0) pick = 8;
     }
     if (const char* e = std::getenv("SFF_MATCH_SPLIT")) {
         if (std::strcmp(e, "0") == 0) split = false;
