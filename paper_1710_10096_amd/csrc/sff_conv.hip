@@ -664,7 +664,7 @@ bool conv_shape_ok(int n, int H, int W, int cin, int cout, int dil) {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// conv32_fwd_kernel and the 32-channel weight gradient read x (and mask, dy)
+// conv32_column_kernel and the 32-channel weight gradient read x (and mask, dy)
 // in 16-byte pieces; unaligned tensors and SFF_CONV_IM2COL=1 (testing and
 // timing) take the element-wise kernels (the im2col forward, element-wise
 // staging of the gradient tiles), which give the same results.
@@ -683,7 +683,7 @@ bool staged_conv_enabled() {
 // as zeros (the zero padding the next layer reads), every layer's output is
 // rounded to BF16 as the per-layer kernels store it, and each output element
 // is the same MFMAs in the same order on the same values as conv3_fwd_kernel
-// and conv32_fwd_kernel, so the results are identical (tested).
+// and conv32_column_kernel, so the results are identical (tested).
 // Tiles are 26 wide so that every layer's region is at most two 16-pixel
 // groups wide (32, 30, 28 and 26 pixels: 15 % of the computed groups fall
 // outside a region, against 22 % for 64-wide tiles) and 24 tall, the most that
