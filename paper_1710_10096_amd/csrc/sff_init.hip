@@ -308,9 +308,10 @@ __global__ void __launch_bounds__(256) init_nn_kernel(InitArgs a, SplitPlanes P)
                     for (int e = 0; e < 4; ++e) {
                         if (!__any(k[e] < tk[t][K - 1])) continue;  // wave-uniform
                         int nk = k[e], ni = r * Wk + c0 + 4 * g + e;
+                        bool lt = false;  // once entered, every later entry moves down, equal keys too
 #pragma unroll
                         for (int l = 0; l < K; ++l) {
-                            const bool lt = nk < tk[t][l];
+                            lt = lt || nk < tk[t][l];
                             const int ok_ = tk[t][l], oi = ti[t][l];
                             tk[t][l] = lt ? nk : ok_;
                             ti[t][l] = lt ? ni : oi;
