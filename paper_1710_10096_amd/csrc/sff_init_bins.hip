@@ -28,8 +28,6 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-constexpr int kQRows = 8;    // query rows per block (one 16-query MFMA tile each)
-constexpr int kParts = 256 / (16 * kQRows);  // threads per query in the epipolar searches
 constexpr int kWaves = 4;    // waves per block, splitting the candidate rows
 constexpr int kCentre = 510;  // bins lie in 0..1020
 
@@ -178,8 +176,8 @@ __global__ void __launch_bounds__(256) op_planes_kernel(BinInitArgs a, OpPlanes 
         for (int x = P.offx + a.Wk; x < P.wx; ++x) row[x] = sqf;
 }
 
-// One block: kQRows rows x 16 consecutive columns of reference grid pixels of
-// one field.  Wave w scans the candidate rows r = rlo + w (mod kWaves) of the
+// One block: QR rows x 16 consecutive columns of reference grid pixels of
+// one field (a 16-query MFMA tile per row).  Wave w scans the candidate rows r = rlo + w (mod kWaves) of the
 // union of the queries' boxes, 16 candidates per MFMA tile.
 //
 // MFMA operands: A (16 x K) holds candidates, lane l giving candidate l % 16;
@@ -204,21 +202,22 @@ __global__ void __launch_bounds__(256) op_planes_kernel(BinInitArgs a, OpPlanes 
 // ms for K = 4 and 1.25 ms for K = 2, now 0.53 and 0.52 ms (K = 1: 0.36 ms).
 constexpr int kLeafCap = 56;  // candidates a query's list holds (75 KB of LDS with K = 4: two blocks per CU)
 
-template <int C, int K>
+template <int C, int K, int QR>
 __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes P) {
     using KS = KSplit<C>;
+    constexpr int kParts = 256 / (16 * QR);  // threads per query in the epipolar searches
     // partial minima of the 16 lanes of a query; for K > 1 also the lists
-    __shared__ unsigned long long red[K == 1 ? kWaves * 4 : kLeafCap][kQRows][16];
-    __shared__ int list_n[kQRows][16];
-    __shared__ int res_u[kQRows][16][K], res_v[kQRows][16][K];
-    __shared__ uint32_t res_t[kQRows][16][K];
-    __shared__ int res_n[kQRows][16];
-    __shared__ unsigned long long red2[kParts][kQRows][16];
-    __shared__ unsigned long long redx[K][kParts][kQRows][16];
+    __shared__ unsigned long long red[K == 1 ? kWaves * 4 : kLeafCap][QR][16];
+    __shared__ int list_n[QR][16];
+    __shared__ int res_u[QR][16][K], res_v[QR][16][K];
+    __shared__ uint32_t res_t[QR][16][K];
+    __shared__ int res_n[QR][16];
+    __shared__ unsigned long long red2[kParts][QR][16];
+    __shared__ unsigned long long redx[K][kParts][QR][16];
     static_assert(kLeafCap >= kWaves * 4, "the lists' memory also holds partial minima");
     const int lane = threadIdx.x & 63, w = wave_id();
     const int nq = lane & 15, g = lane >> 4;
-    const int j0 = blockIdx.x * 16, i0 = blockIdx.y * kQRows;
+    const int j0 = blockIdx.x * 16, i0 = blockIdx.y * QR;
     const int z = blockIdx.z;  // dir_index * batch + b
     const int di = z / a.batch, b = z - di * a.batch;
     const int s = (a.ndir == 2) ? (di == 0 ? 1 : -1) : a.dir0;
@@ -237,18 +236,18 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
     addr.RS = a.Wq * bin_entry_bytes(C);
 
     // queries (B operands), one 16-column tile per query row
-    h8 q32[kQRows][KS::N32 > 0 ? KS::N32 : 1];
-    h4 q16[kQRows];
+    h8 q32[QR][KS::N32 > 0 ? KS::N32 : 1];
+    h4 q16[QR];
     const int jq = min(j0 + nq, Wk - 1);
 #pragma unroll
-    for (int t = 0; t < kQRows; ++t) {
+    for (int t = 0; t < QR; ++t) {
         const size_t o = zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq;
 #pragma unroll
         for (int c = 0; c < KS::N32; ++c)
             q32[t][c] = *reinterpret_cast<const h8*>(P.q32 + ((size_t)c * P.nzk + o) * 32 + 8 * g);
         if constexpr (KS::N16 > 0) q16[t] = *reinterpret_cast<const h4*>(P.q16 + o * 16 + 4 * g);
     }
-    const int rlo = max(0, i0 - F), rhi = min(Hk - 1, i0 + kQRows - 1 + F);
+    const int rlo = max(0, i0 - F), rhi = min(Hk - 1, i0 + QR - 1 + F);
     const int nct = (16 + 2 * F + 15) / 16;
     const int ct_lo = max(0, (F - j0) >> 4);                 // first c0 + 15 >= 0
     const int ct_hi = min(nct - 1, (Wk - 1 - j0 + F) >> 4);  // last c0 < Wk
@@ -302,7 +301,7 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             if (q + 1 < total) nxt = load_tile(rn, ctn);
             const int c0 = j0 - F + 16 * ct;
             // every query row of the block has row r inside its box (wave-uniform)
-            const bool all_rows = i0 + kQRows - 1 < Hk && r >= i0 + kQRows - 1 - F && r <= i0 + F;
+            const bool all_rows = i0 + QR - 1 < Hk && r >= i0 + QR - 1 - F && r <= i0 + F;
             // Interior tiles (every candidate inside every query's box) and rows
             // inside every query row's box skip those tests.  Both conditions are
             // wave-uniform.
@@ -323,7 +322,7 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
                     }
                 }
 #pragma unroll
-                for (int t = 0; t < kQRows; ++t) {
+                for (int t = 0; t < QR; ++t) {
                     if constexpr (!kRowsIn) {
                         const int iq = i0 + t;
                         if (iq >= Hk || r < iq - F || r > iq + F) continue;
@@ -387,10 +386,10 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
         // first tile that reaches it are kept (the running minimum folded in by
         // two 3-input minima, the tile recorded when it strictly decreases); the
         // target inside that tile is recovered afterwards.
-        float best[kQRows];
-        int btile[kQRows];
+        float best[QR];
+        int btile[QR];
 #pragma unroll
-        for (int t = 0; t < kQRows; ++t) {
+        for (int t = 0; t < QR; ++t) {
             best[t] = kInf;
             btile[t] = 0;
         }
@@ -400,13 +399,13 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             best[t] = nb;
         });
 #pragma unroll
-        for (int t = 0; t < kQRows; ++t) redo = redo || (best[t] >= kExact && best[t] != kInf);
+        for (int t = 0; t < QR; ++t) redo = redo || (best[t] >= kExact && best[t] != kInf);
         redo = __syncthreads_or(redo);
         if (!redo) {
             // the smallest target index of the winning tile that reaches the minimum
             // (exact bin-grid squared distances, equal to the MFMA identity's)
 #pragma unroll
-            for (int t = 0; t < kQRows; ++t) {
+            for (int t = 0; t < QR; ++t) {
                 uint32_t bssd = 0xFFFFFFFFu, bidx = 0;
                 if (best[t] != kInf) {
                     const int r = btile[t] >> 16, c0 = j0 - F + 16 * (btile[t] & 0xFFFF);
@@ -433,7 +432,7 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             }
             __syncthreads();
             // combine the 16 partial minima (waves x lane groups) of each query
-            if (threadIdx.x < kQRows * 16) {
+            if (threadIdx.x < QR * 16) {
                 const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
                 unsigned long long m = ~0ull;
                 for (int k = 0; k < kWaves * 4; ++k) m = red[k][t][q] < m ? red[k][t][q] : m;
@@ -444,12 +443,12 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
     } else {
         // bounds: the K-th smallest of the 16 lanes' minima, plus 1 (a list takes
         // keys strictly below); none where fp32 keys would not be exact
-        float(*minima)[kQRows][16] = reinterpret_cast<float(*)[kQRows][16]>(&red[0][0][0]);
+        float(*minima)[QR][16] = reinterpret_cast<float(*)[QR][16]>(&red[0][0][0]);
         float(*bounds)[16] = reinterpret_cast<float(*)[16]>(&redx[0][0][0][0]);
         {
-            float best[kQRows];
+            float best[QR];
 #pragma unroll
-            for (int t = 0; t < kQRows; ++t) best[t] = kInf;
+            for (int t = 0; t < QR; ++t) best[t] = kInf;
             // At a stride of 4 pixels and more neighbouring patches differ, and a
             // bound from half of the rows keeps the lists short (1024 x 436, K = 4,
             // n = 4: 534 us against 629 from all rows); below, a minimum's
@@ -459,10 +458,10 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
                 best[t] = min(min(best[t], k[0]), min(min(k[1], k[2]), k[3]));
             });
 #pragma unroll
-            for (int t = 0; t < kQRows; ++t) minima[w * 4 + g][t][nq] = best[t];
+            for (int t = 0; t < QR; ++t) minima[w * 4 + g][t][nq] = best[t];
         }
         __syncthreads();
-        if (threadIdx.x < kQRows * 16) {
+        if (threadIdx.x < QR * 16) {
             const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
             float sm[K];
 #pragma unroll
@@ -482,9 +481,9 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
         __syncthreads();
 #pragma unroll 1
         for (bool again = true; again;) {
-            float bound[kQRows];
+            float bound[QR];
 #pragma unroll
-            for (int t = 0; t < kQRows; ++t) bound[t] = bounds[t][nq];
+            for (int t = 0; t < QR; ++t) bound[t] = bounds[t][nq];
             run_scan(0.f, 1, [&](int t, const float (&k)[4], int r, int c0, int) {
                 if (!__any(min(min(k[0], k[1]), min(k[2], k[3])) < bound[t])) return;  // wave-uniform, mostly
 #pragma unroll
@@ -503,7 +502,7 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             // a list that overflowed: the K-th smallest of the candidates it holds is a
             // lower bound for the next try, unless too many are equal
             bool over = false;
-            if (threadIdx.x < kQRows * 16) {
+            if (threadIdx.x < QR * 16) {
                 const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
                 if (list_n[t][q] > kLeafCap) {
                     unsigned long long sm[K];
@@ -529,11 +528,11 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             if (again) {
                 redo = __syncthreads_or(redo);
                 if (redo) break;
-                if (threadIdx.x < kQRows * 16) list_n[threadIdx.x >> 4][threadIdx.x & 15] = 0;
+                if (threadIdx.x < QR * 16) list_n[threadIdx.x >> 4][threadIdx.x & 15] = 0;
                 __syncthreads();
             }
         }
-        if (!redo && threadIdx.x < kQRows * 16) {
+        if (!redo && threadIdx.x < QR * 16) {
             // the K smallest, by K selection passes (indices are distinct)
             const int t = threadIdx.x >> 4, q = threadIdx.x & 15, cnt = list_n[t][q];
             unsigned long long prev = 0;
@@ -552,18 +551,18 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
     }
     if (redo) {  // block-uniform
         // leaf by leaf with int32 keys: the smallest (key, index) past the previous
-        int pk[kQRows], pi[kQRows];
+        int pk[QR], pi[QR];
 #pragma unroll
-        for (int t = 0; t < kQRows; ++t) {
+        for (int t = 0; t < QR; ++t) {
             pk[t] = INT_MIN;
             pi[t] = -1;
         }
-        if (threadIdx.x < kQRows * 16) res_n[threadIdx.x >> 4][threadIdx.x & 15] = 0;
+        if (threadIdx.x < QR * 16) res_n[threadIdx.x >> 4][threadIdx.x & 15] = 0;
 #pragma unroll 1
         for (int l = 0; l < K; ++l) {
-            int best[kQRows], bidx[kQRows];
+            int best[QR], bidx[QR];
 #pragma unroll
-            for (int t = 0; t < kQRows; ++t) {
+            for (int t = 0; t < QR; ++t) {
                 best[t] = INT_MAX;
                 bidx[t] = 0;
             }
@@ -579,14 +578,14 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             });
             __syncthreads();
 #pragma unroll
-            for (int t = 0; t < kQRows; ++t) {
+            for (int t = 0; t < QR; ++t) {
                 const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
                 red[w * 4 + g][t][nq] =
                     best[t] == INT_MAX ? ~0ull
                                        : ((unsigned long long)((uint32_t)best[t] + asq) << 32) | (uint32_t)bidx[t];
             }
             __syncthreads();
-            if (threadIdx.x < kQRows * 16) {
+            if (threadIdx.x < QR * 16) {
                 const int t = threadIdx.x >> 4, q = threadIdx.x & 15;
                 unsigned long long m = ~0ull;
                 for (int k = 0; k < kWaves * 4; ++k) m = red[k][t][q] < m ? red[k][t][q] : m;
@@ -598,7 +597,7 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             }
             __syncthreads();
 #pragma unroll
-            for (int t = 0; t < kQRows; ++t) {
+            for (int t = 0; t < QR; ++t) {
                 const unsigned long long m = red2[0][t][nq];
                 const uint32_t asq = P.sq[zR + (size_t)min(i0 + t, Hk - 1) * Wk + jq];
                 pk[t] = m == ~0ull ? INT_MAX : (int)((uint32_t)(m >> 32) - asq);
@@ -609,7 +608,7 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
     __syncthreads();
 
     // epipolar searches: kParts threads per query, candidates interleaved
-    const int q = threadIdx.x & 15, t = (threadIdx.x >> 4) % kQRows, part = threadIdx.x / (16 * kQRows);
+    const int q = threadIdx.x & 15, t = (threadIdx.x >> 4) % QR, part = threadIdx.x / (16 * QR);
     const int iq = i0 + t, jqq = j0 + q;
     const bool live = iq < Hk && jqq < Wk;
     const int x = n * min(jqq, Wk - 1), y = n * min(iq, Hk - 1);
@@ -682,13 +681,32 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
     a.cost[o] = 16u * (uint32_t)bestJ;
 }
 
-template <int C>
-void launch_init_bins(int leaves, dim3 grid, hipStream_t st, const BinInitArgs& a, const OpPlanes& P) {
+template <int C, int QR>
+void launch_init_rows(int leaves, hipStream_t st, const BinInitArgs& a, const OpPlanes& P) {
+    const dim3 grid((a.Wk + 15) / 16, (a.Hk + QR - 1) / QR, a.ndir * a.batch);
     switch (leaves) {
-        case 1: hipLaunchKernelGGL((init_bins_kernel<C, 1>), grid, dim3(256), 0, st, a, P); break;
-        case 2: hipLaunchKernelGGL((init_bins_kernel<C, 2>), grid, dim3(256), 0, st, a, P); break;
-        default: hipLaunchKernelGGL((init_bins_kernel<C, 4>), grid, dim3(256), 0, st, a, P); break;
+        case 1: hipLaunchKernelGGL((init_bins_kernel<C, 1, QR>), grid, dim3(256), 0, st, a, P); break;
+        case 2: hipLaunchKernelGGL((init_bins_kernel<C, 2, QR>), grid, dim3(256), 0, st, a, P); break;
+        default: hipLaunchKernelGGL((init_bins_kernel<C, 4, QR>), grid, dim3(256), 0, st, a, P); break;
     }
+}
+
+// A candidate tile is loaded once for all query rows of a block, so 8 rows where the
+// blocks fill the chip; a smaller grid waits on the chain of tiles and rows of one
+// block, which fewer rows shorten while CUs are idle.  us of the initialisation with
+// 8, 4 and 2 rows, by the number of 8-row blocks: 24 (30 x 40) 49, 36, 27; 40 (two
+// levels of 61 x 157) 57, 37, 29; 240 (96 x 160, C = 1) 72, 57, 60; 286 (97 x 161) 170,
+// 139, 160; 300 (two levels of 240 x 320) 163, 137, 155; 480 (KITTI size) 192, 190,
+// 272; with four leaves 87, 61, 47 ... 330, 269, 324 and 311, 375, 408.
+template <int C>
+void launch_init_bins(int leaves, hipStream_t st, const BinInitArgs& a, const OpPlanes& P) {
+    const size_t blocks = (size_t)((a.Wk + 15) / 16) * ((a.Hk + 7) / 8) * a.ndir * a.batch;
+    if (blocks < 100)
+        launch_init_rows<C, 2>(leaves, st, a, P);
+    else if (blocks < 400)
+        launch_init_rows<C, 4>(leaves, st, a, P);
+    else
+        launch_init_rows<C, 8>(leaves, st, a, P);
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -778,24 +796,23 @@ extern "C" sff_status sff_init_nn_bins(const sff_params* p, int32_t batch, int32
     P.offx = L.offx;
     const int nz4 = 4 * batch;
     const dim3 sgrid((g.Hk * g.Wk + 255) / 256, nz4);
-    const dim3 grid((g.Wk + 15) / 16, (g.Hk + kQRows - 1) / kQRows, a.ndir * batch);
     hipStream_t st = as_stream(stream);
     switch (p->C) {
         case 1:
             hipLaunchKernelGGL(op_planes_kernel<1>, sgrid, dim3(256), 0, st, a, P, nz4);
-            launch_init_bins<1>(leaves, grid, st, a, P);
+            launch_init_bins<1>(leaves, st, a, P);
             break;
         case 2:
             hipLaunchKernelGGL(op_planes_kernel<2>, sgrid, dim3(256), 0, st, a, P, nz4);
-            launch_init_bins<2>(leaves, grid, st, a, P);
+            launch_init_bins<2>(leaves, st, a, P);
             break;
         case 3:
             hipLaunchKernelGGL(op_planes_kernel<3>, sgrid, dim3(256), 0, st, a, P, nz4);
-            launch_init_bins<3>(leaves, grid, st, a, P);
+            launch_init_bins<3>(leaves, st, a, P);
             break;
         default:
             hipLaunchKernelGGL(op_planes_kernel<4>, sgrid, dim3(256), 0, st, a, P, nz4);
-            launch_init_bins<4>(leaves, grid, st, a, P);
+            launch_init_bins<4>(leaves, st, a, P);
             break;
     }
     return launch_status();
