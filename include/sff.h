@@ -402,8 +402,9 @@ sff_status sff_dense_sift(const sff_params* p, int32_t nimg, const uint8_t* img,
  * workspace: sff_sift_workspace_bytes(p, 4 * batch) bytes, 256-byte aligned.
  * The eigenvectors come from a subspace iteration that stops when the
  * residuals of the three leading pairs fall below 1e-12 of the largest
- * eigenvalue (at most 4000 iterations); for a zero covariance the axes are
- * arbitrary unit vectors and phi is zero.
+ * eigenvalue, or, where the spectrum does not let it, from a direct solution;
+ * they are orthonormal, also where eigenvalues are equal or zero (for a zero
+ * covariance the axes are arbitrary unit vectors and phi is zero).
  * Errors: SFF_ERR_INVALID_ARG, SFF_ERR_WORKSPACE. */
 sff_status sff_sift_pca(const sff_params* p, int32_t batch, const uint8_t* imgs, double* mean,
                         double* cov, double* eigval, double* axes, float* phi, void* workspace,

@@ -40,7 +40,7 @@ constexpr size_t kGramMaxPx = 16384;  // descriptors per Gram block (exact int32
 constexpr int kPart = kDesc * kDesc + kDesc;  // doubles per Gram partial
 constexpr int kSub = 8;                     // subspace dimension of the eigen iteration
 constexpr int kCheck = 4;                   // iterations between Rayleigh-Ritz checks
-constexpr int kMaxIter = 4000;
+constexpr int kMaxIter = 16;                // then the direct solution
 constexpr int kWinR = 3;                    // cost window -3 .. +3
 constexpr int kCT = 16;                     // cost tile side
 
@@ -589,16 +589,20 @@ __device__ double block_sum(double v, double* red) {
     return r;
 }
 
-// The three leading eigenvectors of one pair's covariance A.  The SIFT
-// covariance has a flat spectrum (neighbouring eigenvalues within a few
-// percent), so plain subspace iteration converges slowly; the iteration runs
+// The three leading eigenvectors of one pair's covariance A.  A SIFT covariance
+// often has a flat spectrum (neighbouring eigenvalues within a few percent), so
+// plain subspace iteration converges slowly; the iteration runs
 // on M = A^(2^kSquare) instead (same eigenvectors, ratios raised to that
 // power), formed beforehand by square_kernel (squarings normalised by the
 // trace).  Subspace iteration with
 // kSub vectors: Z = M Q, Q = orth(Z) (Cholesky QR, twice).  Every kCheck-th
 // step multiplies by A itself and does a Rayleigh-Ritz step in span(Q): Ritz
 // pairs of A and their residuals ||A y - theta y|| (A y = Z s); it stops when
-// the three leading residuals are below 1e-12 theta_1 (or after kMaxIter).
+// the three leading ones are unit vectors with residuals below 1e-12 theta_1.
+// Where the spectrum falls steeply (images that are flat in part, stripes), M has
+// lost the second or third vector in its rounding ((theta_3 / theta_1)^64 below
+// 1e-6 for a ratio below 0.8); such a pair, and one that has not
+// converged after kMaxIter steps, is solved directly (direct_eigen).
 // The matrices are read from global memory (symmetric: row r of M Q is read
 // down column r, coalesced).  Each axis is signed so that its component of
 // largest magnitude is positive.  Also writes the FP32 axes and mean used by
@@ -633,21 +637,323 @@ __global__ void __launch_bounds__(256) square_kernel(const double* __restrict__ 
     C[(size_t)(16 * ti + r) * kDesc + 16 * tj + c] = acc * sc * sc;
 }
 
+constexpr int kEigParts = 4, kEigThreads = kEigParts * kDesc;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+__device__ __forceinline__ double lane_double(double v, int lane) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+// Sum over the wave, the same in every lane.  All lanes must be active.
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_double<0xB1>(v);   // quad_perm 1,0,3,2
+    v += dpp_double<0x4E>(v);   // quad_perm 2,3,0,1
+    v += dpp_double<0x141>(v);  // row_half_mirror
+    v += dpp_double<0x140>(v);  // row_mirror
+    return (lane_double(v, 0) + lane_double(v, 16)) + (lane_double(v, 32) + lane_double(v, 48));
+}
+
+// 1 / v by two Newton steps on the hardware's estimate: within a few ulp.
+__device__ __forceinline__ double rcp_double(double v) {
+    double r = __builtin_amdgcn_rcp(v);
+    r = fma(fma(-v, r, 1.0), r, r);
+    return fma(fma(-v, r, 1.0), r, r);
+}
+
+// Working set of direct_eigen.  The factors of the tridiagonal systems take the
+// place of the reduction's partial sums.
+struct DirectLds {
+    double v[kDesc][kDesc];
+    union {
+        double part[kEigThreads / 64][kDesc];
+        struct {
+            double u0[3][kDesc], u1[3][kDesc], u2[3][kDesc], mult[3][kDesc];
+        };
+    };
+    double d[kDesc], e[kDesc], beta[kDesc], head[kDesc], x[3][kDesc];
+    double red[kEigThreads / 64];
+    int count[6], swapped[3][kDesc];
+};
+
+// The three largest eigenvalues of the symmetric A and orthonormal eigenvectors
+// (to th[0..2] and Y), whatever the spectrum: Householder reduction to a
+// tridiagonal matrix (the matrix in registers), the eigenvalues by bisection on Sturm counts (128
+// shifts a round for each), the vectors by inverse iteration, orthogonalised in
+// order (equal eigenvalues), and transformed back (Golub and Van Loan, "Matrix
+// Computations", sections 8.3 to 8.5).  Errors are a few ulp of the norm.
+// Bound: latency: 126 reduction steps of two barriers (half of the time), then
+// serial recurrences; 370 us, 510 with the matrix in LDS.  A pair that does not need
+// it costs an empty launch (less than keeping both methods' code and LDS in one
+// kernel: 590 against 602 us for a KITTI-size pair's features).
+__device__ __forceinline__ void direct_eigen(const double* __restrict__ A, DirectLds& L, double* th, double (*Y)[kDesc]) {
+    constexpr int kWaves = kEigThreads / 64, kRows = kDesc / kWaves;
+    const int t = threadIdx.x, lane = t & 63, wv = wave_id(), c1 = lane + 64;
+    const int h = wv >> 1, r = t & (kDesc - 1);
+    // rows wv + 8 i of the matrix, columns l and l + 64, scaled by a power of two to
+    // entries below 2
+    double a0[kRows], a1[kRows], amax = 0.0;
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        a0[i] = A[(size_t)(wv + kWaves * i) * kDesc + lane];
+        a1[i] = A[(size_t)(wv + kWaves * i) * kDesc + c1];
+        amax = fmax(amax, fmax(fabs(a0[i]), fabs(a1[i])));
+    }
+    for (int m = 1; m < 64; m <<= 1) amax = fmax(amax, __shfl_xor(amax, m));
+    if (lane == 0) L.red[wv] = amax;
+    __syncthreads();
+    for (int k = 0; k < kWaves; ++k) amax = fmax(amax, L.red[k]);
+    if (!(amax > 1e-290)) {  // nothing to tell apart (a flat image)
+        if (t < kDesc)
+            for (int k = 0; k < 3; ++k) Y[k][t] = t == k ? 1.0 : 0.0;
+        if (t < 3) th[t] = 0.0;
+        __syncthreads();
+        return;
+    }
+    const int ex = ilogb(amax);
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        a0[i] = ldexp(a0[i], -ex);
+        a1[i] = ldexp(a1[i], -ex);
+    }
+    if (wv == 0) {
+        L.v[0][lane] = a0[0];
+        L.v[0][c1] = a1[0];
+    }
+    __syncthreads();
+    // step k: row k, left in L.v by its wave, is made alpha e_(k+1) by the reflection
+    // 1 - beta v v^T; v stays there but for its first element, `head`.  Every wave
+    // forms v and w itself, elements l and l + 64 in lane l, and broadcasts those of its
+    // rows by readlane.
+#pragma unroll 1
+    for (int k = 0; k < kDesc - 2; ++k) {
+        double v0 = lane > k ? L.v[k][lane] : 0.0, v1 = c1 > k ? L.v[k][c1] : 0.0;
+        const double diag = L.v[k][k], first = lane_double(k + 1 < 64 ? v0 : v1, (k + 1) & 63);
+        const double n2 = wave_sum(v0 * v0 + v1 * v1);
+        double alpha = 0.0, beta = 0.0, head = 0.0;
+        if (n2 > 1e-60) {  // below: nothing left in the row
+            alpha = first > 0.0 ? -sqrt(n2) : sqrt(n2);
+            head = first - alpha;
+            beta = rcp_double(n2 - alpha * first);
+        }
+        v0 = lane == k + 1 ? head : v0;
+        v1 = c1 == k + 1 ? head : v1;
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < kRows; ++i)
+            if (wv + kWaves * i > k) {  // wave-uniform
+                const double v = lane_double(i < kRows / 2 ? v0 : v1, (wv + kWaves * i) & 63);
+                s0 = fma(a0[i], v, s0);
+                s1 = fma(a1[i], v, s1);
+            }
+        L.part[wv][lane] = s0;
+        L.part[wv][c1] = s1;
+        __syncthreads();
+        double w0 = 0.0, w1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            w0 += L.part[i][lane];
+            w1 += L.part[i][c1];
+        }
+        w0 = lane > k ? beta * w0 : 0.0;
+        w1 = c1 > k ? beta * w1 : 0.0;
+        const double f = 0.5 * beta * wave_sum(v0 * w0 + v1 * w1);
+        w0 -= f * v0;
+        w1 -= f * v1;
+#pragma unroll
+        for (int i = 0; i < kRows; ++i)
+            if (wv + kWaves * i > k) {
+                const int c = (wv + kWaves * i) & 63;
+                const double v = lane_double(i < kRows / 2 ? v0 : v1, c), w = lane_double(i < kRows / 2 ? w0 : w1, c);
+                a0[i] -= fma(v, w0, w * v0);
+                a1[i] -= fma(v, w1, w * v1);
+                if (wv + kWaves * i <= k + 2) {  // the next row; the last ones are read below
+                    L.v[wv + kWaves * i][lane] = a0[i];
+                    L.v[wv + kWaves * i][c1] = a1[i];
+                }
+            }
+        __syncthreads();
+        if (t == 0) {
+            L.d[k] = diag;
+            L.e[k] = alpha;
+            L.beta[k] = beta;
+            L.head[k] = head;
+        }
+    }
+    if (t == 0) {
+        L.d[kDesc - 2] = L.v[kDesc - 2][kDesc - 2];
+        L.d[kDesc - 1] = L.v[kDesc - 1][kDesc - 1];
+        L.e[kDesc - 2] = L.v[kDesc - 2][kDesc - 1];
+        L.e[kDesc - 1] = 0.0;
+    }
+    __syncthreads();
+    // eigenvalue k: #{eigenvalues >= lo} > k >= #{eigenvalues >= hi}; the norm is at most 2 kDesc
+    const int k3 = min(h, 2);
+    double lo = -2.0 * kDesc - 4.0, hi = -lo;
+#pragma unroll 1
+    for (int round = 0; round < 9; ++round) {
+        const double w = hi - lo, sigma = lo + w * ((r + 1) * (1.0 / (kDesc + 1)));
+        double q = L.d[0] - sigma;
+        int below = q < 0.0;
+#pragma unroll 4
+        for (int i = 1; i < kDesc; ++i) {
+            const double e = L.e[i - 1];
+            if (fabs(q) < 1e-200) q = -1e-200;
+            q = fma(-e * e, rcp_double(q), L.d[i] - sigma);
+            below += q < 0.0;
+        }
+        const uint64_t yes = __ballot(kDesc - below > k3);
+        if (lane == 0 && h < 3) L.count[wv] = __popcll(yes);
+        __syncthreads();
+        const int n = L.count[2 * k3] + L.count[2 * k3 + 1];
+        if (n < kDesc) hi = lo + w * ((n + 1) * (1.0 / (kDesc + 1)));
+        if (n > 0) lo = lo + w * (n * (1.0 / (kDesc + 1)));
+        __syncthreads();
+    }
+    const double lam = 0.5 * (lo + hi);
+    // T - lam = L U with row exchanges, by one lane per eigenvalue; pivots no smaller than 1e-15
+    auto pivot = [](double v) { return fabs(v) >= 1e-15 ? v : (v < 0.0 ? -1e-15 : 1e-15); };
+    const bool solver = r == 0 && h < 3;
+    if (solver) {
+        double a = L.d[0] - lam, b = L.e[0];
+#pragma unroll 4
+        for (int i = 0; i + 1 < kDesc; ++i) {
+            const double sub = L.e[i], dg = L.d[i + 1] - lam, sup = L.e[i + 1];
+            const bool swap = fabs(a) < fabs(sub);
+            const double u = rcp_double(pivot(swap ? sub : a)), m = (swap ? a : sub) * u;
+            L.u0[h][i] = u;
+            L.u1[h][i] = swap ? dg : b;
+            L.u2[h][i] = swap ? sup : 0.0;
+            L.mult[h][i] = m;
+            L.swapped[h][i] = swap;
+            a = swap ? b - m * dg : dg - m * b;
+            b = swap ? -m * sup : sup;
+        }
+        L.u0[h][kDesc - 1] = 1.0 / pivot(a);
+        L.u1[h][kDesc - 1] = L.u2[h][kDesc - 1] = 0.0;
+        th[h] = ldexp(lam, ex);
+    }
+    for (int i = t; i < 3 * kDesc; i += kEigThreads) {
+        uint32_t z = (uint32_t)(i + 1) * 2654435761u;
+        z ^= z >> 15;
+        z *= 2246822519u;
+        z ^= z >> 13;
+        L.x[i / kDesc][i % kDesc] = (double)(z & 0xFFFF) / 32768.0 - 1.0;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int it = 0; it < 3; ++it) {
+        if (solver) {
+            double* x = L.x[h];
+            double cur = x[0];
+#pragma unroll 4
+            for (int i = 0; i + 1 < kDesc; ++i) {
+                const double nxt = x[i + 1], m = L.mult[h][i];
+                const bool swap = L.swapped[h][i] != 0;
+                x[i] = swap ? nxt : cur;
+                cur = swap ? cur - m * nxt : nxt - m * cur;
+            }
+            double y1 = 0.0, y2 = 0.0;  // elements i + 1 and i + 2
+#pragma unroll 4
+            for (int i = kDesc - 1; i >= 0; --i) {
+                const double b = i == kDesc - 1 ? cur : x[i];
+                const double y = (b - L.u1[h][i] * y1 - L.u2[h][i] * y2) * L.u0[h][i];
+                x[i] = y;
+                y2 = y1;
+                y1 = y;
+            }
+        }
+        __syncthreads();
+        if (wv == 0) {  // unit vectors, each orthogonal to those before it
+            double a[3], b[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                a[k] = L.x[k][lane];
+                b[k] = L.x[k][lane + 64];
+                auto unit = [&]() {
+                    const double f = 1.0 / sqrt(wave_sum(a[k] * a[k] + b[k] * b[k]));
+                    a[k] *= f;
+                    b[k] *= f;
+                };
+                unit();
+#pragma unroll
+                for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+                    for (int j = 0; j < k; ++j) {
+                        const double f = wave_sum(a[j] * a[k] + b[j] * b[k]);
+                        a[k] -= f * a[j];
+                        b[k] -= f * b[j];
+                    }
+                    if (k > 0) unit();
+                }
+                L.x[k][lane] = a[k];
+                L.x[k][lane + 64] = b[k];
+            }
+        }
+        __syncthreads();
+    }
+    if (wv < 3) {
+        const int c1 = lane + 64;
+        double y0 = L.x[wv][lane], y1 = L.x[wv][c1];
+#pragma unroll 1
+        for (int k = kDesc - 3; k >= 0; --k) {
+            const double head = L.head[k];
+            const double v0 = lane == k + 1 ? head : lane > k ? L.v[k][lane] : 0.0;
+            const double v1 = c1 == k + 1 ? head : c1 > k ? L.v[k][c1] : 0.0;
+            const double f = L.beta[k] * wave_sum(v0 * y0 + v1 * y1);
+            y0 -= f * v0;
+            y1 -= f * v1;
+        }
+        Y[wv][lane] = y0;
+        Y[wv][c1] = y1;
+    }
+    __syncthreads();
+}
+
+
+// Eigenvalues and signed axes of a pair, in FP64 and (with the mean) FP32.
+__device__ __forceinline__ void write_axes(int pair, const double (*Y)[kDesc], const double* th,
+                                           const double* __restrict__ mean_all, double* __restrict__ eigval,
+                                           double* __restrict__ axes, float* __restrict__ ax32) {
+    const int t = threadIdx.x, lane = t & 63, k = wave_id();
+    if (k < 3) {  // the first component of largest magnitude decides the sign
+        double y0 = Y[k][lane], y1 = Y[k][lane + 64], m = fmax(fabs(y0), fabs(y1));
+        for (int d = 1; d < 64; d <<= 1) m = fmax(m, __shfl_xor(m, d));
+        const uint64_t b0 = __ballot(fabs(y0) == m), b1 = __ballot(fabs(y1) == m);
+        const double top = b0 ? lane_double(y0, __builtin_ctzll(b0)) : b1 ? lane_double(y1, __builtin_ctzll(b1)) : 0.0;
+        const double sg = top < 0.0 ? -1.0 : 1.0;
+        y0 *= sg;
+        y1 *= sg;
+        const size_t o = ((size_t)pair * 3 + k) * kDesc + lane, o32 = ((size_t)pair * 4 + k) * kDesc + lane;
+        axes[o] = y0;
+        axes[o + 64] = y1;
+        ax32[o32] = (float)y0;
+        ax32[o32 + 64] = (float)y1;
+        if (lane == 0) eigval[(size_t)pair * 3 + k] = th[k];
+    }
+    if (t < kDesc) ax32[((size_t)pair * 4 + 3) * kDesc + t] = (float)mean_all[(size_t)pair * kDesc + t];
+}
+
 // Bound: latency: four products (each 128 KB from beyond the L2s by one CU), seven
 // small factorisations in one thread, one small eigenproblem.  KITTI-size pair: 62 us;
 // 118 with 256 threads that each summed a row with 16 loads in flight (16 us a
 // product).
-constexpr int kEigParts = 4, kEigThreads = kEigParts * kDesc;
+constexpr int kEigRow = kDesc + 4;  // the rows' bank offsets differ
 __global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* __restrict__ cov_all,
                                                   const double* __restrict__ mean_all,
                                                   double* __restrict__ sq_all, double* __restrict__ eigval,
                                                   double* __restrict__ axes, float* __restrict__ ax32) {
-    constexpr int kRow = kDesc + 4;  // the rows' bank offsets differ
-    __shared__ double Q[kSub][kRow], Z[kSub][kRow];
-    __shared__ double part[kEigParts][kSub][kDesc];
+    __shared__ double Q[kSub][kEigRow], Z[kSub][kEigRow], part[kEigParts][kSub][kDesc];
     __shared__ double G[kSub][kSub], Rinv[kSub][kSub], S[kSub][kSub], th[kSub];
-    __shared__ double red[kEigThreads];
-    __shared__ int done;
+    __shared__ double Y[3][kDesc], red[2][3][2];
+    __shared__ int done;  // 1 converged, 2 to be solved directly
     const int t = threadIdx.x, pair = blockIdx.x;
     const double* A = cov_all + (size_t)pair * kDesc * kDesc;
     double* sq = sq_all + (size_t)pair * 2 * kDesc * kDesc;
@@ -667,7 +973,7 @@ __global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* __restri
     __syncthreads();
 
     // G[i][j] = X_i . Y_j, four lanes to an entry
-    auto inner = [&](const double (*X)[kRow], const double (*Y)[kRow]) {
+    auto inner = [&](const double (*X)[kEigRow], const double (*Y)[kEigRow]) {
         if (t >= 4 * kSub * kSub) return;
         const int i = t / (4 * kSub), j = t / 4 % kSub, q = t & 3;
         double s = 0.0;
@@ -741,22 +1047,33 @@ __global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* __restri
             __syncthreads();
             if (t < 64) ritz_small(G, th, S);
             __syncthreads();
-            double res[3];
-            for (int k = 0; k < 3; ++k) {
-                double az = 0.0, y = 0.0;
-                if (t < kDesc) {
+            if (t < kDesc) {  // residuals and norms, squared, of two waves
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    double az = 0.0, y = 0.0;
 #pragma unroll
                     for (int i = 0; i < kSub; ++i) {
                         az = fma(Z[i][t], S[i][k], az);
                         y = fma(Q[i][t], S[i][k], y);
                     }
+                    const double e = az - th[k] * y;
+                    const double e2 = wave_sum(e * e), y2 = wave_sum(y * y);
+                    if ((t & 63) == 0) {
+                        red[t >> 6][k][0] = e2;
+                        red[t >> 6][k][1] = y2;
+                    }
                 }
-                const double e = az - th[k] * y;
-                res[k] = sqrt(block_sum<kEigThreads>(t < kDesc ? e * e : 0.0, red));
             }
+            __syncthreads();
             if (t == 0) {
                 const double tol = 1e-12 * fabs(th[0]);
-                done = (res[0] <= tol && res[1] <= tol && res[2] <= tol) || th[0] == 0.0 || it == kMaxIter;
+                bool unit = true, close = true;
+                for (int k = 0; k < 3; ++k) {
+                    close = close && sqrt(red[0][k][0] + red[1][k][0]) <= tol;
+                    unit = unit && fabs(red[0][k][1] + red[1][k][1] - 1.0) < 1e-10;
+                }
+                // (a covariance that is all rounding is not positive: descriptors are unit vectors)
+                done = unit && close && th[0] > 1e-13 ? 1 : !unit || !(th[2] > 0.8 * th[0]) || it == kMaxIter ? 2 : 0;
             }
             __syncthreads();
             if (done) break;
@@ -764,8 +1081,11 @@ __global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* __restri
         orth();
     }
 
+    // the first squarings are used up: their place tells eig_direct_kernel whether it
+    // is needed
+    if (t == 0) sq[0] = done == 2 ? 1.0 : 0.0;
+    if (done == 2) return;  // block-uniform
     // Ritz vectors y_k = Q s_k, signed, written out
-    __shared__ double Y[3][kDesc];
     if (t < kDesc)
         for (int k = 0; k < 3; ++k) {
             double y = 0.0;
@@ -774,22 +1094,21 @@ __global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* __restri
             Y[k][t] = y;
         }
     __syncthreads();
-    if (t < 3) {
-        int best = 0;
-        for (int i = 1; i < kDesc; ++i)
-            if (fabs(Y[t][i]) > fabs(Y[t][best])) best = i;
-        red[t] = Y[t][best] < 0.0 ? -1.0 : 1.0;
-        eigval[(size_t)pair * 3 + t] = th[t];
-    }
-    __syncthreads();
-    if (t < kDesc) {
-        for (int k = 0; k < 3; ++k) {
-            const double y = red[k] * Y[k][t];
-            axes[((size_t)pair * 3 + k) * kDesc + t] = y;
-            ax32[((size_t)pair * 4 + k) * kDesc + t] = (float)y;
-        }
-        ax32[((size_t)pair * 4 + 3) * kDesc + t] = (float)mean_all[(size_t)pair * kDesc + t];
-    }
+    write_axes(pair, Y, th, mean_all, eigval, axes, ax32);
+}
+
+// The pairs that eig_kernel leaves.
+__global__ void __launch_bounds__(kEigThreads) eig_direct_kernel(const double* __restrict__ cov_all,
+                                                                 const double* __restrict__ mean_all,
+                                                                 const double* __restrict__ sq_all,
+                                                                 double* __restrict__ eigval, double* __restrict__ axes,
+                                                                 float* __restrict__ ax32) {
+    __shared__ DirectLds lds;
+    __shared__ double Y[3][kDesc], th[3];
+    const int pair = blockIdx.x;
+    if (sq_all[(size_t)pair * 2 * kDesc * kDesc] == 0.0) return;
+    direct_eigen(cov_all + (size_t)pair * kDesc * kDesc, lds, th, Y);
+    write_axes(pair, Y, th, mean_all, eigval, axes, ax32);
 }
 
 // phi = axes (f - mean) per pixel of the pair's four images, float4 (phi, 0).
@@ -1515,6 +1834,7 @@ extern "C" sff_status sff_sift_pca(const sff_params* p, int32_t batch, const uin
                            sqm + (size_t)(i & 1) * kDesc * kDesc, (size_t)2 * kDesc * kDesc);
     }
     hipLaunchKernelGGL(eig_kernel, dim3(batch), dim3(kEigThreads), 0, st, cov, mean, sqm, eigval, axes, ax32);
+    hipLaunchKernelGGL(eig_direct_kernel, dim3(batch), dim3(kEigThreads), 0, st, cov, mean, sqm, eigval, axes, ax32);
     const long total = 4L * (long)g.npx;
     const long groups = (total + kGramPx - 1) / kGramPx;
     hipLaunchKernelGGL(project_kernel, dim3((unsigned)std::min<long>(groups, kProjBlocks), batch), dim3(256), 0,
