@@ -68,8 +68,15 @@ inline int gram_blocks(const SiftGeom& g) {
     return (int)std::max(std::max<size_t>(1, std::min<size_t>(kMaxGramBlocks, nb)), (per + kGramMaxPx - 1) / kGramMaxPx);
 }
 
+// Descriptors that a wave of the Gram pass may hand to the FP64 one.
+constexpr int kGramWaves = 8, kGramStep = 2 * kGramPx;  // waves of a block, descriptors per step
+inline int gram_list(const SiftGeom& g) {
+    const int steps = (int)((4 * g.npx + kGramStep - 1) / kGramStep), nb = gram_blocks(g);
+    return (steps + nb - 1) / nb * (kGramStep / kGramWaves);
+}
+
 struct SiftWs {
-    size_t Cs, part, gsum, sq, ax32, total;
+    size_t Cs, part, list, count, gsum, sq, ax32, total;
 };
 
 inline SiftWs sift_ws(const SiftGeom& g, int nimg) {
@@ -78,7 +85,10 @@ inline SiftWs sift_ws(const SiftGeom& g, int nimg) {
     SiftWs L;
     L.Cs = 0;
     L.part = L.Cs + al((size_t)nimg * kBins * g.plane_c * sizeof(float));
-    L.gsum = L.part + al((size_t)pairs * gram_blocks(g) * kPart * sizeof(double));
+    const size_t waves = (size_t)pairs * gram_blocks(g) * kGramWaves;
+    L.list = L.part + al((size_t)pairs * gram_blocks(g) * kPart * sizeof(double));
+    L.count = L.list + al(waves * gram_list(g) * sizeof(int));
+    L.gsum = L.count + al(waves * sizeof(int));
     L.sq = L.gsum + al((size_t)pairs * kPart * sizeof(double));
     L.ax32 = L.sq + al((size_t)pairs * 2 * kDesc * kDesc * sizeof(double));
     L.total = L.ax32 + al((size_t)pairs * 4 * kDesc * sizeof(float));
@@ -244,17 +254,17 @@ __global__ void __launch_bounds__(256) sift_out_kernel(const float* __restrict__
 // Gram matrix and sum of the descriptors of one pair (4 H W of them), summed
 // exactly in integers on the int8 matrix cores.  An entry f (0 <= f <= 1, FP32)
 // is the fixed-point number F 2^-38 with F = sum_i d_i 256^i, five digits d_i in
-// [-128, 127]: exact for f >= 2^-15 (24 significant bits), within 2^-39 below.
-// With digit planes D_i, G = sum_ij 2^(8 (i + j) - 76) D_i D_j^T; the 19
-// products with i + j >= 3 are formed (v_mfma_i32_16x16x64_i8, K = 64 pixels),
+// [-128, 127]: exact for f = 0 and f >= 2^-15 (24 significant bits).  A descriptor
+// with an entry between (one in twenty to a hundred of textured images, most on
+// images with faint texture) is left out here and listed for gram_rest_kernel, which
+// sums its products in FP64.
+// With digit planes D_i, G = sum_ij 2^(8 (i + j) - 76) D_i D_j^T; the 22
+// products with i + j >= 2 are formed (v_mfma_i32_16x16x64_i8, K = 64 pixels),
 // those of one i + j in one accumulator, exact below 2^31 (5 products of 2^14 per
 // pixel, at most kGramMaxPx pixels per block).  The dropped ones are at most
-// 2^-44 per pixel, with mixed signs: on a KITTI-size pair the covariance agrees
-// with FP64 products of the same descriptors to 1e-12 of its norm, and its error
-// against 64 bits is that of the FP32 descriptors, 4e-8, as before.  (With
-// i + j >= 4 alone it is 3e-11 off: a small entry's lowest digit is a multiple of
-// a power of two, and of +128 and -128 a digit can only be the latter, so its mean
-// is not zero.)
+// 2^-53 per pixel, with mixed signs (a lowest digit is zero for f >= 2^-7): against
+// exact sums of the same descriptors the result is 4e-18 of the matrix's norm off and
+// less, where FP64 sums are 1e-17 to 7e-17 off.  (Without i + j = 2: 1e-14.)
 // Each block takes every nblk-th group of 128 descriptors: a thread forms a
 // quarter descriptor and writes its entries' upper four digits (a word) and
 // lowest digit (a byte) entry-major to LDS; wave w turns entries 16 w .. + 15
@@ -264,22 +274,25 @@ __global__ void __launch_bounds__(256) sift_out_kernel(const float* __restrict__
 // neither the writes nor the reads meet in a bank.  Waves 2 p and 2 p + 1 share
 // the tile rows p and 7 - p of the upper triangle (9 of the 36 16 x 16 tiles).
 // Partials (FP64, upper tiles only) go to part[pair][block].
-// Bound: the vector ALU (forming and splitting descriptors, 55 % of the cycles)
-// and the matrix units beside it (40 %).  The int8 products take less than half
-// of the FP64 products' time at the units' rates; KITTI-size pair: 369 us, against
-// 742 us with v_mfma_f64_16x16x4f64; 408 us with all waves of a block in the same
+// Bound: the vector ALU (forming and splitting descriptors) and the matrix units
+// beside it. The int8 products take less than half
+// of the FP64 products' time at the units' rates; KITTI-size pair: 421 us and 38 for
+// the listed descriptors (5 %), against 742 us with v_mfma_f64_16x16x4f64 for all.
+// Measured with i + j >= 3 alone, 369 us: 408 us with all waves of a block in the same
 // phase, 470 us with two blocks of 4 waves per CU (their accumulators spill).
 struct GramArgs {
     const float* Cs;
     double* part;
-    int H, W, nblk;
+    int *list, *count;  // [pair][block][wave][cap] descriptors for gram_rest_kernel, [pair][block][wave]
+    int H, W, nblk, cap;
 };
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
-constexpr int kDigits = 5, kSum0 = 3, kSums = 6;  // digits of an entry; values of i + j, from kSum0
+constexpr int kDigits = 5, kSum0 = 2, kSums = 7;  // digits of an entry; values of i + j, from kSum0
 constexpr float kFix = 0x1p30f;        // scale of the upper four digits
+constexpr float kFixMin = 0x1p15f;     // smallest entry that five digits hold exactly, scaled
 
-// Tile n (of 9) of wave pair p: rows p (8 - p tiles), then 7 - p.
+// Tile n (of 9) of wave (pair) p: rows p (8 - p tiles), then 7 - p.
 __device__ __forceinline__ void gram_tile(int p, int n, int& I, int& J) {
     const bool first = n < 8 - p;
     I = first ? p : 7 - p;
@@ -297,8 +310,7 @@ __device__ __forceinline__ void digits_4x4(const uint32_t (&w)[4], uint32_t (&d)
     d[3] = __builtin_amdgcn_perm(e, c, 0x07060302u);
 }
 
-constexpr int kGramTiles = 5;                          // tiles of a wave, at most
-constexpr int kGramWaves = 8, kGramStep = 2 * kGramPx;  // waves of a block, descriptors per step
+constexpr int kGramTiles = 5;  // tiles of a wave, at most
 
 __global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
     __shared__ __align__(16) uint32_t hi[2][kDesc * kGramPx];  // entry-major: upper digits,
@@ -310,13 +322,13 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
     const int pair = blockIdx.y;
     const float* Cs = a.Cs + (size_t)pair * 4 * kBins * He * We;
     i32x4 acc[kGramTiles][kSums];
-    int dsum[kDigits];  // this lane's digit sums of entry 16 w + l % 16
+    int64_t dsum = 0;  // this lane's sum of F of entry 16 w + l % 16
+    const int slot_w = (pair * a.nblk + blockIdx.x) * kGramWaves + w;
+    int listed = 0;  // of this wave
 #pragma unroll
     for (int n = 0; n < kGramTiles; ++n)
 #pragma unroll
         for (int k = 0; k < kSums; ++k) acc[n][k] = i32x4{0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < kDigits; ++i) dsum[i] = 0;
     const int wp = w >> 1, n0 = (w & 1) * kGramTiles, nt = w & 1 ? 9 - kGramTiles : kGramTiles;
     float4 rows[8];  // the cells of the step after next
     auto load = [&](int base) {
@@ -328,8 +340,22 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
     auto digits = [&](int base) {
         float v[32];
         desc_normalise(rows, v, base + (t >> 2) < total ? kFix : 0.f);
+        uint32_t least = ~0u;  // smallest entry above zero (its bits, less one)
+#pragma unroll
+        for (int k = 0; k < 32; ++k) least = min(least, __float_as_uint(v[k]) - 1u);
+        if (const uint64_t small = __ballot(least < __float_as_uint(kFixMin) - 1u)) {
+            const uint64_t quads = (small | small >> 1 | small >> 2 | small >> 3) & 0x1111111111111111ull;
+            if ((quads >> (lane & ~3)) & 1) {
+#pragma unroll
+                for (int k = 0; k < 32; ++k) v[k] = 0.f;
+                if (q == 0)
+                    a.list[(size_t)slot_w * a.cap + listed + __popcll(quads & ((1ull << lane) - 1ull))] = base + (t >> 2);
+            }
+            listed += __popcll(quads);
+        }
         // pixel slot turned by the quarter, so that a wave's writes meet all banks
-        const int slot = (px + 16 * q) & 63;
+        int slot = (px + 16 * q) & 63;
+        asm("" : "+v"(slot));  // addresses formed here, not kept in registers between steps
         uint32_t* hs = hi[w >> 2];
         int8_t* ls = low[w >> 2];
 #pragma unroll
@@ -344,9 +370,11 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
     // digit operands of entry tile w: lane = entry l % 16, pixels 16 (l / 16) .. + 15
     // (the entries are quarter w / 2's)
     auto operands = [&]() {
-#pragma unroll
+#pragma unroll 1
         for (int s = 0; s < 2; ++s) {
-            const int li = lane & 15, lg = ((lane >> 4) + wp) & 3, e = 16 * w + li;
+            int ln = lane;
+            asm("" : "+v"(ln));  // as for the digits' addresses: 252 registers, no spills
+            const int li = ln & 15, lg = ((ln >> 4) + wp) & 3, e = 16 * w + li;
             uint32_t d[kDigits][4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -365,8 +393,10 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
 #pragma unroll
             for (int i = 0; i < kDigits; ++i) {
                 ops[s][(w * kDigits + i) * 64 + lane] = i32x4{(int)d[i][0], (int)d[i][1], (int)d[i][2], (int)d[i][3]};
+                int sum = 0;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) dsum[i] = __builtin_amdgcn_sdot4((int)d[i][c], 0x01010101, dsum[i], false);
+                for (int c = 0; c < 4; ++c) sum = __builtin_amdgcn_sdot4((int)d[i][c], 0x01010101, sum, false);
+                dsum += (int64_t)sum << (8 * i);
             }
         }
     };
@@ -427,18 +457,93 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
             double gs = 0.0;
 #pragma unroll
             for (int k = 0; k < kSums; ++k) gs = fma((double)acc[n][k][v], (double)(1ull << (8 * k)), gs);
-            part[(size_t)(16 * I + 4 * (lane >> 4) + v) * kDesc + 16 * J + (lane & 15)] = gs * 0x1p-52;
+            part[(size_t)(16 * I + 4 * (lane >> 4) + v) * kDesc + 16 * J + (lane & 15)] = gs * 0x1p-60;
         }
     }
-    double sum = 0.0;
-#pragma unroll
-    for (int i = 0; i < kDigits; ++i) {
-        int s = dsum[i];  // over the four pixel groups
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        sum = fma((double)s, (double)(1ull << (8 * i)), sum);
-    }
+    // over the four pixel groups (below 2^53)
+    double sum = (double)dsum;
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
     if (lane < 16) part[kDesc * kDesc + 16 * w + lane] = sum * 0x1p-38;
+    if (lane == 0) a.count[slot_w] = listed;
+}
+
+// The listed descriptors' products and sums in FP64, added to the block's partials
+// (v_mfma_f64_16x16x4f64: A = 16 entries of 4 descriptors, B = 16 entries of the same
+// ones).  The descriptors are staged in LDS, 64 at a time; wave w owns the tile rows w
+// and 7 - w, and the operand of tile column J is also the A operand of tile row J.
+// Bound: the FP64 matrix cores where most descriptors are listed; on textured images
+// reading and writing the partials.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <int W>
+__device__ __forceinline__ void rest_tiles(const float (*D)[kDesc + 4], int n, int lane, f64x4 (&acc)[9]) {
+    const int li = lane & 15, lk = lane >> 4;
+    for (int k0 = 0; k0 < n; k0 += 4) {
+        double b[8];
+#pragma unroll
+        for (int J = W; J < 8; ++J) b[J] = (double)D[k0 + lk][16 * J + li];
+#pragma unroll
+        for (int m = 0; m < 9; ++m) {
+            constexpr int I1 = 7 - W;
+            const int I = m < 8 - W ? W : I1, J = m < 8 - W ? W + m : I1 + m - (8 - W);
+            acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[I], b[J], acc[m], 0, 0, 0);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(256) gram_rest_kernel(GramArgs a) {
+    __shared__ float D[kGramPx][kDesc + 4];
+    const int t = threadIdx.x, q = t & 3, px = t >> 2, lane = t & 63, w = wave_id();
+    const int pair = blockIdx.y, block = pair * a.nblk + blockIdx.x;
+    int first[kGramWaves + 1];  // of a wave's list in the block's
+    first[0] = 0;
+#pragma unroll
+    for (int i = 0; i < kGramWaves; ++i) first[i + 1] = first[i] + a.count[block * kGramWaves + i];
+    const int n = first[kGramWaves];
+    if (n == 0) return;
+    const int He = a.H + kExt, We = a.W + kExt, npx = a.H * a.W;
+    f64x4 acc[9];
+#pragma unroll
+    for (int m = 0; m < 9; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+    double sum = 0.0;
+    for (int base = 0; base < n; base += kGramPx) {
+        const int e = min(base + px, n - 1);
+        int wave = 0;
+#pragma unroll
+        for (int i = 1; i < kGramWaves; ++i) wave += e >= first[i];
+        int at = e;  // in the wave's list
+#pragma unroll
+        for (int i = 1; i < kGramWaves; ++i) at = wave == i ? e - first[i] : at;
+        int m, y, x;
+        desc_pixel(a.list[(size_t)(block * kGramWaves + wave) * a.cap + at], npx, a.W, m, y, x);
+        float v[32];
+        desc_quarter(a.Cs + ((size_t)pair * 4 + m) * kBins * He * We, We, y, x, q, v);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 32; ++k) D[px][32 * q + k] = base + px < n ? v[k] : 0.f;
+        __syncthreads();
+        const int here = min(n - base, kGramPx);
+        switch (w) {  // wave-uniform
+            case 0: rest_tiles<0>(D, here, lane, acc); break;
+            case 1: rest_tiles<1>(D, here, lane, acc); break;
+            case 2: rest_tiles<2>(D, here, lane, acc); break;
+            default: rest_tiles<3>(D, here, lane, acc); break;
+        }
+        if (t < kDesc)
+            for (int k = 0; k < here; ++k) sum += (double)D[k][t];
+    }
+    double* part = a.part + (size_t)block * kPart;
+    // accumulator element v of lane l: row l / 16 + 4 v, column l % 16 of the tile
+#pragma unroll
+    for (int m = 0; m < 9; ++m) {
+        int I, J;
+        gram_tile(w, m, I, J);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            part[(size_t)(16 * I + (lane >> 4) + 4 * v) * kDesc + 16 * J + (lane & 15)] += acc[m][v];
+    }
+    if (t < kDesc) part[kDesc * kDesc + t] += sum;
 }
 
 // Partials summed per entry (upper tiles of G, then S) with 8 interleaved
@@ -1819,8 +1924,10 @@ extern "C" sff_status sff_sift_pca(const sff_params* p, int32_t batch, const uin
     hipStream_t st = as_stream(stream);
     launch_cells(g, nimg, p->C, imgs, Cs, st);
     const int nblk = gram_blocks(g);
-    GramArgs ga{Cs, part, g.H, g.W, nblk};
+    GramArgs ga{Cs, part, reinterpret_cast<int*>(ws + L.list), reinterpret_cast<int*>(ws + L.count), g.H, g.W, nblk,
+                gram_list(g)};
     hipLaunchKernelGGL(gram_kernel, dim3(nblk, batch), dim3(64 * kGramWaves), 0, st, ga);
+    hipLaunchKernelGGL(gram_rest_kernel, dim3(nblk, batch), dim3(256), 0, st, ga);
     double* gsum = reinterpret_cast<double*>(ws + L.gsum);
     hipLaunchKernelGGL(gram_sum_kernel, dim3((kSumEntries + 255) / 256, batch), dim3(256), 0, st, part, nblk,
                        gsum);
