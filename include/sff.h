@@ -381,9 +381,10 @@ sff_status sff_disparity_fill(const sff_params* p, int32_t batch, const int16_t*
  * zero). */
 
 /* Device workspace (bytes) of sff_dense_sift for nimg images and of
- * sff_sift_pca for nimg = 4 * batch images: orientation and cell-sum planes
- * (about 64 bytes per pixel and image) plus FP64 partial sums (up to 34 MB
- * per pair); 0 for invalid arguments. */
+ * sff_sift_pca for nimg = 4 * batch images: cell-sum planes and descriptor
+ * lists (about 36 bytes per pixel and image) plus FP64 partial sums (75 KB per
+ * 768 descriptors, from 196608 descriptors 19 MB, per pair); 0 for invalid
+ * arguments. */
 size_t sff_sift_workspace_bytes(const sff_params* p, int32_t nimg);
 
 /* Dense SIFT of nimg images [nimg][H][W][C] uint8 (C = p->C) into

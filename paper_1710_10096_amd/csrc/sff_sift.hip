@@ -37,7 +37,7 @@ constexpr float kClampV = 0.2f;
 constexpr int kGramPx = 64;                 // descriptors per Gram step (4 threads each)
 constexpr int kMaxGramBlocks = 256;  // one block per CU
 constexpr size_t kGramMaxPx = 16384;  // descriptors per Gram block (exact int32 sums)
-constexpr int kPart = kDesc * kDesc + kDesc;  // doubles per Gram partial
+constexpr int kPart = 36 * 256 + kDesc;  // doubles per Gram partial: upper 16 x 16 tiles, sums
 constexpr int kSub = 8;                     // subspace dimension of the eigen iteration
 constexpr int kCheck = 4;                   // iterations between Rayleigh-Ritz checks
 constexpr int kMaxIter = 16;                // then the direct solution
@@ -60,11 +60,14 @@ inline SiftGeom sift_geom(const sff_params& p) {
     return g;
 }
 
-// At most one block per CU, each with at least two steps of 128 descriptors if
-// there are that many, and never more than kGramMaxPx.
+// At most one block per CU, each with at least six steps of 128 descriptors if there
+// are that many (the same for every batch, so that a pair's sums do not depend on it),
+// and never more than kGramMaxPx.  A block costs a partial of 75 KB: a 96 x 160 pair
+// needs 8.8 MB of workspace, 34.6 with two steps a block and whole matrices; its
+// features take as long (597 and 599 us; 617 with eight steps).
 inline int gram_blocks(const SiftGeom& g) {
     const size_t per = 4 * g.npx;
-    const size_t nb = (per + 4 * kGramPx - 1) / (4 * kGramPx);
+    const size_t nb = (per + 12 * kGramPx - 1) / (12 * kGramPx);
     return (int)std::max(std::max<size_t>(1, std::min<size_t>(kMaxGramBlocks, nb)), (per + kGramMaxPx - 1) / kGramMaxPx);
 }
 
@@ -292,6 +295,13 @@ constexpr int kDigits = 5, kSum0 = 2, kSums = 7;  // digits of an entry; values 
 constexpr float kFix = 0x1p30f;        // scale of the upper four digits
 constexpr float kFixMin = 0x1p15f;     // smallest entry that five digits hold exactly, scaled
 
+// Place of entry (r, c) of tile (I, J), I <= J, in a partial.
+__host__ __device__ constexpr int gram_at(int I, int J, int r, int c) {
+    return ((I * (17 - I)) / 2 + J - I) * 256 + r * 16 + c;
+}
+constexpr int kSumAt = 36 * 256;  // and of the sums
+static_assert(gram_at(7, 7, 15, 15) + 1 == kSumAt, "36 tiles");
+
 // Tile n (of 9) of wave (pair) p: rows p (8 - p tiles), then 7 - p.
 __device__ __forceinline__ void gram_tile(int p, int n, int& I, int& J) {
     const bool first = n < 8 - p;
@@ -457,14 +467,14 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_kernel(GramArgs a) {
             double gs = 0.0;
 #pragma unroll
             for (int k = 0; k < kSums; ++k) gs = fma((double)acc[n][k][v], (double)(1ull << (8 * k)), gs);
-            part[(size_t)(16 * I + 4 * (lane >> 4) + v) * kDesc + 16 * J + (lane & 15)] = gs * 0x1p-60;
+            part[gram_at(I, J, 4 * (lane >> 4) + v, lane & 15)] = gs * 0x1p-60;
         }
     }
     // over the four pixel groups (below 2^53)
     double sum = (double)dsum;
     sum += __shfl_xor(sum, 16);
     sum += __shfl_xor(sum, 32);
-    if (lane < 16) part[kDesc * kDesc + 16 * w + lane] = sum * 0x1p-38;
+    if (lane < 16) part[kSumAt + 16 * w + lane] = sum * 0x1p-38;
     if (lane == 0) a.count[slot_w] = listed;
 }
 
@@ -540,20 +550,17 @@ __global__ void __launch_bounds__(256) gram_rest_kernel(GramArgs a) {
         int I, J;
         gram_tile(w, m, I, J);
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            part[(size_t)(16 * I + (lane >> 4) + 4 * v) * kDesc + 16 * J + (lane & 15)] += acc[m][v];
+        for (int v = 0; v < 4; ++v) part[gram_at(I, J, (lane >> 4) + 4 * v, lane & 15)] += acc[m][v];
     }
-    if (t < kDesc) part[kDesc * kDesc + t] += sum;
+    if (t < kDesc) part[kSumAt + t] += sum;
 }
 
-// Partials summed per entry (upper tiles of G, then S) with 8 interleaved
-// accumulators combined in a fixed order: deterministic.
-constexpr int kSumEntries = kDesc * kDesc + kDesc;
+// Partials summed per entry with 8 interleaved accumulators combined in a fixed
+// order: deterministic.
 __global__ void __launch_bounds__(256) gram_sum_kernel(const double* __restrict__ part, int nblk,
                                                        double* __restrict__ gsum) {
     const int e = blockIdx.x * 256 + threadIdx.x, pair = blockIdx.y;
-    if (e >= kSumEntries) return;
-    if (e < kDesc * kDesc && ((e / kDesc) >> 4) > ((e % kDesc) >> 4)) return;  // lower tile: not stored
+    if (e >= kPart) return;
     const double* P = part + (size_t)pair * nblk * kPart + e;
     double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int b = 0;
@@ -561,17 +568,19 @@ __global__ void __launch_bounds__(256) gram_sum_kernel(const double* __restrict_
 #pragma unroll
         for (int u = 0; u < 8; ++u) s[u] += P[(size_t)(b + u) * kPart];
     for (; b < nblk; ++b) s[0] += P[(size_t)b * kPart];
-    gsum[(size_t)pair * kSumEntries + e] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    gsum[(size_t)pair * kPart + e] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
 // mean = S / N, cov = G / N - mean mean^T (G from its upper tiles).
 __global__ void __launch_bounds__(kDesc) gram_cov_kernel(const double* __restrict__ gsum, double inv_n,
                                                         double* __restrict__ mean, double* __restrict__ cov) {
     const int r = blockIdx.x, pair = blockIdx.y, c = threadIdx.x;
-    const double* g = gsum + (size_t)pair * kSumEntries;
-    const bool up = (r >> 4) <= (c >> 4);
-    const double grc = g[up ? (size_t)r * kDesc + c : (size_t)c * kDesc + r];
-    const double mr = g[kDesc * kDesc + r] * inv_n, mc = g[kDesc * kDesc + c] * inv_n;
+    const double* g = gsum + (size_t)pair * kPart;
+    const int lo = min(r, c), hi = max(r, c);
+    const bool up = (r >> 4) != (c >> 4);  // a diagonal tile is stored whole
+    const int a = up ? lo : r, b = up ? hi : c;
+    const double grc = g[gram_at(a >> 4, b >> 4, a & 15, b & 15)];
+    const double mr = g[kSumAt + r] * inv_n, mc = g[kSumAt + c] * inv_n;
     cov[((size_t)pair * kDesc + r) * kDesc + c] = grc * inv_n - mr * mc;
     if (r == 0) mean[(size_t)pair * kDesc + c] = mc;
 }
@@ -1929,7 +1938,7 @@ extern "C" sff_status sff_sift_pca(const sff_params* p, int32_t batch, const uin
     hipLaunchKernelGGL(gram_kernel, dim3(nblk, batch), dim3(64 * kGramWaves), 0, st, ga);
     hipLaunchKernelGGL(gram_rest_kernel, dim3(nblk, batch), dim3(256), 0, st, ga);
     double* gsum = reinterpret_cast<double*>(ws + L.gsum);
-    hipLaunchKernelGGL(gram_sum_kernel, dim3((kSumEntries + 255) / 256, batch), dim3(256), 0, st, part, nblk,
+    hipLaunchKernelGGL(gram_sum_kernel, dim3((kPart + 255) / 256, batch), dim3(256), 0, st, part, nblk,
                        gsum);
     hipLaunchKernelGGL(gram_cov_kernel, dim3(kDesc, batch), dim3(kDesc), 0, st, gsum,
                        1.0 / (4.0 * (double)g.npx), mean, cov);
