@@ -393,7 +393,7 @@ __global__ void flip_weights_kernel(const bf16_t* __restrict__ w, bf16_t* __rest
 // ones.  Global loads run one row ahead.
 // Bound: HBM (192 B per pixel with the mask: 357 MB on four 1242 x 375 images,
 // 73 us at the rate of a large copy).  There, with dy and its mask one tensor
-// (238 MB): 50 us for Cin = 32 and 37 us for Cin = 3, against 328 and 270 us for
+// (238 MB): 56 us for Cin = 32 and 37 us for Cin = 3, against 328 and 270 us for
 // blocks that scattered every row transposed into LDS in 2-byte writes, three
 // times over.
 constexpr int kWgPx = 32, kWgWaves = 8;
@@ -481,6 +481,12 @@ __global__ void __launch_bounds__(64 * kWgWaves) wgrad_column_kernel(const bf16_
             const int e = 64 * k + lane, xx = x0 + (e >> 2);
             zo[k] = xx < W ? xx * 64 + 16 * (e & 3) : kOutside;
         }
+        uint32_t keep[4];  // the K values (pixels 8 g + e) inside the image
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const int px = x0 + 8 * g + 2 * h;
+            keep[h] = (px < W ? 0xFFFFu : 0u) | (px + 1 < W ? 0xFFFF0000u : 0u);
+        }
         uint4 xv[XP], zv[2], mv[2];
         auto load_x = [&](int i) {  // input row i (the window's row of output row i)
             const int yy = phase + dil * (k0 + i);
@@ -542,7 +548,17 @@ __global__ void __launch_bounds__(64 * kWgWaves) wgrad_column_kernel(const bf16_
                 dz[2][t] = read_transposed(zs, 8 * g, 16 * t, 32);
                 accb[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2][t], ones, accb[t], 0, 0, 0);
             }
-            // input row i meets output row i + 1 - ky at kernel row ky
+            // input row i meets output row i + 1 - ky at kernel row ky.  Past the ends of
+            // the chunk and the image's columns there is no output: the zeros in its place
+            // must not meet an infinite x (NaN), so x is cleared there too.  Always, with
+            // masks: 56 us where 50 without; a branch around them takes 60 and spills
+            auto operand = [&](const v8bf& b, int ky) {
+                const uint32_t row = i + 1 - ky >= 0 && i + 1 - ky < nk ? ~0u : 0u;
+                v4u v = __builtin_bit_cast(v4u, b);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) v[h] &= keep[h] & row;
+                return __builtin_bit_cast(v8bf, v);
+            };
             if constexpr (CIN == 32) {
 #pragma unroll
                 for (int kx = 0; kx < 3; ++kx)
@@ -550,20 +566,24 @@ __global__ void __launch_bounds__(64 * kWgWaves) wgrad_column_kernel(const bf16_
                     for (int it = 0; it < 2; ++it) {
                         const v8bf b = read_transposed(xs, 8 * g + kx * dil, 16 * it, 32);
 #pragma unroll
-                        for (int ky = 0; ky < 3; ++ky)
+                        for (int ky = 0; ky < 3; ++ky) {
+                            const v8bf bk = operand(b, ky);
 #pragma unroll
                             for (int ot = 0; ot < 2; ++ot) {
                                 v4f& q = acc[(ot * 2 + it) * 9 + 3 * ky + kx];
-                                q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2 - ky][ot], b, q, 0, 0, 0);
+                                q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2 - ky][ot], bk, q, 0, 0, 0);
                             }
+                        }
                     }
             } else {
                 const v8bf b = read_transposed(xs, 8 * g, 0, 16);
 #pragma unroll
-                for (int ky = 0; ky < 3; ++ky)
+                for (int ky = 0; ky < 3; ++ky) {
+                    const v8bf bk = operand(b, ky);
 #pragma unroll
                     for (int ot = 0; ot < 2; ++ot)
-                        acc[ot * 3 + ky] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2 - ky][ot], b, acc[ot * 3 + ky], 0, 0, 0);
+                        acc[ot * 3 + ky] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dz[2 - ky][ot], bk, acc[ot * 3 + ky], 0, 0, 0);
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
