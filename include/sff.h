@@ -18,9 +18,12 @@
  *    enqueueing returns SFF_ERR_HIP; faults inside kernels surface at the
  *    caller's next synchronisation.
  *  - The library is thread-safe.  Its state, per device, is the fixed scratch
- *    array of sff_wht_features_noalloc and one helper stream with two events
- *    (sff_match_level_bins, sff_cost_f32_bwd), created on first use and kept
- *    until the process ends.
+ *    array of sff_wht_features_noalloc and up to four helper streams with two
+ *    events each (sff_match_level_bins, sff_match_level, sff_cost_f32_bwd),
+ *    dealt to the calling threads, created on first use outside a stream
+ *    capture and kept until the process ends.  Calls may be captured: a helper
+ *    stream then takes part in the capture until that ends, and other calls use
+ *    another or keep to their own stream.
  *
  * Data layouts (row-major)
  *  - image  uint8  [n][H][W][C]                 C = 1..4 channels

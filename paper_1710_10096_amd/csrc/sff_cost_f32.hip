@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <optional>
 #include <type_traits>
 
 #include "sff_internal.hpp"
@@ -1164,17 +1165,13 @@ extern "C" sff_status sff_cost_f32_bwd(int32_t batch, int32_t H, int32_t W, int3
     const bool buf = (size_t)H * W * cf * 4 <= (size_t)kSkipOff;
     // The reference-map gradient and the target-map gradients (with the
     // grouping they need) read the same inputs and write different maps, so
-    // the reference gradient runs on the library's helper stream beside them
+    // the reference gradient runs on a helper stream of the library beside them
     // (SFF_COST_F32_SPLIT=0: one stream; identical results either way).
     const char* sp = std::getenv("SFF_COST_F32_SPLIT");
-    std::unique_lock<std::mutex> lock(helper_lock(), std::defer_lock);
-    HelperStream* hs = nullptr;
-    if (!(sp && std::strcmp(sp, "0") == 0)) {
-        lock.lock();
-        hs = helper_for_current_device();
-        if (hs && !helper_fork(hs, st)) return SFF_ERR_HIP;
-    }
-    hipStream_t sr = hs ? hs->stream : st;
+    std::optional<HelperUse> helper;
+    if (!(sp && std::strcmp(sp, "0") == 0)) helper.emplace(st);
+    const bool split = helper && helper->stream();
+    hipStream_t sr = split ? helper->stream() : st;
     if (lane_grad)
         launch_cf<RefK>(cf, grid, sr, a);
     else if (buf)
@@ -1213,6 +1210,6 @@ extern "C" sff_status sff_cost_f32_bwd(int32_t batch, int32_t H, int32_t W, int3
                                 (const uint32_t*)start, (const uint32_t*)kin, (const uint32_t*)vin);
     }
     const sff_status r = launch_status();
-    if (hs && !helper_join(hs, st)) return SFF_ERR_HIP;
+    if (split && !helper->join()) return SFF_ERR_HIP;
     return r;
 }

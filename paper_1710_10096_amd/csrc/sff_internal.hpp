@@ -137,20 +137,30 @@ __device__ __forceinline__ int uniform_offset(uint32_t x, int r) {
     return (int)(((uint64_t)x * (uint64_t)(2 * r + 1)) >> 32) - r;
 }
 
-// The library's helper stream of the current device (default priority, not
-// blocking on the null stream, created on first use and kept until the
-// process ends) with a fork and a join event, for a call that runs two
-// independent launch sequences concurrently: helper_fork makes the helper
-// wait for the work enqueued on st so far, helper_join makes st wait for the
-// helper's.  Callers hold helper_lock() from the fork to the join (the events
-// are shared); helper_for_current_device returns null on a runtime error.
+// A helper stream of the library (default priority, not blocking on the null
+// stream, created on first use and kept until the process ends) with a fork and a
+// join event.
 struct HelperStream {
+    std::mutex mutex;  // from a fork to its join
     hipStream_t stream = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
 };
-std::mutex& helper_lock();
-HelperStream* helper_for_current_device();
-bool helper_fork(HelperStream* h, hipStream_t st);
-bool helper_join(HelperStream* h, hipStream_t st);
+
+// For a call that runs two independent launch sequences concurrently: the helper
+// stream, which waits for the work enqueued on st so far; join makes st wait for
+// the helper's.  stream() is null, and the call keeps to st, where no helper can be
+// had: all of them in captures of other streams, the first use inside a capture, or a
+// runtime error.
+class HelperUse {
+public:
+    explicit HelperUse(hipStream_t st);
+    hipStream_t stream() const { return h_ ? h_->stream : nullptr; }
+    bool join();
+
+private:
+    hipStream_t st_;
+    HelperStream* h_ = nullptr;
+    std::unique_lock<std::mutex> lock_;
+};
 
 }  // namespace sff

@@ -792,14 +792,12 @@ sff_status run_split(const MatchArgs& a, hipStream_t st, F launch) {
     f1.hyp = a.hyp + 4 * fine;
     f1.cost = a.cost + fine;
     if (a.hyp_coarse) f1.hyp_coarse = a.hyp_coarse + 4 * coarse;
-    std::lock_guard<std::mutex> lock(helper_lock());
-    HelperStream* hs = helper_for_current_device();
-    if (!hs) return launch(a, st);
-    if (!helper_fork(hs, st)) return SFF_ERR_HIP;
+    HelperUse helper(st);
+    if (!helper.stream()) return launch(a, st);
     const sff_status r0 = launch(f0, st);
-    const sff_status r1 = launch(f1, hs->stream);
+    const sff_status r1 = launch(f1, helper.stream());
     // join even after a launch error, so the caller's stream never runs ahead
-    if (!helper_join(hs, st)) return SFF_ERR_HIP;
+    if (!helper.join()) return SFF_ERR_HIP;
     return r0 != SFF_OK ? r0 : r1;
 }
 
