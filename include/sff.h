@@ -506,7 +506,7 @@ sff_status sff_cost_f32_bwd(int32_t batch, int32_t H, int32_t W, int32_t cf, int
  * ((ky - 1) dil, (kx - 1) dil); bias [cout] FP32.  Supported: cin in {3, 32},
  * cout = 32.  Results are rounded to BF16 (nearest even) on store.
  *   y = act(bias + sum_tap W_tap x_shifted), act = ReLU if relu != 0.
- * For cin = 32 and 16-byte aligned tensors the forward, input-gradient and
+ * For cin = 32 and 16-byte aligned tensors (weights among them) the forward, input-gradient and
  * weight-gradient kernels read their inputs in 16-byte pieces (the forward
  * without an im2col tile); SFF_CONV_IM2COL=1 forces the element-wise kernels
  * (same results).
@@ -570,7 +570,7 @@ sff_status sff_quantise_features(int32_t n, int32_t H, int32_t W, const uint16_t
 /* The network's last layer with its output as descriptor records: the 32 -> 32
  * convolution of sff_conv3x3_bf16_fwd without ReLU, its BF16 result normalised,
  * scaled and rounded as by sff_quantise_features (the same records as the two
- * calls, without the features in memory).  x and desc 16-byte aligned.
+ * calls, without the features in memory).  x, w and desc 16-byte aligned.
  * Errors: SFF_ERR_INVALID_ARG. */
 sff_status sff_conv3x3_bf16_records(int32_t n, int32_t H, int32_t W, int32_t dil, const uint16_t* x,
                                     const uint16_t* w, const float* bias, float scale, int16_t* desc,

@@ -203,7 +203,7 @@ __device__ __forceinline__ v4u8a quantise8(const v4u8a& o, int ln, int g, float 
 // are dealt to the two output tiles so that a lane ends up with 8 consecutive
 // channels: one 16-byte store per pixel and lane, 1 KB per wave.  Every output is
 // the MFMAs of conv_fwd_kernel<32, 32> in the same order on the same values, so
-// the results are identical.  x (and mask) must be 16-byte aligned.
+// the results are identical.  x, w (and mask) must be 16-byte aligned.
 // Bound: HBM (128 B per pixel, 192 with the mask): on four 1242 x 375 images
 // 49 us (4.9 TB/s, the rate of a large copy) and 88 us with the mask (357 MB,
 // past the 256 MB of the Infinity Cache), where rows staged in LDS for each of
@@ -684,7 +684,7 @@ bool conv_shape_ok(int n, int H, int W, int cin, int cout, int dil) {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// conv32_column_kernel and the 32-channel weight gradient read x (and mask, dy)
+// conv32_column_kernel and the 32-channel weight gradient read x, w (and mask, dy)
 // in 16-byte pieces; unaligned tensors and SFF_CONV_IM2COL=1 (testing and
 // timing) take the element-wise kernels (the im2col forward, element-wise
 // staging of the gradient tiles), which give the same results.
@@ -893,9 +893,9 @@ __global__ void __launch_bounds__(512) featnet_fwd_kernel(const bf16_t* __restri
     fused_layer32<kFusedY, kFusedX, true>(bufA, nullptr, wa, bz, false, y0, x0, H, W, y, img);
 }
 
-bool use_conv32(const void* x, const void* mask) {
-    if ((reinterpret_cast<uintptr_t>(x) & 15) != 0 || (reinterpret_cast<uintptr_t>(mask) & 15) != 0) return false;
-    return staged_conv_enabled();
+bool use_conv32(const void* x, const void* mask, const void* w = nullptr) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(mask) | reinterpret_cast<uintptr_t>(w);
+    return (at & 15) == 0 && staged_conv_enabled();
 }
 
 // scale > 0: y receives descriptor records (without mask).
@@ -947,7 +947,7 @@ extern "C" sff_status sff_conv3x3_bf16_fwd(int32_t n, int32_t H, int32_t W, int3
     else if (cin == 3)
         hipLaunchKernelGGL((conv_fwd_kernel<3, 32>), grid, dim3(256), 0, st, x, nullptr, w, bias, y,
                            H, W, dil, relu);
-    else if (use_conv32(x, nullptr))
+    else if (use_conv32(x, nullptr, w))
         launch_conv32(x, nullptr, w, bias, y, n, H, W, dil, relu, st);
     else
         hipLaunchKernelGGL((conv_fwd_kernel<32, 32>), grid, dim3(256), 0, st, x, nullptr, w, bias,
@@ -960,7 +960,7 @@ extern "C" sff_status sff_conv3x3_bf16_records(int32_t n, int32_t H, int32_t W, 
                                                int16_t* desc, void* stream) {
     if (!conv_shape_ok(n, H, W, 32, 32, dil) || !x || !w || !desc || !(scale > 0.f) || scale > 8192.f)
         return SFF_ERR_INVALID_ARG;
-    if ((reinterpret_cast<uintptr_t>(x) & 15) != 0 || (reinterpret_cast<uintptr_t>(desc) & 15) != 0)
+    if (((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(desc)) & 15) != 0)
         return SFF_ERR_INVALID_ARG;
     launch_conv32(x, nullptr, w, bias, reinterpret_cast<uint16_t*>(desc), n, H, W, dil, 0, as_stream(stream), scale);
     return launch_status();
