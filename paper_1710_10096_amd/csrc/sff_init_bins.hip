@@ -201,6 +201,10 @@ __global__ void __launch_bounds__(256) op_planes_kernel(BinInitArgs a, OpPlanes 
 // of the 64 lanes inserted in about half of all steps: 1024 x 436, fmax 400, 1.79
 // ms for K = 4 and 1.25 ms for K = 2, now 0.53 and 0.52 ms (K = 1: 0.36 ms).
 constexpr int kLeafCap = 56;  // candidates a query's list holds (75 KB of LDS with K = 4: two blocks per CU)
+// Scans that fill the lists: leaf by leaf costs about as much as eight (300 x 400, n = 1,
+// four leaves, textures periodic in 16 columns and 4 rows: 14 and 22 ms in up to ten
+// scans; 20 and 29 with three at most).
+constexpr int kListTries = 8;
 
 template <int C, int K, int QR>
 __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes P) {
@@ -479,8 +483,9 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
             list_n[t][q] = 0;
         }
         __syncthreads();
+        bool again = true;
 #pragma unroll 1
-        for (bool again = true; again;) {
+        for (int tries = 0; again; ++tries) {
             float bound[QR];
 #pragma unroll
             for (int t = 0; t < QR; ++t) bound[t] = bounds[t][nq];
@@ -524,9 +529,12 @@ __global__ void __launch_bounds__(256) init_bins_kernel(BinInitArgs a, OpPlanes 
                     over = true;
                 }
             }
+            // a texture whose best candidates all fall to one lane (periodic in 16 columns and
+            // 4 rows), met from worse to better, lowers the bound a little per scan: after
+            // kListTries, leaf by leaf
             again = __syncthreads_or(over);
             if (again) {
-                redo = __syncthreads_or(redo);
+                redo = __syncthreads_or(redo || tries == kListTries - 1);
                 if (redo) break;
                 if (threadIdx.x < QR * 16) list_n[threadIdx.x >> 4][threadIdx.x & 15] = 0;
                 __syncthreads();
