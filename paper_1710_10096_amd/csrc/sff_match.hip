@@ -27,6 +27,8 @@
 #include <cstdlib>
 #include <cstring>
 
+#include <type_traits>
+
 #include "sff_device.hpp"
 
 namespace sff {
@@ -620,54 +622,67 @@ __global__ void __launch_bounds__(64) half_step_kernel(MatchArgs a, int it, int 
             return c;
         };
         auto sample = [&](int t) { return offset(t, draw(t, jj)); };
-        constexpr int kRS = E::kRG;
-        for (int t = 0; t < a.rs_samples; t += kRS) {
-            if (kRS > 1 && t + kRS <= a.rs_samples) {
-                Hyp cg[kRS];
-                bool wg[kRS];
-                bool any = false;
-                if constexpr (O < 64) {
-                    // the lanes past the owners draw too: lane group g = lane / O
-                    // draws sample t + LG p + g of owner lane mod O in pass p, and
-                    // each owner collects its draws by shuffles (the same numbers,
-                    // fewer Philox evaluations per lane)
-                    constexpr int LG = 64 / O, NP = (kRS + LG - 1) / LG;
-                    const int og = lane % O, grp = lane / O;
-                    const int col = min(step * (tx * O + og) + par, a.Wk - 1);
-                    U4 rr[NP];
+        // `left` samples from t on, at most G: one group
+        auto group = [&](auto size, int t, int left) {
+            constexpr int G = decltype(size)::value;
+            Hyp cg[G];
+            bool wg[G];
+            bool any = false;
+            if constexpr (O < 64) {
+                // the lanes past the owners draw too: lane group g = lane / O
+                // draws sample t + LG p + g of owner lane mod O in pass p, and
+                // each owner collects its draws by shuffles (the same numbers,
+                // fewer Philox evaluations per lane)
+                constexpr int LG = 64 / O, NP = (G + LG - 1) / LG;
+                const int og = lane % O, grp = lane / O;
+                const int col = min(step * (tx * O + og) + par, a.Wk - 1);
+                U4 rr[NP];
 #pragma unroll
-                    for (int p = 0; p < NP; ++p) rr[p] = draw(t + LG * p + grp, col);
+                for (int p = 0; p < NP; ++p) rr[p] = draw(t + LG * p + grp, col);
 #pragma unroll
-                    for (int m = 0; m < kRS; ++m) {
-                        const int src = (m % LG) * O + og;
-                        U4 d;
-                        d.x = (uint32_t)__shfl((int)rr[m / LG].x, src);
-                        d.y = (uint32_t)__shfl((int)rr[m / LG].y, src);
-                        d.z = (uint32_t)__shfl((int)rr[m / LG].z, src);
-                        d.w = (uint32_t)__shfl((int)rr[m / LG].w, src);
-                        cg[m] = offset(t + m, d);
-                    }
-                } else {
-#pragma unroll
-                    for (int m = 0; m < kRS; ++m) cg[m] = sample(t + m);
+                for (int m = 0; m < G; ++m) {
+                    const int src = (m % LG) * O + og;
+                    U4 d;
+                    d.x = (uint32_t)__shfl((int)rr[m / LG].x, src);
+                    d.y = (uint32_t)__shfl((int)rr[m / LG].y, src);
+                    d.z = (uint32_t)__shfl((int)rr[m / LG].z, src);
+                    d.w = (uint32_t)__shfl((int)rr[m / LG].w, src);
+                    cg[m] = offset(t + m, d);
                 }
-#pragma unroll
-                for (int m = 0; m < kRS; ++m) {
-                    wg[m] = act && !same(cg[m], centre);
-                    any = any || wg[m];
-                }
-                if (!__any(any)) continue;
-                uint32_t cc[kRS];
-                if constexpr (E::kGroups) V.template cost_belowN<kRS>(wg, cg, x, y, bestc, cc);
-#pragma unroll
-                for (int m = 0; m < kRS; ++m) take(wg[m], cg[m], cc[m]);
             } else {
-                for (int u = t; u < min(t + kRS, a.rs_samples); ++u) {
-                    const Hyp c0 = sample(u);
-                    const bool w0 = act && !same(c0, centre);
-                    if (!__any(w0)) continue;
-                    take(w0, c0, V.cost_below(w0, x, y, c0, bestc));
-                }
+#pragma unroll
+                for (int m = 0; m < G; ++m) cg[m] = sample(t + m);
+            }
+#pragma unroll
+            for (int m = 0; m < G; ++m) {
+                wg[m] = act && m < left && !same(cg[m], centre);
+                any = any || wg[m];
+            }
+            if (!__any(any)) return;
+            uint32_t cc[G];
+            if constexpr (E::kGroups) V.template cost_belowN<G>(wg, cg, x, y, bestc, cc);
+#pragma unroll
+            for (int m = 0; m < G; ++m) take(wg[m], cg[m], cc[m]);
+        };
+        // Whole groups (of 6, also one that lacks a single sample), then half a group of
+        // 6, then the rest one by one.  us for 3 to 5 samples, three iterations, records
+        // 375 x 1242: 417, 441, 481 (the rest of a group of 6 one by one 433, 482, 535;
+        // always a whole group 439, 448, 461); bins 97 x 161: 60, 65, 72 (63, 68, 74;
+        // 71, 71, 72).  Two samples in a group of 3: 122 us, one by one 116 (bins 240 x 400).
+        constexpr int kRS = E::kRG, kFull = kRS >= 6 ? kRS - 1 : kRS, kHalf = kRS >= 6 ? kRS / 2 : 1;
+        for (int t = 0; t < a.rs_samples;) {
+            const int left = a.rs_samples - t;
+            if (kRS > 1 && left >= kFull) {
+                group(std::integral_constant<int, kRS>{}, t, left);
+                t += kRS;
+            } else if (kHalf > 1 && left >= kHalf) {
+                group(std::integral_constant<int, kHalf>{}, t, kHalf);
+                t += kHalf;
+            } else {
+                const Hyp c0 = sample(t);
+                const bool w0 = act && !same(c0, centre);
+                if (__any(w0)) take(w0, c0, V.cost_below(w0, x, y, c0, bestc));
+                ++t;
             }
         }
     }
