@@ -252,8 +252,9 @@ sff_status sff_init_nn_bins(const sff_params* p, int32_t batch, int32_t dir, int
  *   (H * W > 16.7 M at C = 3 or 4) each lane gathers its own records.  With
  *   dir = SFF_DIR_BOTH and from 100000 to a million updates the two fields run
  *   on two streams, as in sff_match_level_bins.  SFF_MATCH_EVAL=lane|
- *   coop-narrow|coop-wide|coop-narrow-32|coop-wide-32|coop-46-32|coop-xts and
- *   SFF_MATCH_SPLIT=0|1 force one (identical results; testing and timing).
+ *   coop-46-32|coop-xts and SFF_MATCH_SPLIT=0|1 force one (identical results;
+ *   testing and timing; coop and the names of shapes built before mean
+ *   coop-46-32).
  * Errors: SFF_ERR_INVALID_ARG (also for level >= levels - 1 with a non-NULL
  *   hyp_coarse, and for overlapping hyp/hyp_coarse). */
 sff_status sff_match_level(const sff_params* p, int32_t batch, int32_t dir, int32_t level,
@@ -271,8 +272,9 @@ sff_status sff_match_level(const sff_params* p, int32_t batch, int32_t dir, int3
  * 200000 (262144 at level 0 for C = 3 and 4): 32 pixels per wave, groups of 4 and 3,
  * view by view; above: 64 pixels per
  * wave, view by view, groups of 4 and 3, or 2 and 2 at level 0 for C = 3 and 4);
- * SFF_MATCH_EVAL=lane|coop|coop-32|coop-43-32|coop-46-32|coop-22|coop-43|
- * coop-xts|coop-46-16-xts forces one (identical results).  With dir = SFF_DIR_BOTH
+ * SFF_MATCH_EVAL=lane|coop-46-16-xts|coop-43-32|coop-22|coop-43 forces one
+ * (identical results; the names of shapes built before mean the nearest: coop
+ * coop-43, coop-32 and coop-46-32 coop-43-32, coop-xts coop-46-16-xts).  With dir = SFF_DIR_BOTH
  * and 100000 or more updates the two fields run on two streams: `stream` and
  * a helper stream of the library, which waits for the work enqueued on
  * `stream` before the call, and which `stream` waits for after it (so the

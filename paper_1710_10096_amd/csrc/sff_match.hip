@@ -24,6 +24,7 @@
 // overlap, so one level's planes (BinGeom: 24 bytes per position at C = 3,
 // each bin stored for four rows) are a fifth of the descriptor records' size
 // and the gathers mostly hit the L2 instead of streaming records.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
@@ -122,10 +123,10 @@ __device__ __forceinline__ int dirmul(int s, int v) { return s > 0 ? v : -v; }
 // poor candidate soonest (measured 1.8% faster at level 0 than temporal,
 // stereo, cross).
 //
-// Evaluators with the same results: per lane (LaneEval, BinLane: fewest
-// instructions and the shortest chain of round trips; for launches too small to
-// fill the chip) and cooperative (PatchCoop: fewest cache-line lookups), which
-// must be called by all lanes of the wave.
+// Evaluators with the same results: per lane (LaneEval for record maps of 2 GiB
+// and more, and with BinLane the reference that the tests compare with) and
+// cooperative (PatchCoop: fewest cache-line lookups), which must be called by all
+// lanes of the wave.
 template <int C>
 struct LaneEval {
     static constexpr int kOwners = 64;
@@ -176,7 +177,7 @@ struct LaneEval {
 // patch and the three target patches, with the same early-out and view order as
 // the descriptor records.  A patch is P = bin_pieces(C) pieces of 16 bytes,
 // contiguous (4 entries of 4 plane rows; 4 pieces of packed bins for C = 3).
-// BinLane: each lane gathers its own patches.
+// BinLane: each lane gathers its own patches (reference for the tests).
 template <int C>
 struct BinLane {
     static constexpr int P = bin_pieces(C);
@@ -485,7 +486,7 @@ struct PatchCoop {
 // hand-off (own from the coarse field, neighbours already at this level);
 // 3 = hand-off only (no propagation or search), used when iters == 0.
 //
-// Block = one wave: E::kOwners (64, or 32 for the smallest launches) pixels of
+// Block = one wave: E::kOwners (64, 32, or 16 for the smallest launches) pixels of
 // the half-step's colour in one grid row (all pixels for mode 3).  Lanes past
 // the row's end or past the owners stay in the wave (for the cooperative
 // gathers) without a pixel of their own.  One-wave blocks let a
@@ -758,30 +759,32 @@ constexpr long kBinFullMinUpdates = 200000, kBinFullMinUpdates0 = 262144;
 // updates (240 x 320, two levels, 76,800: 250 against 277 with 43-32; six 96 x 160
 // pairs, 92,160: 309 against 305).
 // Other tile orders were slower (row-major 1.10 ms at level 0, no XCD
-// grouping 1.37 ms, with unpacked patches).  SFF_MATCH_EVAL = "lane" (each lane
-// gathers its own patches), "coop" (2/3, 64 owners, early-out), "coop-32",
-// "coop-43-32", "coop-46-32" (32 owners, early-out), "coop-22", "coop-43"
-// (64 owners, early-out), "coop-xts" (1/1, 64 owners, three views a round) or
-// "coop-46-16-xts" (32 owners for C = 1) forces one (all
-// give identical results); anything else: auto.
+// grouping 1.37 ms, with unpacked patches).
+enum class BinShape { kLane, kSmall, k43x32, k22, k43 };
+
 template <int C>
-sff_status launch_bin_pick(int pick, const MatchArgs& a, int iters, hipStream_t st) {
-    switch (pick) {
-        case 0: return launch_level<C, BinLane<C>>(a, iters, st);
-        case 1: return launch_level<C, PatchCoop<BinMap<C>, 2, 3>>(a, iters, st);
-        case 2: return launch_level<C, PatchCoop<BinMap<C>, 2, 3, 32>>(a, iters, st);
-        case 3: return launch_level<C, PatchCoop<BinMap<C>, 4, 3, 32>>(a, iters, st);
-        case 5: return launch_level<C, PatchCoop<BinMap<C>, 1, 1, 64, true>>(a, iters, st);
-        case 7: return launch_level<C, PatchCoop<BinMap<C>, 2, 2>>(a, iters, st);
-        case 8: return launch_level<C, PatchCoop<BinMap<C>, 4, 3>>(a, iters, st);
-        case 6:
-            if constexpr (16 * bin_pieces(C) % 64 == 0)
-                return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 16, true>>(a, iters, st);
-            else
-                return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 32, true>>(a, iters, st);
-        default: break;
+sff_status launch_bin_shape(BinShape shape, const MatchArgs& a, int iters, hipStream_t st) {
+    switch (shape) {
+        case BinShape::kLane: return launch_level<C, BinLane<C>>(a, iters, st);
+        case BinShape::k43x32: return launch_level<C, PatchCoop<BinMap<C>, 4, 3, 32>>(a, iters, st);
+        case BinShape::k22:
+            if constexpr (C >= 3) return launch_level<C, PatchCoop<BinMap<C>, 2, 2>>(a, iters, st);
+            [[fallthrough]];
+        case BinShape::k43: return launch_level<C, PatchCoop<BinMap<C>, 4, 3>>(a, iters, st);
+        case BinShape::kSmall: break;
     }
-    return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 32>>(a, iters, st);
+    return launch_level<C, PatchCoop<BinMap<C>, 4, 6, 16 * bin_pieces(C) % 64 == 0 ? 16 : 32, true>>(a, iters, st);
+}
+
+// The value of an environment variable among `names`, else -1.
+int env_choice(const char* var, std::initializer_list<const char*> names) {
+    const char* e = std::getenv(var);
+    int i = 0;
+    for (const char* n : names) {
+        if (e && std::strcmp(e, n) == 0) return i;
+        ++i;
+    }
+    return -1;
 }
 
 // The forward and inverse fields of a level are independent (each reads only
@@ -816,55 +819,47 @@ sff_status run_split(const MatchArgs& a, hipStream_t st, F launch) {
     return r0 != SFF_OK ? r0 : r1;
 }
 
-// SFF_MATCH_SPLIT = "0" or "1" forces one launch sequence for both fields or
-// the two-stream split (identical results; the switch exists to test and time
-// both); anything else: by launch size.
+// SFF_MATCH_EVAL = "lane" (each lane gathers its own patches), "coop-46-16-xts" (the
+// smallest calls' shape), "coop-43-32", "coop-22", "coop-43" (64 owners) and
+// SFF_MATCH_SPLIT = "0" (one launch sequence for both fields) or "1" (two streams)
+// force one (identical results; to test and time each), names of shapes that are no
+// longer built the nearest one; anything else: by launch size.
 template <int C>
 sff_status run_bin_level(const MatchArgs& a, int iters, hipStream_t st) {
     const long updates = (long)a.ndir * a.batch * a.Hk * ((a.Wk + 1) / 2);
-    const bool unpack = C >= 3 && a.level == 0;  // bound by unpacking as much as by gathers
-    int pick = updates < (C == 1 ? kBinC1MaxUpdates : kHalfOwnersMaxUpdates)            ? 6
-               : updates < (unpack ? kBinFullMinUpdates0 : kBinFullMinUpdates) ? 3
-               : unpack                                                                 ? 7
-                                                                                        : 8;
-    bool split = a.ndir == 2 && updates >= kSplitMinUpdates;
-    if (const char* e = std::getenv("SFF_MATCH_EVAL")) {
-        if (std::strcmp(e, "lane") == 0) pick = 0;
-        if (std::strcmp(e, "coop") == 0) pick = 1;
-        if (std::strcmp(e, "coop-32") == 0) pick = 2;
-        if (std::strcmp(e, "coop-43-32") == 0) pick = 3;
-        if (std::strcmp(e, "coop-46-32") == 0) pick = 4;
-        if (std::strcmp(e, "coop-xts") == 0) pick = 5;
-        if (std::strcmp(e, "coop-46-16-xts") == 0) pick = 6;
-        if (std::strcmp(e, "coop-22") == 0) pick = 7;
-        if (std::strcmp(e, "coop-43") == 0) pick = 8;
-    }
-    if (const char* e = std::getenv("SFF_MATCH_SPLIT")) {
-        if (std::strcmp(e, "0") == 0) split = false;
-        if (std::strcmp(e, "1") == 0) split = a.ndir == 2;
-    }
-    if (!split) return launch_bin_pick<C>(pick, a, iters, st);
-    return run_split(a, st, [&](const MatchArgs& f, hipStream_t fs) { return launch_bin_pick<C>(pick, f, iters, fs); });
+    // C = 3 unpacks its bins and C = 4 has as many pieces again: at level 0, where patches
+    // overlap most, these are bound by the vector ALU as much as by the gathers
+    const bool wide = C >= 3 && a.level == 0;
+    BinShape shape = updates < (C == 1 ? kBinC1MaxUpdates : kHalfOwnersMaxUpdates) ? BinShape::kSmall
+                     : updates < (wide ? kBinFullMinUpdates0 : kBinFullMinUpdates) ? BinShape::k43x32
+                     : wide                                                        ? BinShape::k22
+                                                                                   : BinShape::k43;
+    const int eval = env_choice("SFF_MATCH_EVAL", {"lane", "coop-46-16-xts", "coop-43-32", "coop-22", "coop-43",  // as listed
+                                                   "coop-xts", "coop-32", "coop-46-32", "coop"});
+    constexpr BinShape kNearest[] = {BinShape::kSmall, BinShape::k43x32, BinShape::k43x32, BinShape::k43};
+    if (eval >= 0) shape = eval < 5 ? (BinShape)eval : kNearest[eval - 5];
+    const int forced = env_choice("SFF_MATCH_SPLIT", {"0", "1"});
+    const bool split = a.ndir == 2 && (forced >= 0 ? forced == 1 : updates >= kSplitMinUpdates);
+    if (!split) return launch_bin_shape<C>(shape, a, iters, st);
+    return run_split(a, st, [&](const MatchArgs& f, hipStream_t fs) { return launch_bin_shape<C>(shape, f, iters, fs); });
 }
 
 // Largest descriptor map (bytes) the cooperative evaluators address (32-bit offsets).
 constexpr size_t kMaxCoopMapBytes = (size_t)kNoTarget;
 
+enum class RecShape { kLane, kSmall, k46x32 };
+
 template <int C>
-sff_status launch_rec_pick(int pick, const MatchArgs& a, int iters, hipStream_t st) {
-    switch (pick) {
-        case 0: return launch_level<C, LaneEval<C>>(a, iters, st);
-        case 1: return launch_level<C, PatchCoop<RecMap<C>, 2, 3>>(a, iters, st);
-        case 2: return launch_level<C, PatchCoop<RecMap<C>, 4, 3>>(a, iters, st);
-        case 3: return launch_level<C, PatchCoop<RecMap<C>, 2, 3, 32>>(a, iters, st);
-        case 4: return launch_level<C, PatchCoop<RecMap<C>, 4, 3, 32>>(a, iters, st);
-        case 6:  // 16-owner waves need 4 or 8 pieces a record
-            if constexpr (C % 2 == 0)
-                return launch_level<C, PatchCoop<RecMap<C>, 4, 6, 16, true>>(a, iters, st);
-            else
-                return launch_level<C, PatchCoop<RecMap<C>, 4, 3, 32, true>>(a, iters, st);
-        default: return launch_level<C, PatchCoop<RecMap<C>, 4, 6, 32>>(a, iters, st);
+sff_status launch_rec_shape(RecShape shape, const MatchArgs& a, int iters, hipStream_t st) {
+    switch (shape) {
+        case RecShape::kLane: return launch_level<C, LaneEval<C>>(a, iters, st);
+        case RecShape::k46x32: return launch_level<C, PatchCoop<RecMap<C>, 4, 6, 32>>(a, iters, st);
+        case RecShape::kSmall: break;
     }
+    if constexpr (C % 2 == 0)  // 16-owner waves need 4 or 8 pieces a record
+        return launch_level<C, PatchCoop<RecMap<C>, 4, 6, 16, true>>(a, iters, st);
+    else
+        return launch_level<C, PatchCoop<RecMap<C>, 4, 3, 32, true>>(a, iters, st);
 }
 
 // Record evaluators by launch size (updates per half-step).  One level's records
@@ -888,33 +883,24 @@ sff_status launch_rec_pick(int pick, const MatchArgs& a, int iters, hipStream_t 
 // 0.148 ms with a gather per lane, 0.113 in groups of 4/6 view by view, 0.101).
 // One candidate at a time with its views in one round (the bins' choice for large
 // launches): 1.63 at 446,464 updates.
-// SFF_MATCH_EVAL = "lane" (each lane gathers its own records), "coop-narrow",
-// "coop-wide" (groups of 2/3 and 4/3, 64 owners), "coop-narrow-32",
-// "coop-wide-32" (32 owners), "coop-46-32" or "coop-xts" (the two above) forces an
-// evaluator, SFF_MATCH_SPLIT the split (all give identical results; the switches
-// exist to test and time each one); anything else: auto.
+// SFF_MATCH_EVAL = "lane" (each lane gathers its own records), "coop-xts" (the
+// smallest calls' shape) or "coop-46-32" (also by the names of cooperative shapes that
+// are no longer built) forces an evaluator, SFF_MATCH_SPLIT the split (identical
+// results; to test and time each); anything else: by launch size.
 constexpr long kRecSplitMaxUpdates = 1000000;
 template <int C>
 sff_status run_level(const MatchArgs& a, int iters, hipStream_t st) {
     const long updates = (long)a.ndir * a.batch * a.Hk * ((a.Wk + 1) / 2);
-    int pick = updates < kHalfOwnersMaxUpdates ? 6 : 5;
-    bool split = a.ndir == 2 && updates >= kSplitMinUpdates && updates < kRecSplitMaxUpdates;
-    if (const char* e = std::getenv("SFF_MATCH_EVAL")) {
-        if (std::strcmp(e, "lane") == 0) pick = 0;
-        if (std::strcmp(e, "coop-narrow") == 0) pick = 1;
-        if (std::strcmp(e, "coop-wide") == 0) pick = 2;
-        if (std::strcmp(e, "coop-narrow-32") == 0) pick = 3;
-        if (std::strcmp(e, "coop-wide-32") == 0) pick = 4;
-        if (std::strcmp(e, "coop-46-32") == 0) pick = 5;
-        if (std::strcmp(e, "coop-xts") == 0) pick = 6;
-    }
-    if (const char* e = std::getenv("SFF_MATCH_SPLIT")) {
-        if (std::strcmp(e, "0") == 0) split = false;
-        if (std::strcmp(e, "1") == 0) split = a.ndir == 2;
-    }
-    if (a.img_bytes > kMaxCoopMapBytes) pick = 0;
-    if (!split) return launch_rec_pick<C>(pick, a, iters, st);
-    return run_split(a, st, [&](const MatchArgs& f, hipStream_t fs) { return launch_rec_pick<C>(pick, f, iters, fs); });
+    RecShape shape = updates < kHalfOwnersMaxUpdates ? RecShape::kSmall : RecShape::k46x32;
+    const int eval = env_choice("SFF_MATCH_EVAL", {"lane", "coop-xts", "coop-46-32",  // as listed
+                                                   "coop", "coop-narrow", "coop-wide", "coop-narrow-32", "coop-wide-32"});
+    if (eval >= 0) shape = (RecShape)std::min(eval, (int)RecShape::k46x32);
+    if (a.img_bytes > kMaxCoopMapBytes) shape = RecShape::kLane;
+    const int forced = env_choice("SFF_MATCH_SPLIT", {"0", "1"});
+    const bool split =
+        a.ndir == 2 && (forced >= 0 ? forced == 1 : updates >= kSplitMinUpdates && updates < kRecSplitMaxUpdates);
+    if (!split) return launch_rec_shape<C>(shape, a, iters, st);
+    return run_split(a, st, [&](const MatchArgs& f, hipStream_t fs) { return launch_rec_shape<C>(shape, f, iters, fs); });
 }
 
 }  // namespace
