@@ -623,8 +623,8 @@ __global__ void __launch_bounds__(64) half_step_kernel(MatchArgs a, int it, int 
             return c;
         };
         auto sample = [&](int t) { return offset(t, draw(t, jj)); };
-        // `left` samples from t on, at most G: one group
-        auto group = [&](auto size, int t, int left) {
+        // samples t .. t + G - 1 as one group
+        auto group = [&](auto size, int t) {
             constexpr int G = decltype(size)::value;
             Hyp cg[G];
             bool wg[G];
@@ -656,7 +656,7 @@ __global__ void __launch_bounds__(64) half_step_kernel(MatchArgs a, int it, int 
             }
 #pragma unroll
             for (int m = 0; m < G; ++m) {
-                wg[m] = act && m < left && !same(cg[m], centre);
+                wg[m] = act && !same(cg[m], centre);
                 any = any || wg[m];
             }
             if (!__any(any)) return;
@@ -665,20 +665,23 @@ __global__ void __launch_bounds__(64) half_step_kernel(MatchArgs a, int it, int 
 #pragma unroll
             for (int m = 0; m < G; ++m) take(wg[m], cg[m], cc[m]);
         };
-        // Whole groups (of 6, also one that lacks a single sample), then half a group of
-        // 6, then the rest one by one.  us for 3 to 5 samples, three iterations, records
-        // 375 x 1242: 417, 441, 481 (the rest of a group of 6 one by one 433, 482, 535;
-        // always a whole group 439, 448, 461); bins 97 x 161: 60, 65, 72 (63, 68, 74;
-        // 71, 71, 72).  Two samples in a group of 3: 122 us, one by one 116 (bins 240 x 400).
-        constexpr int kRS = E::kRG, kFull = kRS >= 6 ? kRS - 1 : kRS, kHalf = kRS >= 6 ? kRS / 2 : 1;
+        // Whole groups; what is left of a group of 6 as one of 5 or 3; then one by one.
+        // us for 3 to 5 samples, three iterations, records 375 x 1242: 410, 437, 454 (all
+        // one by one 433, 482, 535; in a group of 6 with places to spare 439, 448, 461);
+        // bins 97 x 161: 60, 66, 70 (63, 68, 74; 71, 71, 72).  Two samples in a group of 3:
+        // 122 us, one by one 116 (bins 240 x 400).
+        constexpr int kRS = E::kRG;
         for (int t = 0; t < a.rs_samples;) {
             const int left = a.rs_samples - t;
-            if (kRS > 1 && left >= kFull) {
-                group(std::integral_constant<int, kRS>{}, t, left);
+            if (kRS > 1 && left >= kRS) {
+                group(std::integral_constant<int, kRS>{}, t);
                 t += kRS;
-            } else if (kHalf > 1 && left >= kHalf) {
-                group(std::integral_constant<int, kHalf>{}, t, kHalf);
-                t += kHalf;
+            } else if (kRS == 6 && left == 5) {
+                group(std::integral_constant<int, kRS == 6 ? 5 : 1>{}, t);
+                t += 5;
+            } else if (kRS == 6 && left >= 3) {
+                group(std::integral_constant<int, kRS == 6 ? 3 : 1>{}, t);
+                t += 3;
             } else {
                 const Hyp c0 = sample(t);
                 const bool w0 = act && !same(c0, centre);
