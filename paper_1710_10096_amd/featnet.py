@@ -44,25 +44,41 @@ class FeatNet:
     def weights_bf16(self):
         return [self.params[2 * l].to(torch.bfloat16).contiguous() for l in range(4)]
 
+    # Pixels from which four launches beat the one that keeps the activations on chip:
+    # us of forward at 62,468 / 400,000 / 480,000 / 1,863,000 pixels 23 / 65 / 85 / 252 in
+    # one launch and 42 / 73 / 77 / 171 layer by layer; of records 27 / 83 / 103 / 297 and
+    # 41 / 75 / 80 / 188 (150,000: 50 and 51).
+    ONE_LAUNCH_PX, ONE_LAUNCH_RECORDS_PX = 430_000, 150_000
+
+    @staticmethod
+    def _pixels(x: torch.Tensor) -> int:
+        return x.shape[0] * x.shape[1] * x.shape[2]
+
+    def _one_launch(self, x: torch.Tensor, wb):
+        return api.sff_featnet_fwd_bf16(x, wb, [self.params[2 * l + 1] for l in range(4)])
+
     def forward(self, x: torch.Tensor, dil: int = 1, keep: bool = False, wb=None):
         """x bf16 [n][H][W][3] -> bf16 [n][H][W][32] (and the activations).
-        Without `keep`, at dilation 1, the four layers run as one launch with the
-        activations on chip (same bits as the per-layer calls)."""
+        Without `keep`, at dilation 1, small calls run the four layers as one launch with
+        the activations on chip (same bits as the per-layer calls)."""
         wb = wb if wb is not None else self.weights_bf16()
-        if not keep and dil == 1:
-            return api.sff_featnet_fwd_bf16(x, wb, [self.params[2 * l + 1] for l in range(4)])
+        if not keep and dil == 1 and self._pixels(x) < self.ONE_LAUNCH_PX:
+            return self._one_launch(x, wb)
         acts = [x]
         h = x
         for l in range(4):
             h = api.sff_conv3x3_bf16_fwd(h, wb[l], self.params[2 * l + 1], dil, relu=l < 3)
-            acts.append(h)
+            if keep:
+                acts.append(h)
         return (h, acts) if keep else h
 
     def records(self, x: torch.Tensor, dil: int, scale: float, desc: torch.Tensor, wb=None):
         """The quantised features of `forward` (sff_quantise_features) into desc
         int16 [n][H][W][2][16]; the last layer writes them without the features in
-        memory."""
+        memory (small calls at dilation 1: the network in one launch, then the records)."""
         wb = wb if wb is not None else self.weights_bf16()
+        if dil == 1 and self._pixels(x) < self.ONE_LAUNCH_RECORDS_PX:
+            return api.sff_quantise_features(self._one_launch(x, wb), scale, desc)
         h = x
         for l in range(3):
             h = api.sff_conv3x3_bf16_fwd(h, wb[l], self.params[2 * l + 1], dil, relu=True)
