@@ -528,7 +528,7 @@ __global__ void __launch_bounds__(256) grad_target_kernel(CostArgs a, int k, siz
 // gathered feature vectors; then CF / 4 lanes (four channels each) per part
 // of the window rows and row_split(CF) parts per entry gather the vectors and
 // add the same terms in the same order as the one-thread kernels (each part
-// alone, then the parts in order by a shuffle), so the results are identical.
+// alone, then the parts in pairs by exchanges), so the results are identical.
 // Tiles are numbered ((map * batch + b) * H + row) * tiles_x + column tile and
 // given out by XCD, so an XCD's L2 holds a band of rows.
 constexpr int kTileQ = 32;
@@ -831,8 +831,9 @@ __global__ void __launch_bounds__(256) grad_target_tile_kernel(CostArgs a, int t
         return make_uint2(Map::template unit<L>(clampi(py + wy, 0, H - 1) * W + clampi(px + wx, 0, W - 1)),
                           __float_as_uint(-g2));
     };
-    // The N U-th terms of this lane's accumulator in the block starting at term i0 of
-    // the table at `tab`, all loads in flight together; m terms in all.
+    // N terms of this lane's accumulator from the table at `tab`, which holds the terms
+    // from i0 on: part, part + kSplit, ..., all loads in flight together.  The entry has m
+    // terms in all; table places past them are left out.
     auto add_terms = [&](auto count, const uint2* tab, uint32_t i0, uint32_t m, const float4& fq, float4& acc) {
         constexpr int N = decltype(count)::value;
         uint2 tt[N];
