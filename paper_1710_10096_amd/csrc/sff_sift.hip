@@ -13,10 +13,10 @@
 // nor the normalised descriptor.
 //
 // Pipeline of sff_sift_pca: cell-sum planes -> Gram
-// matrix and sum of all descriptors of the pair (FP64 accumulation, partial
-// per block, reduced in a fixed order) -> covariance -> the three leading
-// eigenvectors (subspace iteration on a power of the covariance, in one
-// block) -> projected features.
+// matrix and sum of all descriptors of the pair (exact digit products, FP64 for
+// descriptors with very small entries; a partial per block, reduced in a fixed
+// order) -> covariance -> the three leading eigenvectors (subspace iteration on a
+// power of the covariance in one block, or a direct solution) -> projected features.
 // Descriptors are recomputed from the cell-sum planes in the Gram and the
 // projection pass instead of being stored (512 B per pixel).
 #include <cmath>
